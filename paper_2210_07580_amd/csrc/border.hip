@@ -213,7 +213,7 @@ __device__ __forceinline__ void border_grid(const GridView& gv, const CoreOut& c
                 }
             }
             const uint32_t incl = wave_incl_scan(cn);
-            const uint32_t tot = __shfl(incl, kWave - 1);
+            const uint32_t tot = last_lane(incl);
             if (tot == 0) continue;
             s_start[lane] = cs;
             s_excl[lane] = incl - cn;
@@ -254,25 +254,25 @@ __device__ __forceinline__ void border_grid(const GridView& gv, const CoreOut& c
     }
 }
 
-// Reductions within groups of S lanes (S a power of two up to 64).
+// Reductions within groups of S lanes.
 template <int S>
 __device__ __forceinline__ uint32_t group_incl_scan(uint32_t v) {
-    const int sub = lane_id() % S;
-#pragma unroll
-    for (int o = 1; o < S; o <<= 1) {
-        const uint32_t t = __shfl_up(v, o, S);
-        if (sub >= o) v += t;
-    }
+    static_assert(S == 16, "a group is a row of 16 lanes (see dpp)");
+    v += dpp<kRowShr + 1>(0u, v);
+    v += dpp<kRowShr + 2>(0u, v);
+    v += dpp<kRowShr + 4>(0u, v);
+    v += dpp<kRowShr + 8>(0u, v);
     return v;
 }
 
 template <int S>
 __device__ __forceinline__ uint64_t group_min_u64(uint64_t v) {
-#pragma unroll
-    for (int o = S / 2; o > 0; o >>= 1) {
-        const uint64_t t = __shfl_xor(v, o, S);
-        v = t < v ? t : v;
-    }
+    static_assert(S == 16, "a group is a row of 16 lanes (see dpp)");
+    auto low = [](uint64_t a, uint64_t b) { return b < a ? b : a; };
+    v = low(v, dpp<kRowRor + 8>(v, v));
+    v = low(v, dpp<kRowRor + 4>(v, v));
+    v = low(v, dpp<kRowRor + 2>(v, v));
+    v = low(v, dpp<kRowRor + 1>(v, v));
     return v;
 }
 

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
                 if (cn >= 16u * kWave && !cell_near<D>(gv, cc, active, qx, side, lim)) cn = 0;
             }
             const uint32_t incl = wave_incl_scan(cn);
-            const uint32_t tot = __shfl(incl, kWave - 1);
+            const uint32_t tot = last_lane(incl);
             s_start[w][lane] = cs;
             s_excl[w][lane] = incl - cn;
             wave_sync();

@@ -204,12 +204,7 @@ __device__ __forceinline__ typename Dist<kWide>::T nearest(const PointSet& s, co
 }
 
 __device__ __forceinline__ float wave_min_f32(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float t = __shfl_xor(v, o);
-        v = t < v ? t : v;
-    }
-    return v;
+    return wave_reduce(v, [](float a, float b) { return b < a ? b : a; });
 }
 
 // Rounding slack of the single-precision angle rule.  Every operand is an

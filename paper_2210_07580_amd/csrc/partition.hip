@@ -131,11 +131,8 @@ __device__ __forceinline__ void minmax_tile(Inst& I, int64_t lo, int64_t hi, int
 #pragma unroll
     for (int j = 0; j < D; ++j) {
         int a = lmn[j], c = lmx[j];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            a = min(a, __shfl_xor(a, o));
-            c = max(c, __shfl_xor(c, o));
-        }
+        a = wave_reduce(a, [](int x, int y) { return min(x, y); });
+        c = wave_reduce(c, [](int x, int y) { return max(x, y); });
         if (lane_id() == 0) {
             smn[wave_id() * kMaxD + j] = a;
             smx[wave_id() * kMaxD + j] = c;
