@@ -72,7 +72,8 @@ typedef struct {
     int32_t d;
     int32_t key_bits;          /* bits of the packed grid identifier */
     int64_t grids;             /* |Gs|: non-empty grids */
-    int64_t neighbor_entries;  /* sum over grids of |Nei(g)| */
+    int64_t neighbor_entries;  /* sum over grids of |Nei(g)| (counted by gd_get_stats when the
+                                  call did not write the lists) */
     int64_t core_points;
     int64_t core_grids;
     int64_t dense_grids;       /* grids with >= MinPts points (all core) */
@@ -227,7 +228,9 @@ typedef enum {
                                  most 8 points and border assignment each walk
                                  the grid tree for their own grid (lists only
                                  for grids with more core points: far less
-                                 memory, slower); 0 (default) lists, or walks
+                                 memory, slower); 0 (default) lists (from four
+                                 dimensions on, sparse grids instead share
+                                 lists of grid-tree nodes), or walks
                                  when the lists would not fit the workspace
                                  (GD_OPT_WORKSPACE_LIMIT, or the fixed array
                                  of dbscan_noalloc).  The result is the same in
@@ -328,7 +331,8 @@ int gd_autotune(gd_ctx *ctx, const gd_instance *inst, int32_t count, void *strea
  */
 int gd_set_tuning_file(gd_ctx *ctx, const char *path);
 
-/* Copy the counters of the last successful dbscan() call. */
+/* Copy the counters of the last successful dbscan() call (counting the entries
+ * of its neighbour lists on the device if the call did not need them). */
 int gd_get_stats(gd_ctx *ctx, gd_stats *out);
 
 /* Phases of dbscan() timed with GD_OPT_TIMING. */

@@ -41,7 +41,8 @@ struct DevBuf {
 // The workspace buffers a call grows on demand.
 struct Bufs {
     DevBuf arena;   // everything sized by the batch's points and dimension
-    DevBuf nei;     // the neighbour lists, sized by their total
+    DevBuf nei;     // the neighbour lists (or the families' node lists), sized by their total
+    DevBuf mid;     // node lists of every other tree level while they are built
     DevBuf table;   // identifier -> label hash table of the output pass
     DevBuf sumbuf;  // CellSummary per grid (learned proposal)
     DevBuf huge;    // queue and device-memory bitmaps for core sets beyond the LDS bitmaps
@@ -118,6 +119,11 @@ struct gd_ctx {
     int nei_query = kNeiAuto;      // GD_OPT_NEIGHBOR_QUERY (kNeiAuto for option value 0)
     bool last_walk = false;        // the last eager call walked (no full lists)
     bool last_wide = false;        // the last eager call took 64-bit distances
+    bool last_runs = false;        // the last eager call found neighbours as runs (no lists per grid)
+    bool last_by_level = false;    // ... built its lists level by level
+    int64_t last_nodes[kMaxLevels] = {};  // its tree nodes per level, lanes per node and
+    int last_lanes[kMaxLevels] = {};      // largest node-list total per buffer
+    uint64_t last_ents[2] = {};
     gd_stats last{};
     // what the last successful call left in the workspace (for gd_debug_*)
     bool have_last = false;
@@ -164,6 +170,21 @@ struct gd_ctx {
     bool ran[P_COUNT] = {};
     double phase_ms[P_COUNT] = {};
     hipStream_t st = nullptr;
+    // What counting or writing Nei(g) per grid needs, after a call that found
+    // the neighbours as runs: gd_get_stats, gd_debug_neighbors and
+    // gd_proposal_harvest ask for it, the call itself does not.
+    struct Lists {
+        bool pending = false;  // neighbor_entries not counted yet
+        bool missing = false;  // lists not written yet
+        GridView g{};
+        TreeView t{};
+        uint32_t* off_counts = nullptr;
+        uint64_t* nei_off = nullptr;
+        uint64_t* partial = nullptr;
+        uint2* nei_up = nullptr;
+    };
+    Lists lists;       // of the last call
+    Lists plan_lists;  // of a replay of the captured graph
 
     void mark(int phase, int which) {
         if (!timing || !events_ok || !marking) return;
@@ -249,6 +270,27 @@ int grow(gd_ctx* ctx, DevBuf& b, size_t need, size_t other_held) {
     return GD_OK;
 }
 
+void release(gd_ctx* ctx, DevBuf& b) {
+    if (!b.p) return;
+    (void)hipFree(b.p);
+    b = DevBuf{};
+    ++ctx->generation;
+}
+
+// The context's own stream (graph replays, counts and lists asked for after
+// a call) and its event.
+bool own_stream(gd_ctx* ctx) {
+    if (ctx->gstream) return true;
+    if (hipStreamCreateWithFlags(&ctx->gstream, hipStreamNonBlocking) == hipSuccess &&
+        hipEventCreateWithFlags(&ctx->gev, hipEventDisableTiming) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    if (ctx->gstream) (void)hipStreamDestroy(ctx->gstream);
+    ctx->gstream = nullptr;
+    ctx->gev = nullptr;
+    return false;
+}
+
 int bit_length(uint64_t v) { return v == 0 ? 0 : 64 - __builtin_clzll(v); }
 
 // Capacities of a sync-free run (see run_batch).
@@ -259,6 +301,11 @@ struct Plan {
     int64_t ncc;       // core grids
     int64_t max_core;  // largest core set
     bool walk;         // consumers walk the grid tree (lists only for big core sets)
+    bool runs;         // neighbours as runs: node lists instead of neighbour lists
+    bool by_level;     // neighbour lists built level by level
+    uint64_t ents[2];            // entries per node-list buffer
+    int64_t nodes[kMaxLevels];   // tree nodes per level
+    int lanes[kMaxLevels];       // lanes per node in the build
 };
 
 // Largest delta of approximate merging: (eps + delta)^2 must fit 32 bits.
@@ -327,7 +374,9 @@ struct Layout {
 // Bytes of a packed identifier of `bits` bits: one 32- or 64-bit word, or two.
 int key_bytes_of(int bits) { return bits <= 32 ? 4 : bits <= 64 ? 8 : 16; }
 
-Layout carve(char* base, int64_t n, int D, uint32_t tiles, int key_bytes = 8) {
+// exact: the size without the word that only node lists need (for workspaces
+// of a fixed size, which do not use them).
+Layout carve(char* base, int64_t n, int D, uint32_t tiles, int key_bytes, bool exact) {
     Layout L{};
     Carve c{base};
     const int64_t kw = std::max(key_bytes, 8) / 8;  // identifier buffers hold n 64-bit words, or 2n
@@ -351,7 +400,7 @@ Layout carve(char* base, int64_t n, int D, uint32_t tiles, int key_bytes = 8) {
     }
     L.off_counts = c.take<uint32_t>((int64_t)D * n);
     L.nei_off = c.take<uint64_t>(n + 1);
-    L.nei_up = c.take<uint2>(n);
+    L.nei_up = c.take<uint2>(n + (exact ? 0 : 1));
     L.core = c.take<uint8_t>(n);
     L.core_cnt = c.take<uint32_t>(n);
     L.core_begin = c.take<uint32_t>(n);
@@ -371,6 +420,48 @@ Layout carve(char* base, int64_t n, int D, uint32_t tiles, int key_bytes = 8) {
 int readback(gd_ctx* ctx, hipStream_t st) {
     GD_TRY(hipMemcpyAsync(ctx->hdr_host, ctx->hdr_dev, sizeof(Header), hipMemcpyDeviceToHost, st));
     GD_TRY(hipStreamSynchronize(st));
+    return GD_OK;
+}
+
+NeiQuery walk_order_query(const TreeView& t) {
+    NeiQuery nq{};
+    nq.t = t;
+    nq.kind = kNeiTreeWalkOrder;
+    return nq;
+}
+
+// After a call that found the neighbours as runs: counts sum |Nei(g)| into
+// the statistics (the call's tree is still in the workspace).
+int count_entries(gd_ctx* ctx) {
+    gd_ctx::Lists& a = ctx->lists;
+    if (!a.pending) return GD_OK;
+    DeviceGuard guard(ctx->device);
+    if (!guard.ok || !own_stream(ctx)) return ctx->fail(GD_EDEVICE, "no stream to count the neighbour lists on");
+    hipStream_t st = ctx->gstream;
+    GD_TRY(launch_nei_count(a.g, walk_order_query(a.t), a.off_counts, nullptr, nullptr, st));
+    GD_TRY(launch_nei_offsets(a.g, a.off_counts, a.nei_off, a.partial, st));
+    int rc;
+    if ((rc = readback(ctx, st))) return rc;
+    ctx->last.neighbor_entries = (int64_t)ctx->hdr_host->nei_total;
+    a.pending = false;
+    return GD_OK;
+}
+
+// And the lists themselves, for the views that read them.
+int write_lists(gd_ctx* ctx) {
+    gd_ctx::Lists& a = ctx->lists;
+    if (!a.missing) return GD_OK;
+    int rc;
+    if ((rc = count_entries(ctx))) return rc;
+    const uint64_t total = (uint64_t)ctx->last.neighbor_entries;
+    if ((rc = grow(ctx, ctx->own.nei, (size_t)std::max<uint64_t>(total, 1) * sizeof(uint32_t), ctx->own.arena.cap)))
+        return rc;
+    GD_TRY(launch_nei_fill(a.g, walk_order_query(a.t), a.off_counts, nullptr, a.nei_off, (uint32_t*)ctx->own.nei.p,
+                           total, nullptr, a.nei_up, ctx->gstream));
+    GD_TRY(hipStreamSynchronize(ctx->gstream));
+    ctx->last_nei = (const uint32_t*)ctx->own.nei.p;
+    ctx->last_nei_total = total;
+    a.missing = false;
     return GD_OK;
 }
 
@@ -525,6 +616,7 @@ int run_bfs(gd_ctx* ctx, const GridView& g, const CoreOut& co, const uint64_t* n
 // a HIP graph; device-side checks raise kErrPlan when the data outgrow it.
 int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStream_t st, const Plan* plan) {
     ctx->have_last = false;
+    if (!plan) ctx->lists = gd_ctx::Lists{};
     std::memset(&ctx->last, 0, sizeof(ctx->last));
     ctx->last.n = n;
     ctx->last.d = D;
@@ -532,10 +624,12 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
 
     // ---- workspace (identifiers of one word; two once the layout needs them)
     int kbytes = plan ? key_bytes_of(plan->key_bits) : 8;
-    Layout L = carve(nullptr, n, D, tiles, kbytes);
+    // a bounded workspace keeps to the lists it was sized for
+    const bool bounded = ctx->bump_base || ctx->ws_limit > 0;
+    Layout L = carve(nullptr, n, D, tiles, kbytes, bounded);
     int rc = plan ? GD_OK : grow(ctx, ctx->cur->arena, L.bytes, ctx->cur->nei.cap);
     if (rc) return rc;
-    L = carve((char*)ctx->cur->arena.p, n, D, tiles, kbytes);
+    L = carve((char*)ctx->cur->arena.p, n, D, tiles, kbytes, bounded);
     Header* Hd = ctx->hdr_dev;
     Header* H = ctx->hdr_host;
 
@@ -582,8 +676,9 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         // two-word identifiers: the identifier buffers double (the min/max
         // records, the only data so far, are folded into the instance table)
         kbytes = key_bytes_of(key_bits);
-        if ((rc = grow(ctx, ctx->cur->arena, carve(nullptr, n, D, tiles, kbytes).bytes, ctx->cur->nei.cap))) return rc;
-        L = carve((char*)ctx->cur->arena.p, n, D, tiles, kbytes);
+        if ((rc = grow(ctx, ctx->cur->arena, carve(nullptr, n, D, tiles, kbytes, bounded).bytes, ctx->cur->nei.cap)))
+            return rc;
+        L = carve((char*)ctx->cur->arena.p, n, D, tiles, kbytes, bounded);
     }
     // the narrowest word that holds the identifiers (32-bit identifiers sort
     // and carry packed rows as one-word keys; the buffers carved for a wider
@@ -631,9 +726,39 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     g.ck = L.ck;
     g.ck_stride = n;
 
+    int64_t max_eps = 0, min_minpts = INT64_MAX;
+    for (int k = 0; k < count; ++k) {
+        max_eps = std::max<int64_t>(max_eps, ctx->inst_host[k].eps);
+        min_minpts = std::min<int64_t>(min_minpts, ctx->inst_host[k].minpts);
+    }
+    // eps above the 32-bit bound anywhere in the batch: 64-bit distances
+    const bool wide = max_eps > GD_EPS_MAX;
+    const bool prune = n >= 1024 * std::max<int64_t>(ncell, 1);
+    // offset order pays for itself through core marking's early exit only
+    // when grids hold several points; sparse grids take walk order, and so do
+    // more than 2^19 grids, whose ordered fill (scattered over the offset
+    // buckets) outweighs the early exit
+    const bool sparse = !(ncell <= ((int64_t)1 << 19) && n >= 8 * std::max<int64_t>(ncell, 1));
+    // Sparse grids in four dimensions and more: neighbours as runs, from lists
+    // of tree nodes (runs.hpp), unless the lists per grid were asked for or
+    // something reads them: an option, the BFS order, the learned proposal,
+    // the counters of the work done on them.  A bounded workspace and 64-bit
+    // distances keep the lists.  In two and three dimensions the lists are
+    // short, and the same levels end in them (nodes.hip); in two dimensions
+    // that takes no further memory.
+    bool runs = plan ? plan->runs
+                     : D >= kMinRunD && sparse && ctx->nei_query == kNeiAuto && ctx->nei_mode == 0 && !ctx->bfs &&
+                           !stats && !ctx->proposal_on && !bounded && !wide && !prune && ncell < kMaxRunNodes;
+    bool by_level = plan ? plan->by_level
+                         : (D == 2 || (D == 3 && !bounded)) && !(!ctx->bfs && ctx->nei_mode == 2) &&
+                               (ctx->nei_query == kNeiTreeWalkOrder || (ctx->nei_query == kNeiAuto && sparse)) &&
+                               ncell < kMaxRunNodes;
+
     // ---- Algorithm 2 (grid tree) and Algorithm 3 (Nei for every grid)
+    uint32_t* tpar[kMaxLevels] = {};
+    for (int l = 1; l < D && (runs || by_level); ++l) tpar[l] = L.off_counts + (int64_t)(l - 1) * n;
     ctx->mark(P_TREE, 0);
-    GD_TRY(launch_tree(g, L.level_excl, (uint32_t*)L.partial, L.tkey, L.tchild, st));
+    GD_TRY(launch_tree(g, L.level_excl, (uint32_t*)L.partial, L.tkey, L.tchild, tpar, st));
     ctx->mark(P_TREE, 1);
     TreeView t{};
     for (int l = 0; l < D; ++l) {
@@ -657,13 +782,8 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     auto build_lists = [&](const uint32_t* only_big, bool fallback) -> int {
         NeiQuery nq{};
         nq.t = t;
-        // offset order pays for itself through core marking's early exit
-        // only when grids hold several points; sparse grids take walk order,
-        // and so do more than 2^19 grids, whose ordered fill (scattered over
-        // the offset buckets) outweighs the early exit
         int kind = ctx->nei_query;
-        if (kind == kNeiAuto)
-            kind = ncell <= ((int64_t)1 << 19) && n >= 8 * std::max<int64_t>(ncell, 1) ? kNeiTree : kNeiTreeWalkOrder;
+        if (kind == kNeiAuto) kind = sparse ? kNeiTreeWalkOrder : kNeiTree;
         nq.kind = only_big ? kNeiTree : kind;
         nq.key_bytes = kbytes;
         nq.inst = b.inst;
@@ -697,11 +817,17 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         nei_total = plan ? plan->nei : H->nei_total;
         if (!plan && (rc2 = grow(ctx, ctx->cur->nei, (size_t)std::max<uint64_t>(nei_total, 1) * sizeof(uint32_t),
                                  ctx->cur->arena.cap))) {
+            // the node lists of an earlier call are in the way of these
+            if (rc2 == GD_ENOMEM && ctx->cur->mid.p) {
+                release(ctx, ctx->cur->mid);
+                ctx->err.clear();
+                rc2 = grow(ctx, ctx->cur->nei, (size_t)nei_total * sizeof(uint32_t), ctx->cur->arena.cap);
+            }
             if (fallback && rc2 == GD_ENOMEM) {
                 ctx->err.clear();
                 return kListsDoNotFit;
             }
-            return rc2;
+            if (rc2) return rc2;
         }
         nei = (uint32_t*)ctx->cur->nei.p;
         ctx->mark(P_NEI_FILL, 0);
@@ -710,34 +836,125 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         ctx->mark(P_NEI_FILL, 1);
         return GD_OK;
     };
-    if (!walk) {
+    // The node lists of the levels 2 .. last, each from the one before: the
+    // last is level D-1 (runs) or D, the grids themselves.
+    RunSource rsrc{};
+    // the grids' ranges of larger neighbours: D == 2 has no level before the
+    // last, whose offsets nei_up would hold; at D == 3 the parents are done with
+    uint2* const grid_up = D == 2 ? L.nei_up : (uint2*)L.off_counts;
+    double visits = kNear;  // entries per list of the level before (level 1: places around a node)
+    auto build_levels = [&](int last) -> int {
+        NodeLists nl{};
+        for (int l = 1; l < D; ++l) nl.par[l] = tpar[l];
+        nl.excl = L.level_excl + (int64_t)(D - 1) * (g.ncell + 1);
+        nl.near = last < D ? L.off_counts + (int64_t)(D - 1) * n : nullptr;
+        const int fin = last & 1;
+        DevBuf* buf[2];
+        buf[fin] = &ctx->cur->nei;
+        buf[1 - fin] = &ctx->cur->mid;
+        nl.off[fin] = L.nei_off;
+        nl.off[1 - fin] = (uint64_t*)L.nei_up;
+        nl.cnt = L.side_off;
+        nl.up = grid_up;
+        int rc2;
+        int64_t nodes[kMaxLevels];
+        for (int l = 0; l < kMaxLevels; ++l) nodes[l] = plan ? plan->nodes[l] : ncell;
+        if (plan) {
+            for (int p = 0; p < 2; ++p) {
+                nl.ent[p] = (uint32_t*)buf[p]->p;
+                nl.cap[p] = plan->ents[p];
+            }
+        } else {
+            ctx->last_ents[0] = ctx->last_ents[1] = 0;
+        }
+        // the node counts are worth a read-back where a launch over every
+        // grid would not be
+        bool known = plan != nullptr;
+        auto read_nodes = [&]() {
+            for (int l = 0; l <= D; ++l) nodes[l] = (int64_t)H->level_count[l];
+            known = true;
+        };
+        ctx->mark(P_NEI_COUNT, 0);
+        if (!known && last >= 3 && ncell > 65536) {
+            if ((rc2 = readback(ctx, st))) return rc2;
+            read_nodes();
+        }
+        for (int l = 2; l <= last; ++l) {
+            // (a grid of three dimensions has at most 25 parents' entries)
+            const int lanes = plan ? plan->lanes[l] : visits <= 12 ? 8 : visits <= 24 || l == D ? 16 : kWave;
+            if (plan) GD_TRY(launch_plan_check(Hd, 3, l, plan->nodes[l], st));
+            GD_TRY(launch_level_count(g, t, nl, l, nodes[l], lanes, L.partial, st));
+            if (plan) {
+                GD_TRY(launch_plan_check(Hd, 1, (int64_t)plan->ents[l & 1], 0, st));
+            } else {
+                if ((rc2 = readback(ctx, st))) return rc2;
+                if (!known) read_nodes();
+                const uint64_t total = std::max<uint64_t>(H->nei_total, 1);
+                if ((rc2 = grow(ctx, *buf[l & 1], (size_t)total * sizeof(uint32_t), ctx->cur->arena.cap))) {
+                    if (rc2 != GD_ENOMEM) return rc2;
+                    ctx->err.clear();
+                    release(ctx, ctx->cur->mid);
+                    return kListsDoNotFit;
+                }
+                nl.ent[l & 1] = (uint32_t*)buf[l & 1]->p;
+                nl.cap[l & 1] = total;
+                ctx->last_ents[l & 1] = std::max(ctx->last_ents[l & 1], total);
+                ctx->last_lanes[l] = lanes;
+                visits = (double)total / (double)std::max<int64_t>(nodes[l], 1);
+                if (l == D) nei_total = H->nei_total;
+            }
+            GD_TRY(launch_level_fill(g, t, nl, l, nodes[l], lanes, st));
+        }
+        ctx->mark(P_NEI_COUNT, 1);
+        if (!plan)
+            for (int l = 0; l < kMaxLevels; ++l) ctx->last_nodes[l] = nodes[l];
+        if (last == D) {
+            nei = nl.ent[fin];
+            if (plan) nei_total = plan->ents[fin];
+            lists_up = true;
+        } else {
+            rsrc.t = t;
+            rsrc.excl = nl.excl;
+            rsrc.off = nl.off[fin];
+            rsrc.ent = nl.ent[fin];
+            rsrc.near = nl.near;
+            rsrc.families = nodes[D - 1];
+        }
+        return GD_OK;
+    };
+    if (runs || by_level) {
+        rc = build_levels(runs ? D - 1 : D);
+        if (rc == kListsDoNotFit)
+            runs = by_level = false;
+        else if (rc)
+            return rc;
+    }
+    if (!walk && !runs && !by_level) {
         rc = build_lists(nullptr, may_walk);
         if (rc == kListsDoNotFit)
             walk = true;
         else if (rc)
             return rc;
     }
+    const RunSource* rs = runs ? &rsrc : nullptr;
     ctx->last.neighbor_walk = walk ? 1 : 0;
+    if (!plan) {
+        ctx->last_runs = runs;
+        ctx->last_by_level = by_level;
+    }
     // lanes per grid in the kernels that serve small grids (tiny-set merge,
     // border points): short lists leave most of a wave per grid idle
     const uint64_t grids = (uint64_t)std::max<int64_t>(ncell, 1);
-    const int small_lanes =
-        ctx->grid_lanes ? ctx->grid_lanes : (nei_total <= 40 * grids && (uint64_t)n <= 32 * grids ? 16 : 64);
+    const bool few = nei_total <= 40 * grids;
+    const int small_lanes = ctx->grid_lanes ? ctx->grid_lanes : few && (uint64_t)n <= 32 * grids ? 16 : 64;
 
     // ---- core points
     ctx->mark(P_CORE_MARK, 0);
-    int64_t max_eps = 0, min_minpts = INT64_MAX;
-    for (int k = 0; k < count; ++k) {
-        max_eps = std::max<int64_t>(max_eps, ctx->inst_host[k].eps);
-        min_minpts = std::min<int64_t>(min_minpts, ctx->inst_host[k].minpts);
-    }
-    // eps above the 32-bit bound anywhere in the batch: 64-bit distances
-    const bool wide = max_eps > GD_EPS_MAX;
     if (walk)
         GD_TRY(launch_core_walk(g, t, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr, wide, st));
     else
-        GD_TRY(launch_core_mark(g, L.nei_off, nei, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
-                                max_eps, min_minpts, n >= 1024 * std::max<int64_t>(ncell, 1), st));
+        GD_TRY(launch_core_mark(g, L.nei_off, nei, rs, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
+                                max_eps, min_minpts, prune, st));
     ctx->mark(P_CORE_MARK, 1);
     CoreOut co{};
     co.core = L.core;
@@ -767,7 +984,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     if (!plan && max_core >= kHeavyCore) {
         unsigned long long lists = 0;
         GD_TRY(fill<unsigned long long>(ctx->counter_dev, 1, 0ull, st));
-        GD_TRY(launch_huge_scan(g, co, L.nei_off, ctx->counter_dev, st));
+        GD_TRY(launch_huge_scan(g, co, L.nei_off, rs, ctx->counter_dev, st));
         GD_TRY(hipMemcpyAsync(&lists, ctx->counter_dev, sizeof(lists), hipMemcpyDeviceToHost, st));
         GD_TRY(hipStreamSynchronize(st));
         const uint64_t cap = 2 * (uint64_t)lists + 64;
@@ -792,10 +1009,12 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
 
     // ---- merging (Algorithm 5 + union-find, LDF order)
     uint32_t* ldf = nullptr;
+    uint32_t* free_words = nullptr;  // n words that nothing uses after the order
     {
         // the sort buffer that does not hold the sorted identifiers is free
         uint32_t* ka = (uint32_t*)(skeys == L.keys_b ? L.keys_c : L.keys_b);
         uint32_t* kb = ka + n;
+        free_words = ka;
         uint32_t* vb = (sidx == L.vals_a) ? L.vals_b : L.vals_a;
         ctx->mark(P_LDF, 0);
         // a planned run sorts ncc slots, the unused ones last under an all-ones key
@@ -831,11 +1050,11 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         if (walk)
             GD_TRY(launch_merge_walk(g, co, t, ldf, n_small, L.parent, stats ? ctx->stats_dev->merge : nullptr, wide,
                                      st));
-        GD_TRY(launch_merge(g, co, L.nei_off, nei, lists_up && !walk ? L.nei_up : nullptr, ldf, L.rank, ncc,
-                            n_small, max_core, ctx->merge_waves,
+        GD_TRY(launch_merge(g, co, L.nei_off, nei, !lists_up || walk ? nullptr : by_level ? grid_up : L.nei_up, rs,
+                            ldf, L.rank, ncc, n_small, max_core, ctx->merge_waves,
                             small_lanes, walk,
                             hm.q, wide, L.parent, stats ? ctx->stats_dev->merge : nullptr,
-                            ctx->proposal_on ? ctx->proposal_dev : nullptr, sum, st));
+                            ctx->proposal_on ? ctx->proposal_dev : nullptr, sum, free_words, st));
         GD_TRY(launch_merge_huge(g, co, hm.q, hm.slabs, hm.words, hm.blocks, false, wide, nullptr, nullptr, nullptr,
                                  L.parent, stats ? ctx->stats_dev->merge : nullptr, st));
         ctx->mark(P_MERGE, 1);
@@ -862,11 +1081,22 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     if (walk)
         GD_TRY(launch_border_walk(g, co, t, L.cell_label, wide, st));
     else
-        GD_TRY(launch_output(g, co, L.nei_off, nei, L.cell_label, wide, small_lanes, st));
+        GD_TRY(launch_output(g, co, L.nei_off, nei, rs, L.cell_label, wide, small_lanes, free_words, st));
     ctx->mark(P_OUTPUT, 1);
+    gd_ctx::Lists lists{};
+    if (runs) {
+        lists.pending = lists.missing = true;
+        lists.g = g;
+        lists.t = t;
+        lists.off_counts = L.off_counts;
+        lists.nei_off = L.nei_off;
+        lists.partial = L.partial;
+        lists.nei_up = L.nei_up;
+    }
     if (stats) GD_TRY(hipMemcpyAsync(ctx->stats_host, ctx->stats_dev, sizeof(StatBlock), hipMemcpyDeviceToHost, st));
     if (plan) {
         // the caller synchronises and checks the header
+        ctx->plan_lists = lists;
         GD_TRY(hipMemcpyAsync(ctx->hdr_host, ctx->hdr_dev, sizeof(Header), hipMemcpyDeviceToHost, st));
         return GD_OK;
     }
@@ -883,6 +1113,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     }
 
     ctx->have_last = true;
+    ctx->lists = lists;
     ctx->last_n = n;
     ctx->last_d = D;
     ctx->last_ncell = ncell;
@@ -949,6 +1180,8 @@ void drop_graph(gd_ctx* ctx) {
 
 int ensure_inst_capacity(gd_ctx* ctx, int count) {
     if (count <= ctx->inst_cap) return GD_OK;
+    (void)count_entries(ctx);  // the last call's counts read the table that goes
+    ctx->lists = gd_ctx::Lists{};
     // a captured graph reads the instance table through the old pointers
     // (its copy node from the pinned host table, every kernel from the
     // device table): it must never run again
@@ -1030,6 +1263,8 @@ std::vector<int64_t> batch_signature(const gd_ctx* ctx, int count) {
     sig.push_back(ctx->tile_pts);
     sig.push_back(ctx->merge_waves);
     sig.push_back(ctx->grid_lanes);
+    sig.push_back(ctx->nei_mode);
+    sig.push_back(ctx->nei_query);
     sig.push_back(ctx->pack_rows ? (ctx->fuse_rows ? 1 : 2) : 0);
     for (int k = 0; k < count; ++k) {
         sig.push_back(ctx->inst_host[k].n);
@@ -1058,13 +1293,17 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
     p.ncc = std::min<int64_t>(p.ncell, e.core_grids + e.core_grids / 16 + 256);
     p.max_core = std::min<int64_t>(std::min<int64_t>(n, kMaxCoreBits), ctx->last_max_core + ctx->last_max_core / 16 + 64);
     p.walk = ctx->last_walk;
-    if (!ctx->gstream) {
-        if (hipStreamCreateWithFlags(&ctx->gstream, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&ctx->gev, hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            return;
+    p.runs = ctx->last_runs;
+    p.by_level = ctx->last_by_level;
+    const bool levels = p.runs || p.by_level;
+    if (levels) {
+        for (int k = 0; k < 2; ++k) p.ents[k] = ctx->last_ents[k] + ctx->last_ents[k] / 16 + 4096;
+        for (int l = 0; l < kMaxLevels; ++l) {
+            p.nodes[l] = std::min<int64_t>(p.ncell, ctx->last_nodes[l] + ctx->last_nodes[l] / 16 + 1024);
+            p.lanes[l] = ctx->last_lanes[l];
         }
     }
+    if (!own_stream(ctx)) return;
     const std::string saved_err = ctx->err;
     const uint64_t gen0 = ctx->generation;
     struct Invalidate {  // debug views of the eager call may point into reallocated buffers
@@ -1074,7 +1313,10 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
             if (c->generation != g) c->have_last = false;
         }
     } inval{ctx, gen0};
-    if (grow(ctx, ctx->cur->nei, (size_t)std::max<uint64_t>(p.nei, 1) * sizeof(uint32_t), ctx->cur->arena.cap) ||
+    const int fin = (p.runs ? D - 1 : D) & 1;
+    if (grow(ctx, ctx->cur->nei, (size_t)std::max<uint64_t>(levels ? p.ents[fin] : p.nei, 1) * sizeof(uint32_t),
+             ctx->cur->arena.cap) ||
+        (levels && grow(ctx, ctx->cur->mid, (size_t)p.ents[1 - fin] * sizeof(uint32_t), ctx->cur->arena.cap)) ||
         (p.key_bits <= 64 && grow(ctx, ctx->cur->table, output_table_bytes(table_bits(p.ncell), key_bytes_of(p.key_bits)),
                                   ctx->cur->arena.cap + ctx->cur->nei.cap)) ||
         (ctx->proposal_on && grow(ctx, ctx->cur->sumbuf, sizeof(CellSummary) * (size_t)std::max<int64_t>(p.ncell, 1),
@@ -1091,9 +1333,11 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
     // debug views stay those of the call that just ran
     const gd_stats saved_last = ctx->last;
     const bool saved_have = ctx->have_last;
+    const gd_ctx::Lists saved_lists = ctx->lists;
     const int rc = run_batch(ctx, count, D, n, tiles, ctx->gstream, &p);
     ctx->last = saved_last;
     ctx->have_last = saved_have;
+    ctx->lists = saved_lists;
     const hipError_t ce = hipStreamEndCapture(ctx->gstream, &graph);
     hipGraphExec_t exec = nullptr;
     if (rc == GD_OK && ce == hipSuccess && graph &&
@@ -1129,6 +1373,7 @@ int run_call(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStream
             ctx->last.key_bits = ctx->last_key_bits;
             ctx->last.grids = H->ncell;
             ctx->last.neighbor_entries = (int64_t)H->nei_total;
+            ctx->lists = ctx->plan_lists;
             ctx->last.core_points = H->counts[0];
             ctx->last.core_grids = H->counts[1];
             ctx->last.dense_grids = H->counts[3];
@@ -1273,6 +1518,7 @@ void gd_destroy(gd_ctx* ctx) {
     DeviceGuard guard(ctx->device);
     if (ctx->own.arena.p) (void)hipFree(ctx->own.arena.p);
     if (ctx->own.nei.p) (void)hipFree(ctx->own.nei.p);
+    if (ctx->own.mid.p) (void)hipFree(ctx->own.mid.p);
     if (ctx->hdr_dev) (void)hipFree(ctx->hdr_dev);
     if (ctx->hdr_host) (void)hipHostFree(ctx->hdr_host);
     if (ctx->stats_dev) (void)hipFree(ctx->stats_dev);
@@ -1323,7 +1569,7 @@ int dbscan_noalloc(gd_ctx* ctx, const float* points, int64_t n, int32_t d, doubl
     int64_t total;
     uint32_t tiles;
     finish_table(ctx, 1, &D, &total, &tiles);
-    const size_t need = carve(nullptr, total, D, tiles).bytes;
+    const size_t need = carve(nullptr, total, D, tiles, 8, true).bytes;
     if (need > (size_t)GD_NOALLOC_SCRATCH_BYTES)
         return ctx->fail(GD_ENOMEM,
                          "dbscan_noalloc: n = %lld at d = %d needs %zu bytes of workspace before its neighbour "
@@ -1515,6 +1761,8 @@ int gd_set_option(gd_ctx* ctx, int option, int64_t value) {
 
 int gd_get_stats(gd_ctx* ctx, gd_stats* out) {
     if (!ctx || !out) return GD_EINVAL;
+    const int rc = count_entries(ctx);
+    if (rc) return rc;
     *out = ctx->last;
     return GD_OK;
 }
@@ -1556,6 +1804,7 @@ int gd_debug_neighbors(gd_ctx* ctx, uint64_t* offsets, uint32_t* neighbors) {
                                           "(GD_OPT_NEIGHBOR_MODE = 1 keeps them)");
     DeviceGuard guard(ctx->device);
     int rc;
+    if ((rc = write_lists(ctx))) return rc;
     if ((rc = copy_d2h(ctx, offsets, ctx->last_nei_off, sizeof(uint64_t) * (ctx->last_ncell + 1)))) return rc;
     return copy_d2h(ctx, neighbors, ctx->last_nei, sizeof(uint32_t) * ctx->last_nei_total);
 }
@@ -1637,6 +1886,7 @@ int gd_proposal_harvest(gd_ctx* ctx, uint32_t seed, uint32_t keep_mod, int64_t c
     hipStream_t st = (hipStream_t)stream;
     const GridView& g = ctx->last_g;
     int rc;
+    if ((rc = write_lists(ctx))) return rc;
     if ((rc = grow(ctx, ctx->cur->sumbuf, sizeof(CellSummary) * (size_t)std::max<int64_t>(g.ncell, 1),
                    ctx->cur->arena.cap + ctx->cur->nei.cap)))
         return rc;

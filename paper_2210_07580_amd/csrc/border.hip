@@ -21,6 +21,7 @@
 
 #include "hash.hpp"
 #include "launch.hpp"
+#include "runs.hpp"
 #include "scan.hpp"
 
 namespace gd {
@@ -415,9 +416,177 @@ __global__ __launch_bounds__(kBlock) void output_kernel(GridView gv, CoreOut co,
     }
 }
 
+// Smallest core index of each family's grids (kNone: no core point).
+__global__ __launch_bounds__(kBlock) void family_min_kernel(const uint32_t* families, const uint32_t* __restrict__ child,
+                                                            const uint32_t* __restrict__ cell_min_core,
+                                                            uint32_t* __restrict__ family_min) {
+    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (p >= (int64_t)*families) return;
+    uint32_t m = kNone;
+    for (uint32_t c = child[p]; c < child[p + 1]; ++c) m = min(m, cell_min_core[c]);
+    family_min[p] = m;
+}
+
+// Border and noise points with neighbours as runs (runs.hpp), a wave for the
+// grids with a non-core point among G neighbouring ones (G = 16 for millions of
+// grids, most of which have none: a wave for each would mostly be waves that
+// leave at once).  Entries whose family's smallest core index
+// cannot improve any open query (most families around a noise point hold no
+// core point at all) are dropped before their grids are looked at; the rest
+// queue up until every lane has one.  A run is one contiguous range of sorted
+// points, streamed whole: its non-core points are passed over, and the grid of
+// the best hit is found from the run's first grid at the end.  10M 5-D points:
+// 8.0 ms without the families' minima and G = 1, 4.1 ms now (3.0 from lists, which
+// took 33 ms to write).
+template <int D, int G>
+__global__ __launch_bounds__(kBlock) void border_runs_kernel(GridView gv, CoreOut co, RunSource rs,
+                                                             const uint32_t* __restrict__ family_min,
+                                                             const int32_t* __restrict__ cell_label) {
+    __shared__ uint32_t s_row[kWavesPerBlock][kWave];   // first row of each lane's run, minus its place
+    __shared__ uint32_t s_head[kWavesPerBlock][kWave];  // lane + 1 of the run that starts at this candidate
+    __shared__ uint32_t s_lo[kWavesPerBlock][kWave];    // first grid of each lane's run
+    __shared__ uint32_t s_queue[kWavesPerBlock][2 * kWave];
+    const int w = wave_id(), lane = lane_id();
+    const int64_t cw = (xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w) * G;
+    const int64_t ncell = *gv.ncell_dev;
+    uint32_t st_l = 0, k_l = 0;
+    bool need = false;  // not all core: those were written in input order by the hash pass
+    if (lane < G && cw + lane < ncell) {
+        st_l = gv.cell_start[cw + lane];
+        k_l = gv.cell_start[cw + lane + 1] - st_l;
+        need = co.core_cnt[cw + lane] != k_l;
+    }
+    for (uint64_t todo = ballot(need); todo; todo &= todo - 1ull) {
+        const int64_t c = cw + ffs64(todo);
+        const uint32_t st = readlane(st_l, ffs64(todo)), k = readlane(k_l, ffs64(todo));
+        const Inst& I = cell_inst(gv, c);
+        RunCursor<D> rc;
+        rc.open(rs, gv, c);
+        const uint32_t off = (uint32_t)I.off;  // cluster ids and output slots are local to the instance
+        int32_t GD_GLOBAL* __restrict__ labels = as_global(I.labels);
+        uint8_t GD_GLOBAL* __restrict__ core_flags = as_global(I.core);
+        const int32_t own_label = cell_label[c];
+        const uint32_t own_min = co.cell_min_core[c];
+        const uint32_t T = I.T;
+        for (uint32_t qb = 0; qb < k; qb += kWave) {
+            const uint32_t s = st + qb + lane;
+            const bool v = qb + lane < k;
+            const bool query = v && !co.core[s];
+            const uint32_t o = v ? gv.sidx[s] - off : 0u;
+            if (v && !query) {
+                labels[o] = own_label - (int32_t)off;
+                core_flags[o] = 1;
+            }
+            const uint64_t open = ballot(query);
+            if (!open) continue;
+            int32_t qx[D];
+            load_row<D>(gv.crd, query ? s : st, qx);
+            // the best core neighbour's input index, its row and the first grid of
+            // its run; the own grid's core points are all within eps
+            uint32_t best = own_min, best_row = 0, best_lo = kNone;
+            uint32_t held = 0;
+            auto drain = [&]() {  // up to 64 queued entries, one run per lane
+                wave_sync();
+                uint32_t lo = 0, hi = 0;
+                if ((uint32_t)lane < held) rc.run_of(rs, s_queue[w][lane], lo, hi);
+                const uint32_t nx = s_queue[w][kWave + lane];
+                const uint32_t cs = lo < hi ? gv.cell_start[lo] : 0u;
+                const uint32_t cn = lo < hi ? gv.cell_start[hi] - cs : 0u;
+                const uint32_t incl = wave_incl_scan(cn);
+                const uint32_t tot = last_lane(incl);
+                const uint32_t excl = incl - cn;
+                s_row[w][lane] = cs - excl;
+                s_lo[w][lane] = lo;
+                uint32_t carry = 0;  // run of the last candidate so far (see core_mark_runs_kernel)
+                for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
+                    const uint32_t t = t0 + lane;
+                    s_head[w][lane] = 0;
+                    wave_sync();
+                    if (cn != 0 && excl >= t0 && excl < t0 + kWave) s_head[w][excl - t0] = (uint32_t)lane + 1u;
+                    wave_sync();
+                    uint32_t j = wave_max_scan(s_head[w][lane]);
+                    j = j ? j : carry;
+                    carry = last_lane(j);
+                    j = (j ? j : 1u) - 1u;
+                    const uint32_t q = t < tot ? s_row[w][j] + t : st;
+                    const bool cand = t < tot && co.core[q];
+                    int32_t y[D];
+                    load_row<D>(gv.crd, q, y);
+                    const uint32_t idx = gv.sidx[q];
+                    if (!ballot(cand)) continue;
+                    for (uint64_t act = open; act; act &= act - 1ull) {
+                        const int qi = ffs64(act);
+                        uint32_t dd = 0;
+#pragma unroll
+                        for (int jj = 0; jj < D; ++jj) dd += sq24(y[jj], readlane(qx[jj], qi));
+                        const bool in = cand && dd <= T && idx < readlane(best, qi);
+                        if (ballot(in)) {
+                            const uint32_t m = wave_min_u32(in ? idx : kNone);
+                            const int from = ffs64(ballot(in && idx == m));
+                            const uint32_t row = readlane(q, from), lo0 = readlane(s_lo[w][j], from);
+                            if (lane == qi) {
+                                best = m;
+                                best_row = row;
+                                best_lo = lo0;
+                            }
+                        }
+                    }
+                }
+                wave_sync();
+                s_queue[w][lane] = nx;
+                held = held > (uint32_t)kWave ? held - kWave : 0u;
+            };
+            for (uint64_t e = rc.e0; e < rc.e1; e += kWave) {
+                // the index an improvement has to beat for some open query
+                const uint32_t worst = wave_max_u32(query ? best : 0u);
+                bool keep = false;
+                uint32_t x = 0;
+                if (e + lane < rc.e1) {
+                    x = rs.ent[e + lane];
+                    keep = family_min[entry_node(x)] < worst;  // kNone: no core point
+                }
+                const uint64_t m = ballot(keep);
+                if (keep) s_queue[w][held + (uint32_t)popc64(m & lanemask_lt())] = x;
+                held += (uint32_t)popc64(m);
+                if (held >= (uint32_t)kWave) drain();
+            }
+            if (held) drain();
+            if (query) {
+                int32_t lab = best == kNone ? -1 : own_label - (int32_t)off;
+                if (best_lo != kNone) {
+                    while (gv.cell_start[best_lo + 1] <= best_row) ++best_lo;
+                    lab = cell_label[best_lo] - (int32_t)off;
+                }
+                labels[o] = lab;
+                core_flags[o] = 0;
+            }
+        }
+    }
+}
+
 hipError_t launch_output(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
-                         const int32_t* cell_label, bool wide, int lanes, hipStream_t st) {
+                         const RunSource* runs, const int32_t* cell_label, bool wide, int lanes, uint32_t* family_min,
+                         hipStream_t st) {
     if (g.ncell == 0) return hipSuccess;
+    if (runs) {
+        if (wide) return hipErrorInvalidValue;
+        family_min_kernel<<<dim3(grid_for(runs->families)), dim3(kBlock), 0, st>>>(
+            runs->t.level_count + (g.D - 1), runs->t.child[g.D - 1], c.cell_min_core, family_min);
+        GD_DISPATCH_D(g.D, ({
+                          if constexpr (D >= kMinRunD) {
+                              if (g.ncell >= kBorderGroupMinGrids)
+                                  border_runs_kernel<D, 16>
+                                      <<<grid_of(grid_for(g.ncell, kWavesPerBlock * 16)), dim3(kBlock), 0, st>>>(
+                                          g, c, *runs, family_min, cell_label);
+                              else
+                                  border_runs_kernel<D, 1>
+                                      <<<grid_of(grid_for(g.ncell, kWavesPerBlock)), dim3(kBlock), 0, st>>>(
+                                          g, c, *runs, family_min, cell_label);
+                              return hipGetLastError();
+                          }
+                      }));
+        return hipErrorInvalidValue;
+    }
     const unsigned many = grid_for(g.ncell, kWavesPerBlock * kWave), one = grid_for(g.ncell, kWavesPerBlock);
     if (lanes == 16) {  // four grids per wave, side by side
         const unsigned four = grid_for(g.ncell, kWavesPerBlock * 4);

@@ -187,6 +187,17 @@ __device__ __forceinline__ T wave_incl_scan(T v) {
     return v;
 }
 
+// inclusive running maximum across the 64 lanes (values >= 0)
+__device__ __forceinline__ uint32_t wave_max_scan(uint32_t v) {
+    v = max(v, dpp<kRowShr + 1>(0u, v));
+    v = max(v, dpp<kRowShr + 2>(0u, v));
+    v = max(v, dpp<kRowShr + 4>(0u, v));
+    v = max(v, dpp<kRowShr + 8>(0u, v));
+    v = max(v, dpp<kRowBcast15, 0xA>(0u, v));
+    v = max(v, dpp<kRowBcast31, 0xC>(0u, v));
+    return v;
+}
+
 // Sum over all lanes (whole numbers; floats keep their own order of additions).
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
@@ -239,6 +250,16 @@ __device__ __forceinline__ T load_acq(const T* p) {
 template <typename T>
 __device__ __forceinline__ void store_rel(T* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Access through the caches, for data where a value of some time ago does.
+template <typename T>
+__device__ __forceinline__ T load_cached(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+template <typename T>
+__device__ __forceinline__ void store_cached(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 // floor(u * sqrt(d) / eps) exactly, for integers 0 <= u <= 2^25, 1 <= d <= 8,

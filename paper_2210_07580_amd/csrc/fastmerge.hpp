@@ -68,6 +68,23 @@ __device__ __forceinline__ uint32_t uf_find(uint32_t* parent, uint32_t x) {
     return uf_find_at(parent, x, load_acq(&parent[x]));
 }
 
+// The same on cached loads, which may show a parent of some time ago: an
+// ancestor of x's set that was its root then.  Equal results prove that two
+// elements are in one set; different ones prove nothing.
+__device__ __forceinline__ uint32_t uf_peek_at(uint32_t* parent, uint32_t x, uint32_t p) {
+    for (;;) {
+        if (p == x) return x;
+        const uint32_t gp = load_cached(&parent[p]);
+        if (gp == p) return p;
+        store_cached(&parent[x], gp);
+        x = gp;
+        p = load_cached(&parent[x]);
+    }
+}
+__device__ __forceinline__ uint32_t uf_peek(uint32_t* parent, uint32_t x) {
+    return uf_peek_at(parent, x, load_cached(&parent[x]));
+}
+
 __device__ __forceinline__ void uf_union(uint32_t* parent, uint32_t a, uint32_t b) {
     for (;;) {
         a = uf_find(parent, a);

@@ -150,8 +150,8 @@ __device__ __forceinline__ const Inst& cell_inst(const GridView& g, int64_t c) {
 hipError_t launch_minmax(const Batch& b, int32_t* part, int plan_bits, hipStream_t st);
 // Sync-free runs: compare the device counts with the capacities the run was
 // planned with (stage 0: grids; 1: neighbour entries; 2: core grids and the
-// largest core set).  On overflow, or after an input error, kErrPlan goes up
-// and the grid count drops to zero, so every later kernel finds no work.
+// largest core set; 3: cap_b nodes of tree level cap_a).  On overflow, or after an input error, kErrPlan goes up
+// and the grid and node counts drop to zero, so every later kernel finds no work.
 hipError_t launch_plan_check(Header* hdr, int stage, int64_t cap_a, int64_t cap_b, hipStream_t st);
 // Packed rows: each coordinate's low pack_bits(d) bits ride through the sort
 // in the high half of a 64-bit value (the point's index in the low half).
@@ -200,8 +200,45 @@ hipError_t launch_cells(const Batch& b, const K* skeys, uint32_t* partial, uint3
                         int32_t* ck, int64_t ck_stride, hipStream_t st);
 // Grid tree levels over the sorted grids.  level_excl: D x (ncell+1) scratch;
 // partial: scan scratch of 64-bit words (passed as the u32 view).
+// tpar (or nullptr): per level 1 .. D-1, where each node's parent (its index
+// in the level above) goes.
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
-                       uint32_t* const* tchild, hipStream_t st);
+                       uint32_t* const* tchild, uint32_t* const* tpar, hipStream_t st);
+
+// ---- nodes.hip: lists of neighbouring tree nodes (runs.hpp)
+// Working set of the level-by-level build: the lists of level l live in
+// buffer l & 1 (ent, cap entries) with offsets off[l & 1] (nodes + 1).
+struct NodeLists {
+    uint32_t* par[kMaxLevels];  // launch_tree's tpar
+    const uint32_t* excl;       // level D-1: nodes before grid c (c in [0, ncell])
+    uint64_t* off[2];
+    uint32_t* ent[2];
+    uint64_t cap[2];
+    uint32_t* cnt;              // scratch: one word per node
+    uint32_t* near;             // entries of each node's list that touch it, listed first (or nullptr)
+    uint2* up;                  // level D: see launch_nei_fill's nei_up
+};
+// Places around a level-1 node that hold all its level-1 neighbours (windows of +-3 keys).
+constexpr int kNear = 7;
+// Entries hold a node above 6 bits.
+constexpr int64_t kMaxRunNodes = (int64_t)1 << 26;
+// Level l (2 .. D): list lengths and offsets, total into the header
+// (nei_total); then the lists, for l = D those of the grids, in walk order.  nodes: nodes of level l (or an upper bound);
+// lanes: 8, 16 or 64 per node (by the length of the parents' lists).
+hipError_t launch_level_count(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
+                              int lanes, uint64_t* partial, hipStream_t st);
+hipError_t launch_level_fill(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
+                             int lanes, hipStream_t st);
+// Where the consumers find a grid's neighbours as runs of grids (runs.hpp).
+constexpr int kMinRunD = 4;  // below, the lists of the grids are short (at most 20 or 116 entries)
+struct RunSource {
+    TreeView t;
+    const uint32_t* excl;   // level D-1: nodes before grid c (c in [0, ncell])
+    const uint64_t* off;    // list of level-(D-1) node p = ent[off[p], off[p + 1])
+    const uint32_t* ent;
+    const uint32_t* near;   // entries of p's list that touch, listed first
+    int64_t families;       // nodes of level D-1 (or an upper bound)
+};
 
 // ---- neighbors.hip (Algorithm 3)
 // The query that produces the lists: the grid tree with offset-ordered lists
@@ -276,9 +313,11 @@ struct CoreStats {
 // candidate rows per lane per step).  prune (used at d <= 4): test large
 // neighbour grids' cells against the open queries before streaming them,
 // for data whose grids hold a thousand points and more.
-hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, uint8_t* core,
-                            uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts, bool prune,
-                            hipStream_t st);
+// runs (or nullptr): neighbours as runs instead of lists (then without stats,
+// prune and eps above GD_EPS_MAX).
+hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const RunSource* runs,
+                            uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
+                            bool prune, hipStream_t st);
 // Whether core marking compares coordinates as packed 16-bit differences
 // for a batch whose largest eps is max_eps (exact for eps <= 10000: points
 // of neighbouring grids differ by less than 2.13 eps per coordinate).
@@ -327,18 +366,21 @@ struct CellSummary;
 // tiny_done: the pairs of two tiny core sets were already merged (walk mode).
 // nei_up (optional, lists in walk order): each list's range of larger-index
 // neighbours (launch_nei_fill), the only ones the tiny-set kernel tests.
+// runs (or nullptr): neighbours as runs instead of lists (then without stats,
+// proposal, nei_up, walk mode and eps above GD_EPS_MAX); family_root: scratch
+// of one word per level-(D-1) node.
 hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
-                        const uint2* nei_up,
+                        const uint2* nei_up, const RunSource* runs,
                         const uint32_t* ldf_list, const uint4* rank, int64_t n_core_cells, int64_t n_small,
                         int64_t max_core, int waves, int small_lanes, bool tiny_done, const HugeQueue& huge,
                         bool wide,
                         uint32_t* parent, MergeStats* stats, const __half* proposal, const CellSummary* sum,
-                        hipStream_t st);
+                        uint32_t* family_root, hipStream_t st);
 // Sum over core grids with at least kHeavyCore core points of |Nei(g)| + 1
 // (added to *sum; the caller clears it): with both orders no pair is queued
 // twice from one side, so twice this bounds the queue.
-hipError_t launch_huge_scan(const GridView& g, const CoreOut& c, const uint64_t* nei_off, unsigned long long* sum,
-                            hipStream_t st);
+hipError_t launch_huge_scan(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const RunSource* runs,
+                            unsigned long long* sum, hipStream_t st);
 // Tests the queued pairs (FastMerging, union on yes) with `blocks`
 // workgroups of kCoopWaves waves, each with 2 * words words of device memory
 // at slabs.  bfs: the pair's second grid is claimed for the search (state,
@@ -391,8 +433,11 @@ hipError_t launch_border_walk(const GridView& g, const CoreOut& c, const TreeVie
 // Grids with a non-core point: border search and output through the permutation.
 // lanes: 16 serves four grids per wave side by side; otherwise a wave per
 // grid (a wave checks 64 grids when there are millions of them).
+// runs (or nullptr): neighbours as runs instead of lists (eps <= GD_EPS_MAX;
+// family_min: scratch of one word per level-(D-1) node).
 hipError_t launch_output(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
-                         const int32_t* cell_label, bool wide, int lanes, hipStream_t st);
+                         const RunSource* runs, const int32_t* cell_label, bool wide, int lanes, uint32_t* family_min,
+                         hipStream_t st);
 // All-core grids: output in input order through an identifier -> label hash
 // table of 2^bits slots (+1) in `table` (output_table_bytes).  keys_in: the
 // identifiers in input order, shifted up by key_lo bits (the packed-row

@@ -8,6 +8,7 @@
 #include "fastmerge_block.hpp"
 #include "launch.hpp"
 #include "learned.hpp"
+#include "runs.hpp"
 #include "scan.hpp"
 
 namespace gd {
@@ -183,6 +184,198 @@ __global__ __launch_bounds__(kBlock) void merge_small_kernel(GridView gv, CoreOu
     }
 }
 
+// Tiny core sets with neighbours as runs (runs.hpp).  The pairs of families
+// (p, b >= p) are taken in three phases: pairs of grids that share a face,
+// those that share an edge (keys one apart in two dimensions), all.  After each of the first
+// two, every family whose tiny core grids are all in one set is marked with
+// its root (family_root_kernel), and the phases that follow drop an entry
+// when both families are marked with one set, before any of their grids is
+// looked at: the first phase joins most of each cluster with a few tests per
+// grid, and what is left to test lies at the clusters' rims.
+// A wave takes kFamilies families one after another and queues the pairs (grid
+// of p, entry) that are left until every lane has one: a pair is a chain of a
+// dozen dependent loads, and one family seldom has more than a few.  A lane
+// skips a pair of grids already in one set and decides the others by their
+// distances (FastMerging's answer, Theorem 2).
+// 10M 5-D points: 33.2 -> 10.9 ms for the tiny sets (2.9 + 3.0 + 4.9 ms for the
+// three phases; a first phase over all touching grids and none in between took
+// 13.8, one over faces and then everything 24.7 ms).  Bound by the latency of
+// the pairs' loads (11-18% of the vector issue rate at full occupancy).
+constexpr uint32_t kFamilyEmpty = 0xFFFFFFFEu;  // no tiny core grid
+constexpr uint32_t kFamilyMixed = kNone;        // tiny core grids of several sets
+constexpr int kFamilies = 8;
+enum FamilyPhase { kPhaseFace = kFace, kPhaseEdge = kEdge, kPhaseAll };
+
+__global__ __launch_bounds__(kBlock) void family_root_kernel(const uint32_t* families, const uint32_t* __restrict__ child,
+                                                             const uint4* __restrict__ rank, uint32_t* parent,
+                                                             uint32_t* __restrict__ family_root) {
+    const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (p >= (int64_t)*families) return;
+    uint32_t root = kFamilyEmpty;
+    for (uint32_t c = child[p]; c < child[p + 1] && root != kFamilyMixed; ++c) {
+        const uint4 q = rank[c];
+        if (q.x == kNone || q.z > kSmallSet) continue;
+        const uint32_t r = uf_find(parent, c);
+        root = root == kFamilyEmpty || root == r ? r : kFamilyMixed;
+    }
+    family_root[p] = root;
+}
+
+template <int D, int kPhase>
+__global__ __launch_bounds__(kBlock) void merge_family_kernel(GridView gv, CoreOut co, RunSource rs,
+                                                              const uint4* __restrict__ rank,
+                                                              const uint32_t* __restrict__ family_root,
+                                                              uint32_t* parent) {
+    __shared__ uint2 queue[kWavesPerBlock][2 * kWave];  // (grid, entry)
+    const int w = wave_id(), lane = lane_id();
+    const uint32_t* __restrict__ child = rs.t.child[D - 1];
+    const int32_t* __restrict__ key = rs.t.key[D];
+    const int64_t families = rs.t.level_count[D - 1];
+    const int64_t f0 = (xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w) * kFamilies;
+    const int64_t f1 = min(f0 + kFamilies, families);
+    if (f0 >= f1) return;
+    // Every load that does not need an earlier one's result is issued ahead of
+    // its use: the pair is bound by the length of its chain of loads.
+    auto pair = [&](uint32_t a, uint32_t v) {
+        const uint32_t b = entry_node(v);
+        const uint4 own = rank[a];
+        const int32_t k = key[a];
+        const uint32_t pa = load_cached(&parent[a]);
+        const uint32_t T = cell_inst(gv, a).Tm;
+        // the last key may be one apart where fewer of the others are than the phase takes
+        const int win = kPhase == kPhaseAll ? walk_window(entry_budget(v)) : entry_touch(v) < kPhase ? 1 : 0;
+        uint32_t lo, hi, b0, b1;
+        node_children(child, b, b0, b1);
+        child_window(key, b0, b1, k, win, lo, hi);
+        if (a >= b0) lo = lo > a ? lo : a + 1;  // the own family: the grids above a
+        if (lo >= hi) return;
+        int32_t x0[D];
+        load_row<D>(co.ccrd, own.y, x0);
+        uint32_t pc = load_cached(&parent[lo]);
+        uint4 q = rank[lo];
+        uint32_t ra = uf_peek_at(parent, a, pa);
+        for (uint32_t c = lo; c < hi; ++c) {
+            const uint4 qc = q;
+            const uint32_t pcc = pc;
+            if (c + 1 < hi) {
+                pc = load_cached(&parent[c + 1]);
+                q = rank[c + 1];
+            }
+            if (qc.x == kNone || qc.z > kSmallSet) continue;
+            int32_t y[2][D];
+            load_row<D>(co.ccrd, qc.y, y[0]);
+            load_row<D>(co.ccrd, qc.y + min(1u, qc.z - 1), y[1]);
+            const uint32_t rc = uf_peek_at(parent, c, pcc);
+            if (rc == ra) continue;
+            bool yes = false;
+            int32_t x[D];
+#pragma unroll
+            for (int t = 0; t < D; ++t) x[t] = x0[t];
+            for (uint32_t i = 0; i < own.z && !yes; ++i) {
+                if (i) load_row<D>(co.ccrd, own.y + i, x);
+                for (uint32_t j = 0; j < qc.z && !yes; j += 2) {
+                    if (qc.z > 2) {
+                        load_row<D>(co.ccrd, qc.y + j, y[0]);
+                        load_row<D>(co.ccrd, qc.y + min(j + 1, qc.z - 1), y[1]);
+                    }
+                    uint32_t d0 = 0, d1 = 0;
+#pragma unroll
+                    for (int t = 0; t < D; ++t) {
+                        d0 += sq24(x[t], y[0][t]);
+                        d1 += sq24(x[t], y[1][t]);
+                    }
+                    yes = d0 <= T || d1 <= T;
+                }
+            }
+            if (yes) ra = uf_union_from(parent, ra, rc);
+        }
+    };
+    uint32_t held = 0;
+    // a full wave of pairs, then the rest moves to the front
+    auto drain = [&]() {
+        wave_sync();
+        const uint2 it = queue[w][lane];
+        const uint2 nx = queue[w][kWave + lane];
+        if ((uint32_t)lane < held) pair(it.x, it.y);
+        wave_sync();
+        queue[w][lane] = nx;
+        held = held > (uint32_t)kWave ? held - kWave : 0u;
+    };
+    // lane i holds family f0 + i: its grids, its entries of this phase, its mark
+    const int nf = (int)(f1 - f0);
+    uint32_t fc0 = 0, fc1 = 0, froot = 0;
+    uint64_t fe0 = 0, fe1 = 0;
+    if (lane < nf) {
+        const int64_t f = f0 + lane;
+        fc0 = child[f];
+        fc1 = child[f + 1];
+        fe0 = rs.off[f];
+        fe1 = kPhase == kPhaseAll ? rs.off[f + 1] : fe0 + rs.near[f];
+        if constexpr (kPhase != kPhaseFace) froot = family_root[f];
+    }
+    auto lane64 = [](uint64_t x, int i) -> uint64_t {
+        return (uint64_t)readlane((uint32_t)(x >> 32), i) << 32 | readlane((uint32_t)x, i);
+    };
+    // the first entries and merge records of a family load while the one
+    // before is worked on
+    uint32_t v_next = 0;
+    uint2 q_next = make_uint2(kNone, 0u);
+    auto record = [&](uint32_t c) {  // rank and size of grid c's core set
+        const uint4 q = rank[c];
+        return make_uint2(q.x, q.z);
+    };
+    auto prefetch = [&](int i) {
+        const uint64_t e = lane64(fe0, i) + lane;
+        const uint32_t c = readlane(fc0, i) + lane;
+        v_next = e < lane64(fe1, i) ? rs.ent[e] : 0u;
+        q_next = c < readlane(fc1, i) ? record(c) : make_uint2(kNone, 0u);
+    };
+    prefetch(0);
+    for (int i = 0; i < nf; ++i) {
+        const uint32_t v_first = v_next;
+        const uint2 q_first = q_next;
+        if (i + 1 < nf) prefetch(i + 1);
+        const uint32_t p = (uint32_t)(f0 + i);
+        const uint32_t rp = readlane(froot, i);
+        if (kPhase != kPhaseFace && rp == kFamilyEmpty) continue;
+        const uint32_t c0 = readlane(fc0, i), c1 = readlane(fc1, i);
+        const uint64_t e0 = lane64(fe0, i), e1 = lane64(fe1, i);
+        for (uint32_t cb = c0; cb < c1; cb += kWave) {  // the family's grids, 64 at a time
+            uint2 q = q_first;
+            if (cb != c0) q = cb + lane < c1 ? record(cb + lane) : make_uint2(kNone, 0u);
+            const uint64_t grids = ballot(q.x != kNone && q.y <= kSmallSet);
+            if (!grids) continue;
+            for (uint64_t e = e0; e < e1; e += kWave) {
+                bool keep = false;
+                uint32_t v = v_first;
+                if (e + lane < e1) {
+                    if (e != e0) v = rs.ent[e + lane];
+                    const uint32_t b = entry_node(v);
+                    if (b >= p) {
+                        keep = kPhase == kPhaseAll || entry_touch(v) <= kPhase;
+                        if (kPhase != kPhaseFace && keep) {
+                            const uint32_t rb = family_root[b];
+                            keep = rb != kFamilyEmpty && (rb == kFamilyMixed || rb != rp);
+                            // two marked families: their sets may have been joined since
+                            if (keep && rb != kFamilyMixed && rp != kFamilyMixed)
+                                keep = uf_peek(parent, rp) != uf_peek(parent, rb);
+                        }
+                    }
+                }
+                const uint64_t m = ballot(keep);
+                if (!m) continue;
+                const uint32_t at = (uint32_t)popc64(m & lanemask_lt());
+                for (uint64_t g = grids; g; g &= g - 1ull) {
+                    if (keep) queue[w][held + at] = make_uint2(cb + ffs64(g), v);
+                    held += (uint32_t)popc64(m);
+                    if (held >= (uint32_t)kWave) drain();
+                }
+            }
+        }
+    }
+    if (held) drain();
+}
+
 // Queues the pairs (g_i, g_j) of the lanes in `lanes` (each lane holds its
 // g_j) for merge_huge_kernel, with one append for the wave.
 __device__ __noinline__ void defer_pairs(const HugeQueue& q, uint64_t lanes, uint32_t ci, uint32_t cj, Header* hdr) {
@@ -224,9 +417,9 @@ __device__ __forceinline__ uint32_t orderable(float z) {
 // unrolling inside a wave.  The scorer's fragments, and rows of d >= 5, do
 // not fit in that budget (they would spill to scratch), so those variants
 // run four.
-template <int D, bool kLearned, bool kWide>
+template <int D, bool kLearned, bool kWide, bool kRuns>
 __global__ __launch_bounds__(kBlock, (kLearned || D >= 5) ? 4 : 6) void merge_big_kernel(GridView gv, CoreOut co, const uint64_t* __restrict__ nei_off,
-                                                           const uint32_t* __restrict__ nei,
+                                                           const uint32_t* __restrict__ nei, RunSource rs,
                                                            const uint32_t* __restrict__ ldf,
                                                            const uint4* __restrict__ rank, int64_t r0, int64_t r1,
                                                            const uint32_t* split, uint32_t words, HugeQueue huge,
@@ -251,7 +444,16 @@ __global__ __launch_bounds__(kBlock, (kLearned || D >= 5) ? 4 : 6) void merge_bi
     // every load that depends on ci alone is issued before the first use
     const Inst& I = cell_inst(gv, ci);
     const uint4 own = rank[ci];
-    const uint64_t e0 = nei_off[ci], e1 = nei_off[ci + 1];
+    uint64_t e0, e1;
+    RunCursor<D> cur;
+    if constexpr (kRuns) {
+        cur.open(rs, gv, ci);
+        e0 = cur.e0;
+        e1 = cur.e1;
+    } else {
+        e0 = nei_off[ci];
+        e1 = nei_off[ci + 1];
+    }
     const uint32_t pci = load_acq(&parent[ci]);
     const typename Dist<kWide>::T T = inst_T<kWide>(I), Tm = inst_Tm<kWide>(I);
     const double eps = (double)I.eps;
@@ -274,140 +476,151 @@ __global__ __launch_bounds__(kBlock, (kLearned || D >= 5) ? 4 : 6) void merge_bi
     uint32_t ri = uf_find_at(parent, ci, pci);
     for (uint64_t e = e0; e < e1; e += kWave) {
         const uint64_t idx = e + lane;
-        uint32_t cj = 0, bj = 0, mj = 0, pj = 0;
-        bool cand = false;
-        if (idx < e1) {
-            cj = nei[idx];
-            // the parent link loads beside the record (every grid has one)
-            pj = load_acq(&parent[cj]);
-            const uint4 rc = rank[cj];
-            const uint32_t rj = rc.x;
-            if (rj != kNone) {
-                bj = rc.y;
-                mj = rc.z;
-                cand = mj <= kSmallSet || rj > (uint32_t)r;
+        uint32_t lo = 0, hi = 0;  // this lane's grids (kRuns: a run, one per round)
+        if constexpr (kRuns) {
+            if (idx < e1) cur.run_of(rs, rs.ent[idx], lo, hi);
+        } else if (idx < e1) {
+            lo = nei[idx];
+            hi = lo + 1;
+        }
+        do {
+            uint32_t cj = 0, bj = 0, mj = 0, pj = 0;
+            bool cand = false;
+            if (kRuns && lo == ci) ++lo;
+            if (lo < hi) {
+                cj = lo++;
+                // the parent link loads beside the record (every grid has one)
+                pj = load_acq(&parent[cj]);
+                const uint4 rc = rank[cj];
+                const uint32_t rj = rc.x;
+                if (rj != kNone) {
+                    bj = rc.y;
+                    mj = rc.z;
+                    cand = mj <= kSmallSet || rj > (uint32_t)r;
+                }
             }
-        }
-        // root of each candidate's set, kept as the hint for a union
-        uint32_t root_j = cand ? uf_find_at(parent, cj, pj) : 0u;
-        const bool pend_l = cand && root_j != ri;
-        const uint64_t cands = ballot(cand);
-        uint64_t pend = ballot(pend_l);
-        n_pairs += (unsigned long long)popc64(cands);
-        n_skip += (unsigned long long)(popc64(cands) - popc64(pend));
-        // pairs with a core set beyond the LDS bitmaps, or (eager runs) with
-        // a heavy one, go to the queue
-        const uint64_t over =
-            ballot(pend_l && (si_huge || si_heavy || mj > 64u * words || (huge.pairs && mj >= (uint32_t)kHeavyCore)));
-        if (over) {
-            defer_pairs(huge, over, ci, cj, gv.b.hdr);
-            pend &= ~over;
-        }
-        float my_z0 = 0.f, my_z1 = 0.f;
-        uint32_t my_ra = 0, my_rb = 0;
-        if constexpr (kLearned) {
-            // score every pending pair: features per lane, the scorer on the
-            // matrix cores 16 pairs at a time
-            const bool pl = ((pend >> lane) & 1ull) && mj <= 64u * words;
-            const uint64_t pm = ballot(pl);
-            const uint32_t rk = (uint32_t)popc64(pm & lanemask_lt());
-            const int np = popc64(pm);
-            float f[kFeat];
-            uint32_t ra = 0, rb = 0;
-            if (pl) pair_setup<D>(gv, co, prop.sum, ci, cj, eps, f, ra, rb);
-            my_ra = ra;
-            my_rb = rb;
-            for (int b0 = 0; b0 < np; b0 += 16) {
-                if (pl && rk >= (uint32_t)b0 && rk < (uint32_t)b0 + 16u) {
+            // root of each candidate's set, kept as the hint for a union
+            uint32_t root_j = cand ? uf_find_at(parent, cj, pj) : 0u;
+            const bool pend_l = cand && root_j != ri;
+            const uint64_t cands = ballot(cand);
+            uint64_t pend = ballot(pend_l);
+            n_pairs += (unsigned long long)popc64(cands);
+            n_skip += (unsigned long long)(popc64(cands) - popc64(pend));
+            // pairs with a core set beyond the LDS bitmaps, or (eager runs) with
+            // a heavy one, go to the queue
+            const uint64_t over =
+                ballot(pend_l && (si_huge || si_heavy || mj > 64u * words || (huge.pairs && mj >= (uint32_t)kHeavyCore)));
+            if (over) {
+                defer_pairs(huge, over, ci, cj, gv.b.hdr);
+                pend &= ~over;
+            }
+            float my_z0 = 0.f, my_z1 = 0.f;
+            uint32_t my_ra = 0, my_rb = 0;
+            if constexpr (kLearned) {
+                // score every pending pair: features per lane, the scorer on the
+                // matrix cores 16 pairs at a time
+                const bool pl = ((pend >> lane) & 1ull) && mj <= 64u * words;
+                const uint64_t pm = ballot(pl);
+                const uint32_t rk = (uint32_t)popc64(pm & lanemask_lt());
+                const int np = popc64(pm);
+                float f[kFeat];
+                uint32_t ra = 0, rb = 0;
+                if (pl) pair_setup<D>(gv, co, prop.sum, ci, cj, eps, f, ra, rb);
+                my_ra = ra;
+                my_rb = rb;
+                for (int b0 = 0; b0 < np; b0 += 16) {
+                    if (pl && rk >= (uint32_t)b0 && rk < (uint32_t)b0 + 16u) {
 #pragma unroll
-                    for (int k = 0; k < kFeat; ++k) S[w].feat[rk - b0][k] = (_Float16)f[k];
+                        for (int k = 0; k < kFeat; ++k) S[w].feat[rk - b0][k] = (_Float16)f[k];
+                    }
+                    wave_sync();
+                    float z0[4], z1[4];
+                    mlp_forward_mfma(W[0], S[w], z0, z1);
+                    if ((lane & 15) == 0) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) zb[w][b0 + 4 * (lane >> 4) + j] = make_float2(z0[j], z1[j]);
+                    }
+                    wave_sync();
+                }
+                if (pl) {
+                    my_z0 = zb[w][rk].x;
+                    my_z1 = zb[w][rk].y;
                 }
                 wave_sync();
-                float z0[4], z1[4];
-                mlp_forward_mfma(W[0], S[w], z0, z1);
-                if ((lane & 15) == 0) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) zb[w][b0 + 4 * (lane >> 4) + j] = make_float2(z0[j], z1[j]);
+            }
+            while (pend) {
+                int l;
+                if constexpr (kLearned) {
+                    // the remaining pair with the largest merge logit (ties: lowest
+                    // lane); every pending lane's key is >= 64 > 0, the others' key
+                    const uint64_t key = ((pend >> lane) & 1ull)
+                                             ? (((uint64_t)orderable(my_z0) << 7) | 64ull | (uint64_t)(kWave - 1 - lane))
+                                             : 0ull;
+                    const uint64_t best = ~wave_min_u64(~key);
+                    l = kWave - 1 - (int)(best & 63ull);
+                } else {
+                    l = ffs64(pend);
                 }
-                wave_sync();
-            }
-            if (pl) {
-                my_z0 = zb[w][rk].x;
-                my_z1 = zb[w][rk].y;
-            }
-            wave_sync();
-        }
-        while (pend) {
-            int l;
-            if constexpr (kLearned) {
-                // the remaining pair with the largest merge logit (ties: lowest
-                // lane); every pending lane's key is >= 64 > 0, the others' key
-                const uint64_t key = ((pend >> lane) & 1ull)
-                                         ? (((uint64_t)orderable(my_z0) << 7) | 64ull | (uint64_t)(kWave - 1 - lane))
-                                         : 0ull;
-                const uint64_t best = ~wave_min_u64(~key);
-                l = kWave - 1 - (int)(best & 63ull);
-            } else {
-                l = ffs64(pend);
-            }
-            pend &= ~(1ull << l);
-            sj.base = readlane(bj, l);
-            sj.m = readlane(mj, l);
-            sj.words = (sj.m + kWave - 1) / kWave;
-            uint32_t it = 0;
-            int yes;
-            if constexpr (kLearned) {
-                if (__shfl(my_z1, l) > 0.f)
-                    yes = fast_merging<D, kWide>(sj, si, readlane(my_rb, l), T, Tm, eps, n_dist, it);
-                else
-                    yes = fast_merging<D, kWide>(si, sj, readlane(my_ra, l), T, Tm, eps, n_dist, it);
-            } else {
-                // start in the larger set, so that the first nearest-point
-                // search (on a yes the only one) runs over the smaller set
-                const bool swap = sj.m > si.m;
-                int32_t ps[D];
-                if (swap) load_point<D>(sj, 0u, ps);
+                pend &= ~(1ull << l);
+                sj.base = readlane(bj, l);
+                sj.m = readlane(mj, l);
+                sj.words = (sj.m + kWave - 1) / kWave;
+                uint32_t it = 0;
+                int yes;
+                if constexpr (kLearned) {
+                    if (__shfl(my_z1, l) > 0.f)
+                        yes = fast_merging<D, kWide>(sj, si, readlane(my_rb, l), T, Tm, eps, n_dist, it);
+                    else
+                        yes = fast_merging<D, kWide>(si, sj, readlane(my_ra, l), T, Tm, eps, n_dist, it);
+                } else {
+                    // start in the larger set, so that the first nearest-point
+                    // search (on a yes the only one) runs over the smaller set
+                    const bool swap = sj.m > si.m;
+                    int32_t ps[D];
+                    if (swap) load_point<D>(sj, 0u, ps);
 #pragma unroll
-                for (int k = 0; k < D; ++k) ps[k] = swap ? ps[k] : p0[k];
-                yes = fast_merging_from<D, kWide>(swap ? sj : si, swap ? si : sj, ps, T, Tm, eps, n_dist, it);
-            }
-            ++n_test;
-            n_pts += si.m + sj.m;
-            n_iter += it;
-            max_it = it > max_it ? it : max_it;
-            if (yes < 0) {
-                if (lane == 0) atomicOr(&gv.b.hdr->err, kErrMergeRunaway);
-                continue;
-            }
-            if (yes) {
-                ++n_yes;
-                const uint32_t rl = readlane(root_j, l);
-                uint32_t root = 0;
-                if (lane == 0) root = uf_union_from(parent, ri, rl);
-                ri = readlane(root, 0);
-                if (pend) {
-                    // the union may have joined g_i to other pending grids' sets
-                    const bool pl = (pend >> lane) & 1ull;
-                    if (pl) root_j = uf_find(parent, root_j);
-                    const bool still = pl && root_j != ri;
-                    const uint64_t np = ballot(still);
-                    n_skip += (unsigned long long)(popc64(pend) - popc64(np));
-                    pend = np;
+                    for (int k = 0; k < D; ++k) ps[k] = swap ? ps[k] : p0[k];
+                    yes = fast_merging_from<D, kWide>(swap ? sj : si, swap ? si : sj, ps, T, Tm, eps, n_dist, it);
+                }
+                ++n_test;
+                n_pts += si.m + sj.m;
+                n_iter += it;
+                max_it = it > max_it ? it : max_it;
+                if (yes < 0) {
+                    if (lane == 0) atomicOr(&gv.b.hdr->err, kErrMergeRunaway);
+                    continue;
+                }
+                if (yes) {
+                    ++n_yes;
+                    const uint32_t rl = readlane(root_j, l);
+                    uint32_t root = 0;
+                    if (lane == 0) root = uf_union_from(parent, ri, rl);
+                    ri = readlane(root, 0);
+                    if (pend) {
+                        // the union may have joined g_i to other pending grids' sets
+                        const bool pl = (pend >> lane) & 1ull;
+                        if (pl) root_j = uf_find(parent, root_j);
+                        const bool still = pl && root_j != ri;
+                        const uint64_t np = ballot(still);
+                        n_skip += (unsigned long long)(popc64(pend) - popc64(np));
+                        pend = np;
+                    }
                 }
             }
-        }
+        } while (kRuns && ballot(lo < hi));
     }
     if (stats && lane == 0) flush_stats(stats, r, n_pairs, n_skip, n_test, n_yes, n_iter, max_it, n_dist, n_pts);
 }
 
 hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
-                        const uint2* nei_up,
+                        const uint2* nei_up, const RunSource* runs,
                         const uint32_t* ldf_list, const uint4* rank, int64_t ncc, int64_t n_small, int64_t max_core,
                         int waves, int small_lanes, bool tiny_done, const HugeQueue& huge, bool wide,
                         uint32_t* parent, MergeStats* stats, const __half* proposal, const CellSummary* sum,
-                        hipStream_t st) {
+                        uint32_t* family_root, hipStream_t st) {
     const Proposal prop{proposal, sum};
     if (ncc == 0) return hipSuccess;
+    if (runs && (stats || wide || proposal || tiny_done || g.D < kMinRunD)) return hipErrorInvalidValue;
     // n_small >= 0: the visiting order puts the n_small tiny core grids first
     // (ascending core count).  n_small == -2: the same order, but the count
     // is only known on the device (split); both kernels get grids for all
@@ -421,7 +634,31 @@ hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei
         const int S = small_lanes == 16 ? 16 : kWave;
         const int64_t per_block = (int64_t)kWavesPerBlock * (kWave / S);
         const dim3 blocks = grid_of((s1 + per_block - 1) / per_block), threads(kBlock);
-        if (wide && S == 16)
+        if (runs) {
+            const dim3 fam = grid_of((runs->families + kWavesPerBlock * kFamilies - 1) / (kWavesPerBlock * kFamilies));
+            auto mark = [&](int D) {
+                family_root_kernel<<<dim3(grid_for(runs->families)), threads, 0, st>>>(
+                    runs->t.level_count + (D - 1), runs->t.child[D - 1], rank, parent, family_root);
+            };
+            auto phases = [&]() -> hipError_t {
+                GD_DISPATCH_D(g.D, ({
+                                  if constexpr (D >= kMinRunD) {
+                                      merge_family_kernel<D, kPhaseFace>
+                                          <<<fam, threads, 0, st>>>(g, c, *runs, rank, family_root, parent);
+                                      mark(D);
+                                      merge_family_kernel<D, kPhaseEdge>
+                                          <<<fam, threads, 0, st>>>(g, c, *runs, rank, family_root, parent);
+                                      mark(D);
+                                      merge_family_kernel<D, kPhaseAll>
+                                          <<<fam, threads, 0, st>>>(g, c, *runs, rank, family_root, parent);
+                                  }
+                              }));
+                return hipGetLastError();
+            };
+            const hipError_t e = phases();
+            if (e != hipSuccess) return e;
+        }
+        else if (wide && S == 16)
             GD_DISPATCH_D(g.D, (merge_small_kernel<D, true, 16><<<blocks, threads, 0, st>>>(
                                    g, c, nei_off, nei, nei_up, ldf_list, rank, 0, s1, split, parent, stats)));
         else if (wide)
@@ -447,15 +684,22 @@ hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei
     const bool learned = prop.weights && !wide &&
                          lds + sizeof(MlpMfma) + kWavesPerBlock * (sizeof(MlpMfmaScratch) + sizeof(float2) * kWave) <=
                              65536;
-    if (learned) {
-        GD_DISPATCH_D(g.D, (merge_big_kernel<D, true, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                               g, c, nei_off, nei, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
+    if (runs) {
+        GD_DISPATCH_D(g.D, ({
+                          if constexpr (D >= kMinRunD)
+                              merge_big_kernel<D, false, false, true><<<blocks, dim3(wpb * kWave), lds, st>>>(
+                                  g, c, nullptr, nullptr, *runs, ldf_list, rank, b0, ncc, split, words, huge, parent,
+                                  nullptr, prop);
+                      }));
+    } else if (learned) {
+        GD_DISPATCH_D(g.D, (merge_big_kernel<D, true, false, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
+                               g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
     } else if (wide) {
-        GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, true><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                               g, c, nei_off, nei, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
+        GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, true, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
+                               g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
     } else {
-        GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                               g, c, nei_off, nei, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
+        GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, false, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
+                               g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
     }
     return hipGetLastError();
 }
@@ -655,6 +899,30 @@ __global__ __launch_bounds__(kBlock) void huge_scan_kernel(const uint32_t* ncell
         atomicAdd(sum, (unsigned long long)(nei_off[c + 1] - nei_off[c] + 1));
 }
 
+// The same with neighbours as runs: a wave checks 64 grids and counts the
+// neighbours of each heavy one.
+template <int D>
+__global__ __launch_bounds__(kBlock) void huge_scan_runs_kernel(GridView gv, CoreOut co, RunSource rs,
+                                                                unsigned long long* sum) {
+    const int lane = lane_id();
+    const int64_t c0 = ((int64_t)blockIdx.x * kWavesPerBlock + wave_id()) * kWave;
+    const int64_t ncell = *gv.ncell_dev;
+    uint64_t todo = ballot(c0 + lane < ncell && co.core_cnt[c0 + lane < ncell ? c0 + lane : 0] >= (uint32_t)kHeavyCore);
+    for (; todo; todo &= todo - 1ull) {
+        const int64_t c = c0 + ffs64(todo);
+        RunCursor<D> rc;
+        rc.open(rs, gv, c);
+        unsigned long long m = 0;
+        for (uint64_t e = rc.e0; e < rc.e1; e += kWave) {
+            uint32_t lo = 0, hi = 0;
+            if (e + lane < rc.e1) rc.run_of(rs, rs.ent[e + lane], lo, hi);
+            m += hi - lo;
+        }
+        m = wave_sum(m);  // the own grid is among them
+        if (lane == 0) atomicAdd(sum, m);
+    }
+}
+
 // Persistent: workgroup k takes queued pairs k, k + blocks, ... (every
 // workgroup leaves once it passes the queue's length, read once at entry),
 // and runs FastMerging on each with all of its waves (fastmerge_block.hpp).
@@ -729,9 +997,17 @@ __global__ __launch_bounds__(kCoopWaves * kWave) void merge_heavy_kernel(GridVie
     }
 }
 
-hipError_t launch_huge_scan(const GridView& g, const CoreOut& c, const uint64_t* nei_off, unsigned long long* sum,
-                            hipStream_t st) {
+hipError_t launch_huge_scan(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const RunSource* runs,
+                            unsigned long long* sum, hipStream_t st) {
     if (g.ncell == 0) return hipSuccess;
+    if (runs) {
+        GD_DISPATCH_D(g.D, ({
+                          if constexpr (D >= kMinRunD)
+                              huge_scan_runs_kernel<D><<<dim3(grid_for(g.ncell, kWavesPerBlock * kWave)), dim3(kBlock),
+                                                         0, st>>>(g, c, *runs, sum);
+                      }));
+        return hipGetLastError();
+    }
     huge_scan_kernel<<<dim3(grid_for(g.ncell)), dim3(kBlock), 0, st>>>(g.ncell_dev, c.core_cnt, nei_off, sum);
     return hipGetLastError();
 }

@@ -1,0 +1,301 @@
+// Lists of neighbouring tree nodes for sparse data (runs.hpp): for every
+// node of level l of the grid tree, the nodes of that level within reach (Eq.
+// (2) over the dimensions so far), the node itself included; and, for the last
+// level, the lists Nei(g) themselves.
+//
+// Level by level: the nodes within reach of node a are children of the nodes
+// within reach of a's parent, so S lanes per node take the entries of the
+// parent's list, find each entry's children within the window (child_window)
+// and write them.  All lanes of a group work on one list at every level,
+// where a walk per grid from the root (neighbors.hip) is one long chain of
+// dependent loads per lane with lanes in different loops.
+//
+// 10M 5-D points (6.9M grids, 3.1M families): walks counted and wrote 5.1e9
+// list entries in 52 ms; these lists hold 0.8e9 and take 9.5 ms.  2M and 1M
+// 7-D points: 7.1 -> 0.9 and 5.1 -> 0.6 ms.  The passes over long lists are
+// bound by vector instructions (72-77% of the issue rate), most of them the key
+// search and the entries' arithmetic; pass 2 therefore writes one entry per
+// lane and round rather than each lane its own run (6.3 -> 5.7 ms).  The lists
+// of the grids themselves in two and three dimensions: 43 -> 35 us for 20k
+// points in two, 131 -> 79 us in three (the read-back between the passes
+// included), even at millions of grids.
+#include <algorithm>
+
+#include "launch.hpp"
+#include "runs.hpp"
+#include "scan.hpp"
+
+namespace gd {
+
+namespace {
+
+struct LevelArgs {
+    const Inst* inst;
+    const int32_t* key0;        // instance id of each level-0 node
+    const uint32_t* child0;
+    const uint32_t* par1;       // level-0 node of each level-1 node
+    const int32_t* pkey;        // keys of level l - 1 (l == 2: of the level-1 nodes)
+    const int32_t* key;         // keys of level l
+    const uint32_t* child;      // children of the level-(l-1) nodes
+    const uint32_t* par;        // parent of each level-l node
+    const uint32_t* excl;       // the last level: level-(D-1) nodes before each grid (par is not kept)
+    const uint32_t* nodes;      // device: nodes of level l
+    const uint32_t* pnodes;     // device: nodes of level l - 1
+    const uint64_t* poff;       // lists of level l - 1 (l >= 3)
+    const uint32_t* pent;
+    uint64_t pcap;              // entries pent holds
+    uint32_t* cnt;              // pass 1: list length of each node
+    uint32_t* near;             // touching entries of each node, listed first (nullptr: order kept)
+    const uint64_t* off;        // pass 2: where each list goes
+    uint32_t* ent;
+    uint64_t cap;
+    uint2* up;                  // the last level: range of the larger grids in each list
+    Header* hdr;
+};
+
+// kFirst: l == 2, whose parents' neighbours are the kNear places around them.
+// kGrids: l == D, entries are grid indices and the own grid is left out.
+template <int S, bool kFirst, bool kGrids, bool kFill>
+__global__ __launch_bounds__(kBlock) void level_kernel(LevelArgs A) {
+    constexpr int G = kWave / S;
+    // pass 2 of long lists: the chunk's runs, written out one entry per lane
+    constexpr bool kFlat = kFill && !kGrids && S == kWave;
+    __shared__ uint32_t s_at[kFlat ? kWavesPerBlock : 1][kWave];    // first child of a lane's run, minus its place
+    __shared__ uint32_t s_how[kFlat ? kWavesPerBlock : 1][kWave];   // the entry's low bits
+    __shared__ uint32_t s_head[kFlat ? kWavesPerBlock : 1][kWave];  // lane + 1 of the run that starts here
+    const int lane = lane_id();
+    const int sub = lane % S;
+    const int64_t nodes = *A.nodes;
+    const int64_t a = (xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + wave_id()) * G + lane / S;
+    // a list beyond its buffer (a sync-free run that met more than it was
+    // planned for): nothing is read or written
+    if (kFill && A.off[nodes] > A.cap) {
+        if (block_id() == 0 && threadIdx.x == 0) atomicOr(&A.hdr->err, kErrNeiOverflow);
+        return;
+    }
+    if (!kFirst && A.poff[*A.pnodes] > A.pcap) {
+        if (!kFill && a < nodes && sub == 0) A.cnt[a] = 0;
+        return;
+    }
+    if (a >= nodes) return;
+    const uint32_t p = kGrids ? A.excl[a + 1] - 1 : A.par[a];
+    const int32_t k = A.key[a];
+    uint64_t e0 = 0, e1 = kNear, pos = 0;
+    uint32_t lo1 = 0, hi1 = 0;
+    int32_t k1 = 0;
+    int dk = 0;
+    if constexpr (kFirst) {
+        const uint32_t i0 = A.par1[p];
+        lo1 = A.child0[i0];
+        hi1 = A.child0[i0 + 1];
+        k1 = A.pkey[p];
+        dk = A.inst[A.key0[i0]].d;
+    } else {
+        e0 = A.poff[p];
+        e1 = A.poff[p + 1];
+    }
+    const bool split = !kGrids && A.near != nullptr;
+    uint64_t far = 0;  // where the next entry that does not touch goes
+    if constexpr (kFill) {
+        pos = A.off[a];
+        if (split) far = pos + A.near[a];
+    }
+    uint32_t total = 0, nears = 0;
+    uint32_t own = 0, above = 0;  // kGrids: entries before the own grid, entries above it (this lane's)
+    const uint64_t pos0 = pos;
+    for (uint64_t e = e0; e < e1; e += S) {
+        bool in = e + sub < e1;
+        uint32_t b = 0;
+        int budget = 1, touch = 0;
+        if constexpr (kFirst) {
+            const int64_t x = (int64_t)p + near_step(sub);
+            in = in && x >= (int64_t)lo1 && x < (int64_t)hi1;
+            b = in ? (uint32_t)x : p;
+            const int dl = A.pkey[b] - k1;
+            const int ad = dl < 0 ? -dl : dl;
+            in = in && ad <= walk_window(dk);
+            const int gap = ad > 0 ? ad - 1 : 0;
+            budget = dk - gap * gap;
+            touch = touch_step(0, ad);
+        } else if (in) {
+            const uint32_t v = A.pent[e + sub];
+            b = entry_node(v);
+            budget = entry_budget(v);
+            touch = entry_touch(v);
+        }
+        uint32_t c0 = 0, c1 = 0, lo, hi, mn;
+        if (in) node_children(A.child, b, c0, c1);
+        child_window<!kGrids && !kFlat>(A.key, c0, c1, k, walk_window(budget), lo, hi, mn);
+        uint32_t m = hi - lo;
+        if (!split || touch == kApart) mn = 0;
+        if constexpr (!kFill) {
+            total += m;
+            nears += mn;
+        } else if constexpr (kFlat) {
+            const int w = wave_id();
+            const uint32_t incl = wave_incl_scan(m), excl = incl - m, tot = last_lane(incl);
+            s_at[w][lane] = lo - excl;
+            s_how[w][lane] = node_entry(0u, touch, budget);
+            uint32_t carry = 0;
+            for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
+                // the run of each place: see core_mark_runs_kernel
+                s_head[w][lane] = 0;
+                wave_sync();
+                if (m != 0 && excl >= t0 && excl < t0 + kWave) s_head[w][excl - t0] = (uint32_t)lane + 1u;
+                wave_sync();
+                uint32_t j = wave_max_scan(s_head[w][lane]);
+                j = j ? j : carry;
+                carry = last_lane(j);
+                j = (j ? j : 1u) - 1u;
+                const bool v = t0 + lane < tot;
+                const uint32_t x = v ? s_at[w][j] + t0 + lane : (uint32_t)a;
+                const uint32_t how = s_how[w][j];
+                const int dl = A.key[x] - k;
+                const int ad = dl < 0 ? -dl : dl;
+                const int gap = ad > 0 ? ad - 1 : 0;
+                const int t = touch_step(entry_touch(how), ad);
+                const uint32_t y = node_entry(x, t, entry_budget(how) - gap * gap);
+                const uint64_t nm = ballot(v && split && t != kApart), fm = ballot(v) & ~nm, lt = lanemask_lt();
+                const bool nr = (nm >> lane) & 1ull;
+                uint64_t& fpos = split ? far : pos;
+                const uint64_t to = nr ? pos + popc64(nm & lt) : fpos + popc64(fm & lt);
+                if (v) A.ent[to] = y;
+                fpos += popc64(fm);
+                if (split) pos += popc64(nm);
+            }
+            wave_sync();
+        } else {
+            // the own grid is written nowhere
+            if (kGrids && in && b == p) --m;
+            const uint32_t f = m - mn;
+            const uint32_t fi = group_sum_scan<S>(f), ni = split ? group_sum_scan<S>(mn) : 0u;
+            uint64_t wf = (split ? far : pos) + (fi - f), wn = pos + (ni - mn);
+            for (uint32_t x = lo; x < hi; ++x) {
+                if constexpr (kGrids) {
+                    if (x == (uint32_t)a) {
+                        own = (uint32_t)(wf - pos0);
+                    } else {
+                        A.ent[wf++] = x;
+                        above += x > (uint32_t)a ? 1u : 0u;
+                    }
+                } else {
+                    const int dl = A.key[x] - k;
+                    const int ad = dl < 0 ? -dl : dl;
+                    const int gap = ad > 0 ? ad - 1 : 0;
+                    const int t = touch_step(touch, ad);
+                    uint64_t& to = split && t != kApart ? wn : wf;
+                    A.ent[to++] = node_entry(x, t, budget - gap * gap);
+                }
+            }
+            const uint32_t ft = __shfl(fi, S - 1, S);
+            if (split) {
+                far += ft;
+                pos += __shfl(ni, S - 1, S);
+            } else {
+                pos += ft;
+            }
+        }
+    }
+    if constexpr (!kFill) {
+#pragma unroll
+        for (int o = S / 2; o > 0; o >>= 1) {
+            total += __shfl_xor(total, o, S);
+            nears += __shfl_xor(nears, o, S);
+        }
+        if (sub == 0) {
+            A.cnt[a] = total - (kGrids ? 1u : 0u);
+            if (split) A.near[a] = nears;
+        }
+    } else if constexpr (kGrids) {
+#pragma unroll
+        for (int o = S / 2; o > 0; o >>= 1) {
+            own += __shfl_xor(own, o, S);
+            above += __shfl_xor(above, o, S);
+        }
+        if (sub == 0) A.up[a] = make_uint2(own, own + above);
+    }
+}
+
+struct NodeTotal {
+    const uint32_t* cnt;
+    const uint32_t* nodes;
+    __device__ uint64_t operator()(int64_t a) const { return a < (int64_t)*nodes ? (uint64_t)cnt[a] : 0ull; }
+};
+
+struct NodeOffWriter {
+    uint64_t* off;
+    const uint32_t* nodes;
+    uint64_t* total;
+    __device__ void operator()(int64_t a, uint64_t ex, uint64_t) const {
+        if (a > (int64_t)*nodes) return;
+        off[a] = ex;
+        if (a == (int64_t)*nodes) *total = ex;
+    }
+};
+
+LevelArgs level_args(const GridView& g, const TreeView& t, const NodeLists& nl, int l) {
+    LevelArgs A{};
+    A.inst = g.b.inst;
+    A.key0 = t.key[0];
+    A.child0 = t.child[0];
+    A.par1 = nl.par[1];
+    A.pkey = t.key[l - 1];
+    A.key = t.key[l];
+    A.child = t.child[l - 1];
+    A.par = nl.par[l];
+    A.excl = nl.excl;
+    A.nodes = t.level_count + l;
+    A.pnodes = t.level_count + (l - 1);
+    A.poff = nl.off[(l - 1) & 1];
+    A.pent = nl.ent[(l - 1) & 1];
+    A.pcap = nl.cap[(l - 1) & 1];
+    A.cnt = nl.cnt;
+    A.near = nl.near;
+    A.off = nl.off[l & 1];
+    A.ent = nl.ent[l & 1];
+    A.cap = nl.cap[l & 1];
+    A.up = nl.up;
+    A.hdr = g.b.hdr;
+    return A;
+}
+
+template <bool kFill>
+hipError_t launch_level(const GridView& g, const LevelArgs& A, int l, int64_t nodes, int lanes, hipStream_t st) {
+    const dim3 threads(kBlock);
+    auto blocks = [&](int S) { return grid_of((nodes * S + kBlock - 1) / kBlock); };
+    const bool grids = l == g.D;
+    if (l == 2 && grids)
+        level_kernel<8, true, true, kFill><<<blocks(8), threads, 0, st>>>(A);
+    else if (l == 2)
+        level_kernel<8, true, false, kFill><<<blocks(8), threads, 0, st>>>(A);
+    else if (grids && lanes == 8)
+        level_kernel<8, false, true, kFill><<<blocks(8), threads, 0, st>>>(A);
+    else if (grids)
+        level_kernel<16, false, true, kFill><<<blocks(16), threads, 0, st>>>(A);
+    else if (lanes <= 16)
+        level_kernel<16, false, false, kFill><<<blocks(16), threads, 0, st>>>(A);
+    else
+        level_kernel<kWave, false, false, kFill><<<blocks(kWave), threads, 0, st>>>(A);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_level_count(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
+                              int lanes, uint64_t* partial, hipStream_t st) {
+    if (nodes <= 0) return hipSuccess;
+    const LevelArgs A = level_args(g, t, nl, l);
+    const hipError_t e = launch_level<false>(g, A, l, nodes, lanes, st);
+    if (e != hipSuccess) return e;
+    return scan_apply<uint64_t>(NodeTotal{nl.cnt, A.nodes}, nodes + 1,
+                                NodeOffWriter{nl.off[l & 1], A.nodes, &g.b.hdr->nei_total}, (uint64_t*)nullptr, partial,
+                                st);
+}
+
+hipError_t launch_level_fill(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
+                             int lanes, hipStream_t st) {
+    if (nodes <= 0) return hipSuccess;
+    return launch_level<true>(g, level_args(g, t, nl, l), l, nodes, lanes, st);
+}
+
+}  // namespace gd

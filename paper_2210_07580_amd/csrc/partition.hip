@@ -362,11 +362,14 @@ __global__ void plan_check_kernel(Header* h, int stage, int64_t cap_a, int64_t c
         bad |= (int64_t)h->ncell > cap_a;
     else if (stage == 1)
         bad |= h->nei_total > (uint64_t)cap_a;
-    else
+    else if (stage == 2)
         bad |= (int64_t)h->counts[1] > cap_a || (int64_t)h->counts[2] > cap_b;
+    else
+        bad |= (int64_t)h->level_count[cap_a] > cap_b;
     if (bad) {
         h->err |= kErrPlan;
         h->ncell = 0;
+        for (int l = 0; l < kMaxLevels; ++l) h->level_count[l] = 0;
         h->nei_total = 0;
         h->counts[1] = 0;
     }
@@ -844,6 +847,7 @@ struct TreeBuild {
     int32_t* key[kMaxLevels];
     uint32_t* child[kMaxLevels];
     const uint32_t* excl[kMaxLevels];  // per level: nodes before grid c (c in [0, ncell])
+    uint32_t* par[kMaxLevels];         // per level: each node's parent (nullptr: not kept)
 };
 
 __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict__ ck, int64_t stride,
@@ -855,6 +859,7 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
         if (c == ncell || tb.excl[l][c + 1] != tb.excl[l][c]) {
             const uint32_t a = tb.excl[l][c];
             if (c < ncell) tb.key[l][a] = ck[(int64_t)l * stride + c];
+            if (c < ncell && l > 0 && tb.par[l]) tb.par[l][a] = tb.excl[l - 1][c + 1] - 1;
             // children: the level-(l+1) node that starts at grid c; the last level's nodes are the grids
             tb.child[l][a] = (l + 2 < levels) ? tb.excl[l + 1][c] : (uint32_t)c;
         }
@@ -862,13 +867,14 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
 }
 
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
-                       uint32_t* const* tchild, hipStream_t st) {
+                       uint32_t* const* tchild, uint32_t* const* tpar, hipStream_t st) {
     const int levels = g.D + 1;
     uint32_t* level_count = g.b.hdr->level_count;
     TreeBuild tb{};
     for (int l = 0; l + 1 < levels; ++l) {
         tb.key[l] = tkey[l];
         tb.child[l] = tchild[l];
+        tb.par[l] = tpar && l > 0 ? tpar[l] : nullptr;
         tb.excl[l] = level_excl + (int64_t)l * (g.ncell + 1);
     }
     // several levels per scan: counts are at most ncell + 1
