@@ -350,7 +350,7 @@ constexpr int64_t kMaxCoreBits = 262144;
 // Core sets from this size on are merged by a workgroup of kCoopWaves waves
 // per pair (in eager runs; graph replays keep one wave per grid).
 constexpr int64_t kHeavyCore = 8192;
-constexpr int kCoopWaves = 8;
+constexpr int kCoopWaves = 16;
 // Pairs (g_i, g_j) deferred by the LDS kernels.  pairs == nullptr: no queue
 // (a planned run); meeting a larger set then raises kErrCoreCap.
 struct HugeQueue {
