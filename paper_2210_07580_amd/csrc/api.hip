@@ -733,7 +733,9 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     }
     // eps above the 32-bit bound anywhere in the batch: 64-bit distances
     const bool wide = max_eps > GD_EPS_MAX;
-    const bool prune = n >= 1024 * std::max<int64_t>(ncell, 1);
+    // large grids: streams of thousands of points split into tasks (the queue
+    // and its counts lie in arrays of the steps that follow)
+    const bool split = n >= kSplitMean * std::max<int64_t>(ncell, 1);
     // offset order pays for itself through core marking's early exit only
     // when grids hold several points; sparse grids take walk order, and so do
     // more than 2^19 grids, whose ordered fill (scattered over the offset
@@ -748,7 +750,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     // that takes no further memory.
     bool runs = plan ? plan->runs
                      : D >= kMinRunD && sparse && ctx->nei_query == kNeiAuto && ctx->nei_mode == 0 && !ctx->bfs &&
-                           !stats && !ctx->proposal_on && !bounded && !wide && !prune && ncell < kMaxRunNodes;
+                           !stats && !ctx->proposal_on && !bounded && !wide && !split && ncell < kMaxRunNodes;
     bool by_level = plan ? plan->by_level
                          : (D == 2 || (D == 3 && !bounded)) && !(!ctx->bfs && ctx->nei_mode == 2) &&
                                (ctx->nei_query == kNeiTreeWalkOrder || (ctx->nei_query == kNeiAuto && sparse)) &&
@@ -953,8 +955,16 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     if (walk)
         GD_TRY(launch_core_walk(g, t, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr, wide, st));
     else
+    {
+        SplitQueue sq{};
+        sq.tasks = L.rank;
+        sq.cap = (uint32_t)n;
+        sq.count = &Hd->split[0];
+        sq.left = (uint32_t*)L.cell_label;
+        sq.hits = L.list;
         GD_TRY(launch_core_mark(g, L.nei_off, nei, rs, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
-                                max_eps, min_minpts, prune, st));
+                                max_eps, min_minpts, split ? &sq : nullptr, st));
+    }
     ctx->mark(P_CORE_MARK, 1);
     CoreOut co{};
     co.core = L.core;
@@ -1081,7 +1091,16 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     if (walk)
         GD_TRY(launch_border_walk(g, co, t, L.cell_label, wide, st));
     else
-        GD_TRY(launch_output(g, co, L.nei_off, nei, rs, L.cell_label, wide, small_lanes, free_words, st));
+    {
+        SplitQueue sq{};
+        sq.best = (uint64_t*)L.rank;
+        sq.tasks = L.rank + (n + 1) / 2;
+        sq.cap = (uint32_t)(n / 2);
+        sq.count = &Hd->split[1];
+        sq.left = L.root_min;
+        GD_TRY(launch_output(g, co, L.nei_off, nei, rs, L.cell_label, wide, small_lanes, free_words,
+                             split ? &sq : nullptr, st));
+    }
     ctx->mark(P_OUTPUT, 1);
     gd_ctx::Lists lists{};
     if (runs) {

@@ -157,12 +157,14 @@ size_t output_table_bytes(int bits, int key_bytes) {
     return (size_t)((1ll << bits) + 1) * (key_bytes == 4 ? 8 : 16);
 }
 
-// Border and noise points of grid c (rows [st, st + k)), one wave.
-template <int D, bool kWide>
+// Border and noise points of grid c (rows [st, st + k)), one wave.  kSplit:
+// neighbours of kSplitRows core points and more come last, as tasks for
+// border_tasks_kernel (or streamed here if the queue is full).
+template <int D, bool kWide, bool kSplit>
 __device__ __forceinline__ void border_grid(const GridView& gv, const CoreOut& co, const uint64_t* __restrict__ nei_off,
                                             const uint32_t* __restrict__ nei, const int32_t* __restrict__ cell_label,
                                             int64_t c, uint32_t st, uint32_t k, uint32_t* s_start, uint32_t* s_excl,
-                                            int32_t* s_lab) {
+                                            int32_t* s_lab, const SplitQueue& sq) {
     const int lane = lane_id();
     const Inst& I = cell_inst(gv, c);
     const uint32_t off = (uint32_t)I.off;  // cluster ids and output slots are local to the instance
@@ -175,6 +177,7 @@ __device__ __forceinline__ void border_grid(const GridView& gv, const CoreOut& c
     const uint64_t e0 = nei_off[c], e1 = nei_off[c + 1];
     const double side = D <= 4 ? (double)I.eps / sqrt((double)I.d) : 0.0;
     const double lim = (double)I.eps * (double)I.eps * (1.0 + 1e-9) + 1.0;
+    uint32_t tasks = 0;
     for (uint32_t qb = 0; qb < k; qb += kWave) {
         const uint32_t s = st + qb + lane;
         const bool v = qb + lane < k;
@@ -189,68 +192,170 @@ __device__ __forceinline__ void border_grid(const GridView& gv, const CoreOut& c
         int32_t qx[D];
         load_row<D>(gv.crd, v ? s : st, qx);
         uint64_t best = own_best;  // lane i: best candidate of query i
-        for (uint64_t e = e0; e < e1; e += kWave) {
+        bool later = false;
+        // core points of the neighbour this lane takes from the list that can
+        // still improve an open query (0: none, or of the other pass's size)
+        auto candidate = [&](uint64_t idx, bool large, uint32_t& cc) -> uint32_t {
             // largest best among open queries: grids whose smallest core index is not below it cannot help
             const uint64_t worst = ~wave_min_u64(((open >> lane) & 1ull) ? ~best : ~0ull);
             const uint32_t worst_idx = (uint32_t)(worst >> 32);
-            const uint64_t idx = e + lane;
-            uint32_t cs = 0, cn = 0;
-            int32_t lab = -1;
-            if (idx < e1) {
-                const uint32_t cc = nei[idx];
-                const uint32_t mc = co.cell_min_core[cc];
-                if (mc != kNone && (worst == ~0ull || mc < worst_idx)) {
-                    cs = co.core_begin[cc];
-                    cn = co.core_cnt[cc];
-                    lab = cell_label[cc];
-                    // a query without a hit scans every core point around it;
-                    // a grid of a step or more is dropped when no open query
-                    // comes within eps of its cell (low d only, where grids
-                    // are large: at d = 7 the test cost more than it saved)
-                    if constexpr (D <= 4) {
-                        if (worst == ~0ull && cn >= (uint32_t)kWave && !cell_near<D>(gv, cc, open, qx, side, lim))
-                            cn = 0;
-                    }
+            cc = 0;
+            if (idx >= e1) return 0u;
+            cc = nei[idx];
+            const uint32_t mc = co.cell_min_core[cc];
+            if (mc == kNone || !(worst == ~0ull || mc < worst_idx)) return 0u;
+            const uint32_t cn = co.core_cnt[cc];
+            if constexpr (kSplit) {
+                if ((cn >= kSplitRows) != large) {
+                    later |= !large;
+                    return 0u;
                 }
             }
-            const uint32_t incl = wave_incl_scan(cn);
-            const uint32_t tot = last_lane(incl);
-            if (tot == 0) continue;
-            s_start[lane] = cs;
-            s_excl[lane] = incl - cn;
-            s_lab[lane] = lab;
-            wave_sync();
-            for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
-                const uint32_t t = t0 + lane;
-                const bool tv = t < tot;
-                int j = 0;
+            // a query without a hit scans every core point around it;
+            // a grid of a step or more is dropped when no open query
+            // comes within eps of its cell (low d only, where grids
+            // are large: at d = 7 the test cost more than it saved)
+            if constexpr (D <= 4) {
+                if (worst == ~0ull && cn >= (uint32_t)kWave && !cell_near<D>(gv, cc, open, qx, side, lim)) return 0u;
+            }
+            return cn;
+        };
+        auto stream = [&](bool large) {
+            for (uint64_t e = e0; e < e1; e += kWave) {
+                uint32_t cc;
+                const uint32_t cn = candidate(e + lane, large, cc);
+                const uint32_t cs = cn ? co.core_begin[cc] : 0u;
+                const int32_t lab = cn ? cell_label[cc] : -1;
+                const uint32_t incl = wave_incl_scan(cn);
+                const uint32_t tot = last_lane(incl);
+                if (tot == 0) continue;
+                s_start[lane] = cs;
+                s_excl[lane] = incl - cn;
+                s_lab[lane] = lab;
+                wave_sync();
+                for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
+                    const uint32_t t = t0 + lane;
+                    const bool tv = t < tot;
+                    int j = 0;
 #pragma unroll
-                for (int step = 32; step > 0; step >>= 1)
-                    if (s_excl[j + step] <= t) j += step;
-                const uint32_t q = s_start[j] + (t - s_excl[j]);
-                int32_t y[D];
-                load_row<D>(co.ccrd, tv ? q : 0u, y);
-                const uint64_t cand = tv ? (((uint64_t)co.corig[q] << 32) | (uint32_t)s_lab[j]) : ~0ull;
-                uint64_t act = open;
-                while (act) {
-                    const int qi = ffs64(act);
-                    act &= act - 1ull;
-                    typename Dist<kWide>::T dd = 0;
+                    for (int step = 32; step > 0; step >>= 1)
+                        if (s_excl[j + step] <= t) j += step;
+                    const uint32_t q = s_start[j] + (t - s_excl[j]);
+                    int32_t y[D];
+                    load_row<D>(co.ccrd, tv ? q : 0u, y);
+                    const uint64_t cand = tv ? (((uint64_t)co.corig[q] << 32) | (uint32_t)s_lab[j]) : ~0ull;
+                    uint64_t act = open;
+                    while (act) {
+                        const int qi = ffs64(act);
+                        act &= act - 1ull;
+                        typename Dist<kWide>::T dd = 0;
 #pragma unroll
-                    for (int jj = 0; jj < D; ++jj) dd += sqd<kWide>(y[jj], readlane(qx[jj], qi));
-                    const bool in = tv && dd <= T;
-                    if (ballot(in)) {
-                        const uint64_t m = wave_min_u64(in ? cand : ~0ull);
-                        if (lane == qi && m < best) best = m;
+                        for (int jj = 0; jj < D; ++jj) dd += sqd<kWide>(y[jj], readlane(qx[jj], qi));
+                        const bool in = tv && dd <= T;
+                        if (ballot(in)) {
+                            const uint64_t m = wave_min_u64(in ? cand : ~0ull);
+                            if (lane == qi && m < best) best = m;
+                        }
                     }
                 }
+                wave_sync();
             }
-            wave_sync();
+        };
+        stream(false);
+        if constexpr (kSplit) {
+            if (ballot(later)) {
+                uint32_t total = 0, base, cc;
+                for (uint64_t e = e0; e < e1; e += kWave) total += wave_sum(split_slices(candidate(e + lane, true, cc)));
+                if (total != 0 && split_reserve(sq, total, base)) {
+                    tasks += total;
+                    for (uint64_t e = e0; e < e1; e += kWave) {
+                        const uint32_t want = split_slices(candidate(e + lane, true, cc));
+                        split_write(sq, base, want, (uint32_t)c, qb, cc);
+                    }
+                } else if (total != 0) {
+                    stream(true);
+                }
+            }
+            if (v) sq.best[s] = best;
         }
         if (v && !isc) {
             const uint32_t o = gv.sidx[s] - off;
             labels[o] = best == ~0ull ? -1 : (int32_t)((uint32_t)best - off);
             core_flags[o] = 0;
+        }
+    }
+    if constexpr (kSplit) {
+        if (tasks && lane == 0) sq.left[c] = tasks;  // the last of them settles the grid
+    }
+}
+
+// The tasks border_grid split off: a wave per task looks among its rows for the
+// lowest-index hit of each query of the batch that a core point of the
+// neighbour could still improve; rows are in ascending input index, so a
+// query's first hit is the one.  The wave that ends the last task of a grid
+// writes its labels.  2M 2-D points at eps 5000: 1,947 -> 29 + 44 us.
+template <int D, bool kWide>
+__global__ __launch_bounds__(kBlock) void border_tasks_kernel(GridView gv, CoreOut co,
+                                                              const int32_t* __restrict__ cell_label, SplitQueue sq) {
+    const int w = wave_id(), lane = lane_id();
+    const uint32_t count = min(*sq.count, sq.cap);
+    for (uint32_t i = blockIdx.x * kWavesPerBlock + w; i < count; i += gridDim.x * kWavesPerBlock) {
+        const uint4 task = sq.tasks[i];
+        const uint32_t c = uniform(task.x), qb = uniform(task.y), cc = uniform(task.z);
+        if (c == kNone) continue;
+        const Inst& I = cell_inst(gv, c);
+        const typename Dist<kWide>::T T = inst_T<kWide>(I);
+        const uint32_t st = gv.cell_start[c], k = gv.cell_start[c + 1] - st;
+        const uint32_t first = uniform(task.w) * kSplitRows;
+        const uint32_t row0 = co.core_begin[cc] + first;
+        const uint32_t rows = min(kSplitRows, co.core_cnt[cc] - first);
+        const uint32_t lowest = co.corig[row0];
+        const uint32_t lab = (uint32_t)cell_label[cc];
+        const bool query = qb + lane < k && !co.core[st + qb + (qb + lane < k ? lane : 0)];
+        const uint32_t s = st + qb + (query ? lane : 0);
+        const uint64_t had = query ? load_acq(&sq.best[s]) : 0ull;
+        uint64_t open = ballot(query && (uint32_t)(had >> 32) > lowest);
+        int32_t qx[D];
+        load_row<D>(gv.crd, s, qx);
+        uint32_t found = kNone;  // lane q: input index of query q's first hit
+        int32_t y[D];
+        uint32_t o = 0;
+        auto load = [&](uint32_t t0, int32_t (&r)[D], uint32_t& ro) {
+            const uint32_t q = row0 + min(t0 + (uint32_t)lane, rows - 1);
+            load_row<D>(co.ccrd, q, r);
+            ro = co.corig[q];
+        };
+        load(0, y, o);
+        for (uint32_t t0 = 0; t0 < rows && open; t0 += kWave) {
+            int32_t yn[D];
+            uint32_t on;
+            load(t0 + kWave, yn, on);
+            const bool tv = t0 + lane < rows;
+            for (uint64_t act = open; act; act &= act - 1ull) {
+                const int qi = ffs64(act);
+                typename Dist<kWide>::T dd = 0;
+#pragma unroll
+                for (int j = 0; j < D; ++j) dd += sqd<kWide>(y[j], readlane(qx[j], qi));
+                const uint64_t in = ballot(tv && dd <= T);
+                if (in) {
+                    const uint32_t at = readlane(o, ffs64(in));
+                    if (lane == qi) found = at;
+                    open &= ~(1ull << qi);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < D; ++j) y[j] = yn[j];
+            o = on;
+        }
+        if (found != kNone)
+            atomicMin((unsigned long long*)&sq.best[s], ((unsigned long long)found << 32) | lab);
+        if (!split_last(sq, c)) continue;
+        const uint32_t off = (uint32_t)I.off;
+        int32_t GD_GLOBAL* __restrict__ labels = as_global(I.labels);
+        for (uint32_t q0 = 0; q0 < k; q0 += kWave) {
+            if (q0 + lane >= k || co.core[st + q0 + lane]) continue;
+            const uint64_t best = load_acq(&sq.best[st + q0 + lane]);
+            labels[gv.sidx[st + q0 + lane] - off] = best == ~0ull ? -1 : (int32_t)((uint32_t)best - off);
         }
     }
 }
@@ -392,10 +497,10 @@ __global__ __launch_bounds__(kBlock) void output_group_kernel(GridView gv, CoreO
 // be the kernel's tail.
 constexpr int64_t kBorderGroupMinGrids = 1 << 20;
 
-template <int D, int G, bool kWide>
+template <int D, int G, bool kWide, bool kSplit>
 __global__ __launch_bounds__(kBlock) void output_kernel(GridView gv, CoreOut co, const uint64_t* __restrict__ nei_off,
                                                         const uint32_t* __restrict__ nei,
-                                                        const int32_t* __restrict__ cell_label) {
+                                                        const int32_t* __restrict__ cell_label, SplitQueue sq) {
     __shared__ uint32_t s_start[kWavesPerBlock][kWave];
     __shared__ uint32_t s_excl[kWavesPerBlock][kWave];
     __shared__ int32_t s_lab[kWavesPerBlock][kWave];
@@ -411,8 +516,8 @@ __global__ __launch_bounds__(kBlock) void output_kernel(GridView gv, CoreOut co,
     }
     for (uint64_t todo = ballot(need); todo; todo &= todo - 1ull) {
         const int g = ffs64(todo);
-        border_grid<D, kWide>(gv, co, nei_off, nei, cell_label, c0 + g, readlane(st_l, g), readlane(k_l, g),
-                              s_start[w], s_excl[w], s_lab[w]);
+        border_grid<D, kWide, kSplit>(gv, co, nei_off, nei, cell_label, c0 + g, readlane(st_l, g), readlane(k_l, g),
+                                      s_start[w], s_excl[w], s_lab[w], sq);
     }
 }
 
@@ -566,7 +671,7 @@ __global__ __launch_bounds__(kBlock) void border_runs_kernel(GridView gv, CoreOu
 
 hipError_t launch_output(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
                          const RunSource* runs, const int32_t* cell_label, bool wide, int lanes, uint32_t* family_min,
-                         hipStream_t st) {
+                         const SplitQueue* split, hipStream_t st) {
     if (g.ncell == 0) return hipSuccess;
     if (runs) {
         if (wide) return hipErrorInvalidValue;
@@ -596,15 +701,29 @@ hipError_t launch_output(const GridView& g, const CoreOut& c, const uint64_t* ne
         else
             GD_DISPATCH_D(g.D, (output_group_kernel<D, false, 16><<<grid_of(four), dim3(kBlock), 0, st>>>(
                                    g, c, nei_off, nei, cell_label)));
+    } else if (g.ncell >= kBorderGroupMinGrids && !wide) {
+        GD_DISPATCH_D(g.D, (output_kernel<D, kWave, false, false><<<grid_of(many), dim3(kBlock), 0, st>>>(
+                               g, c, nei_off, nei, cell_label, SplitQueue{})));
+    } else if (split && wide) {
+        GD_DISPATCH_D(g.D, ({
+                          output_kernel<D, 1, true, true><<<grid_of(one), dim3(kBlock), 0, st>>>(g, c, nei_off, nei,
+                                                                                               cell_label, *split);
+                          border_tasks_kernel<D, true><<<dim3(kSplitBlocks), dim3(kBlock), 0, st>>>(g, c, cell_label,
+                                                                                                   *split);
+                      }));
+    } else if (split) {
+        GD_DISPATCH_D(g.D, ({
+                          output_kernel<D, 1, false, true><<<grid_of(one), dim3(kBlock), 0, st>>>(g, c, nei_off, nei,
+                                                                                                cell_label, *split);
+                          border_tasks_kernel<D, false><<<dim3(kSplitBlocks), dim3(kBlock), 0, st>>>(g, c, cell_label,
+                                                                                                    *split);
+                      }));
     } else if (wide) {
-        GD_DISPATCH_D(g.D, (output_kernel<D, 1, true><<<grid_of(one), dim3(kBlock), 0, st>>>(g, c, nei_off, nei,
-                                                                                          cell_label)));
-    } else if (g.ncell >= kBorderGroupMinGrids) {
-        GD_DISPATCH_D(g.D, (output_kernel<D, kWave, false><<<grid_of(many), dim3(kBlock), 0, st>>>(g, c, nei_off, nei,
-                                                                                                cell_label)));
+        GD_DISPATCH_D(g.D, (output_kernel<D, 1, true, false><<<grid_of(one), dim3(kBlock), 0, st>>>(
+                               g, c, nei_off, nei, cell_label, SplitQueue{})));
     } else {
-        GD_DISPATCH_D(g.D, (output_kernel<D, 1, false><<<grid_of(one), dim3(kBlock), 0, st>>>(g, c, nei_off, nei,
-                                                                                           cell_label)));
+        GD_DISPATCH_D(g.D, (output_kernel<D, 1, false, false><<<grid_of(one), dim3(kBlock), 0, st>>>(
+                               g, c, nei_off, nei, cell_label, SplitQueue{})));
     }
     return hipGetLastError();
 }

@@ -78,10 +78,11 @@ __device__ __forceinline__ uint32_t sqdist_pk(const int32_t (&a)[packed_words<D>
 // MinPts (a query needs more hits than one 64-candidate step can give) a
 // step takes two rows; with a small MinPts most queries close within the
 // first 64 candidates and a second row would only add distance tests.
-template <int D, bool kStats, bool kPacked, int R, bool kWide, bool kPrune>
+template <int D, bool kStats, bool kPacked, int R, bool kWide, bool kSplit>
 __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const uint64_t* __restrict__ nei_off,
                                                            const uint32_t* __restrict__ nei, uint8_t* __restrict__ core,
-                                                           uint32_t* __restrict__ core_cnt, CoreStats* stats) {
+                                                           uint32_t* __restrict__ core_cnt, CoreStats* stats,
+                                                           SplitQueue sq) {
     constexpr int PW = packed_words<D>();
     constexpr int S = row_stride(D);
     __shared__ uint32_t s_start[kWavesPerBlock][kWave];
@@ -110,10 +111,10 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
         return;
     }
     const uint32_t need = minpts - k;
-    const double side = kPrune && D <= 4 ? (double)I.eps / sqrt((double)I.d) : 0.0;
+    const double side = kSplit && D <= 4 ? (double)I.eps / sqrt((double)I.d) : 0.0;
     const double lim = (double)I.eps * (double)I.eps * (1.0 + 1e-9) + 1.0;
     unsigned long long ndist = 0, npts = 0, ncells = 0;
-    uint32_t m = 0;
+    uint32_t m = 0, tasks = 0;
     for (uint32_t qb = 0; qb < k; qb += kWave) {
         const uint32_t nq = min((uint32_t)kWave, k - qb);
         uint64_t active = nq == (uint32_t)kWave ? ~0ull : ((1ull << nq) - 1ull);
@@ -129,101 +130,136 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
             }
         }
         uint32_t mycnt = 0;  // lane i: hits of query i
-        for (uint64_t e = e0; e < e1 && active; e += kWave) {
-            const uint64_t idx = e + lane;
-            const bool v = idx < e1;
-            const uint32_t cc = v ? nei[idx] : 0u;
-            const uint32_t cs = v ? gv.cell_start[cc] : 0u;
-            uint32_t cn = v ? gv.cell_start[cc + 1] - cs : 0u;
-            if constexpr (kPrune && D <= 4) {
-                // kPrune (low d, grids of a thousand points and more on
-                // average): a grid of 16 steps or more is dropped when no
-                // open query comes within eps of its cell, since the noise
-                // points of a sparse grid stream every neighbour
-                if (cn >= 16u * kWave && !cell_near<D>(gv, cc, active, qx, side, lim)) cn = 0;
-            }
-            const uint32_t incl = wave_incl_scan(cn);
-            const uint32_t tot = last_lane(incl);
-            s_start[w][lane] = cs;
-            s_excl[w][lane] = incl - cn;
-            wave_sync();
-            // row of flat candidate t (t < tot): binary search over the
-            // chunk's 64 grids
-            auto cand_row = [&](uint32_t t) -> uint32_t {
-                int j = 0;
+        // kSplit: neighbours of kSplitRows points and more wait for the second
+        // pass, which hands them out as tasks (or streams them if the queue
+        // is full)
+        bool later = false;
+        auto stream = [&](bool large) {
+            for (uint64_t e = e0; e < e1 && active; e += kWave) {
+                const uint64_t idx = e + lane;
+                const bool v = idx < e1;
+                const uint32_t cc = v ? nei[idx] : 0u;
+                const uint32_t cs = v ? gv.cell_start[cc] : 0u;
+                uint32_t cn = v ? gv.cell_start[cc + 1] - cs : 0u;
+                if constexpr (kSplit) {
+                    if ((cn >= kSplitRows) != large) {
+                        later |= cn >= kSplitRows;
+                        cn = 0;
+                    }
+                    // a grid of 16 steps or more is dropped when no open query
+                    // comes within eps of its cell, since the noise points of a
+                    // sparse grid stream every neighbour
+                    if constexpr (D <= 4) {
+                        if (cn >= 16u * kWave && !cell_near<D>(gv, cc, active, qx, side, lim)) cn = 0;
+                    }
+                }
+                const uint32_t incl = wave_incl_scan(cn);
+                const uint32_t tot = last_lane(incl);
+                s_start[w][lane] = cs;
+                s_excl[w][lane] = incl - cn;
+                wave_sync();
+                // row of flat candidate t (t < tot): binary search over the
+                // chunk's 64 grids
+                auto cand_row = [&](uint32_t t) -> uint32_t {
+                    int j = 0;
 #pragma unroll
-                for (int step = 32; step > 0; step >>= 1)
-                    if (s_excl[w][j + step] <= t) j += step;
-                return s_start[w][j] + (t - s_excl[w][j]);
-            };
-            // R candidates per lane per step (64 R per step), and the next
-            // step's candidates load while this one is evaluated
-            int32_t y[R][D];
-#pragma unroll
-            for (int u = 0; u < R; ++u) {
-                const uint32_t t = (uint32_t)(u * kWave + lane);
-                load_row<D>(gv.crd, t < tot ? cand_row(t) : st, y[u]);
-            }
-            for (uint32_t t0 = 0; t0 < tot && active; t0 += R * kWave) {
-                uint64_t tvm[R];
-#pragma unroll
-                for (int u = 0; u < R; ++u) tvm[u] = ballot(t0 + u * kWave + lane < tot);
-                int32_t yn[R][D];
+                    for (int step = 32; step > 0; step >>= 1)
+                        if (s_excl[w][j + step] <= t) j += step;
+                    return s_start[w][j] + (t - s_excl[w][j]);
+                };
+                // R candidates per lane per step (64 R per step), and the next
+                // step's candidates load while this one is evaluated
+                int32_t y[R][D];
 #pragma unroll
                 for (int u = 0; u < R; ++u) {
-                    const uint32_t tn = t0 + (R + u) * kWave + lane;
-                    load_row<D>(gv.crd, tn < tot ? cand_row(tn) : st, yn[u]);
+                    const uint32_t t = (uint32_t)(u * kWave + lane);
+                    load_row<D>(gv.crd, t < tot ? cand_row(t) : st, y[u]);
                 }
-                int32_t yp[R][PW];
-                if constexpr (kPacked) {
+                for (uint32_t t0 = 0; t0 < tot && active; t0 += R * kWave) {
+                    uint64_t tvm[R];
 #pragma unroll
-                    for (int u = 0; u < R; ++u) pack_row<D>(y[u], yp[u]);
-                }
-                // every open query against the step's candidates, two queries
-                // per round so their LDS reads overlap: the query row comes
-                // from LDS (one broadcast read), lane qi keeps query qi's
-                // hits; counts and closings are folded in once per step
-                const uint64_t act0 = uniform64(active);
-                uint32_t step_hits = 0;
-                for (uint64_t act = act0; act;) {
-                    const int qa = ffs64(act);
-                    act &= act - 1ull;
-                    const int qb2 = act ? ffs64(act) : qa;
-                    act &= act - 1ull;
-                    uint32_t ha = 0, hb = 0;
-                    if constexpr (kPacked) {
-                        int32_t pa[PW], pb[PW];
-                        load_row<PW>(s_q[w], qa, pa);
-                        load_row<PW>(s_q[w], qb2, pb);
+                    for (int u = 0; u < R; ++u) tvm[u] = ballot(t0 + u * kWave + lane < tot);
+                    int32_t yn[R][D];
 #pragma unroll
-                        for (int u = 0; u < R; ++u) {
-                            ha += (uint32_t)popc64(ballot(sqdist_pk<D>(yp[u], pa) <= T) & tvm[u]);
-                            hb += (uint32_t)popc64(ballot(sqdist_pk<D>(yp[u], pb) <= T) & tvm[u]);
-                        }
-                    } else {
-                        int32_t pa[D], pb[D];
-                        load_row<D>(s_q[w], qa, pa);
-                        load_row<D>(s_q[w], qb2, pb);
-#pragma unroll
-                        for (int u = 0; u < R; ++u) {
-                            ha += (uint32_t)popc64(ballot(sqdist_nb<D, kWide>(y[u], pa) <= T) & tvm[u]);
-                            hb += (uint32_t)popc64(ballot(sqdist_nb<D, kWide>(y[u], pb) <= T) & tvm[u]);
-                        }
+                    for (int u = 0; u < R; ++u) {
+                        const uint32_t tn = t0 + (R + u) * kWave + lane;
+                        load_row<D>(gv.crd, tn < tot ? cand_row(tn) : st, yn[u]);
                     }
-                    step_hits = lane == qa ? ha : step_hits;
-                    step_hits = lane == qb2 ? hb : step_hits;
-                    if constexpr (kStats) ndist += (qb2 != qa ? 2u : 1u) * min(tot - t0, (uint32_t)(R * kWave));
+                    int32_t yp[R][PW];
+                    if constexpr (kPacked) {
+#pragma unroll
+                        for (int u = 0; u < R; ++u) pack_row<D>(y[u], yp[u]);
+                    }
+                    // every open query against the step's candidates, two queries
+                    // per round so their LDS reads overlap: the query row comes
+                    // from LDS (one broadcast read), lane qi keeps query qi's
+                    // hits; counts and closings are folded in once per step
+                    const uint64_t act0 = uniform64(active);
+                    uint32_t step_hits = 0;
+                    for (uint64_t act = act0; act;) {
+                        const int qa = ffs64(act);
+                        act &= act - 1ull;
+                        const int qb2 = act ? ffs64(act) : qa;
+                        act &= act - 1ull;
+                        uint32_t ha = 0, hb = 0;
+                        if constexpr (kPacked) {
+                            int32_t pa[PW], pb[PW];
+                            load_row<PW>(s_q[w], qa, pa);
+                            load_row<PW>(s_q[w], qb2, pb);
+#pragma unroll
+                            for (int u = 0; u < R; ++u) {
+                                ha += (uint32_t)popc64(ballot(sqdist_pk<D>(yp[u], pa) <= T) & tvm[u]);
+                                hb += (uint32_t)popc64(ballot(sqdist_pk<D>(yp[u], pb) <= T) & tvm[u]);
+                            }
+                        } else {
+                            int32_t pa[D], pb[D];
+                            load_row<D>(s_q[w], qa, pa);
+                            load_row<D>(s_q[w], qb2, pb);
+#pragma unroll
+                            for (int u = 0; u < R; ++u) {
+                                ha += (uint32_t)popc64(ballot(sqdist_nb<D, kWide>(y[u], pa) <= T) & tvm[u]);
+                                hb += (uint32_t)popc64(ballot(sqdist_nb<D, kWide>(y[u], pb) <= T) & tvm[u]);
+                            }
+                        }
+                        step_hits = lane == qa ? ha : step_hits;
+                        step_hits = lane == qb2 ? hb : step_hits;
+                        if constexpr (kStats) ndist += (qb2 != qa ? 2u : 1u) * min(tot - t0, (uint32_t)(R * kWave));
+                    }
+                    mycnt += step_hits;
+                    active = act0 & ~ballot(((act0 >> lane) & 1ull) && mycnt >= need);
+                    if constexpr (kStats) npts += min(tot - t0, (uint32_t)(R * kWave));
+#pragma unroll
+                    for (int u = 0; u < R; ++u)
+#pragma unroll
+                        for (int j = 0; j < D; ++j) y[u][j] = yn[u][j];
                 }
-                mycnt += step_hits;
-                active = act0 & ~ballot(((act0 >> lane) & 1ull) && mycnt >= need);
-                if constexpr (kStats) npts += min(tot - t0, (uint32_t)(R * kWave));
-#pragma unroll
-                for (int u = 0; u < R; ++u)
-#pragma unroll
-                    for (int j = 0; j < D; ++j) y[u][j] = yn[u][j];
+                if constexpr (kStats) ncells += large ? 0ull : (unsigned long long)min(e1 - e, (uint64_t)kWave);
+                wave_sync();
             }
-            if constexpr (kStats) ncells += (unsigned long long)min(e1 - e, (uint64_t)kWave);
-            wave_sync();
+        };
+        stream(false);
+        if constexpr (kSplit) {
+            if (active && ballot(later)) {
+                auto slices = [&](uint64_t idx, uint32_t& cc) -> uint32_t {
+                    cc = idx < e1 ? nei[idx] : 0u;
+                    const uint32_t cn = idx < e1 ? gv.cell_start[cc + 1] - gv.cell_start[cc] : 0u;
+                    bool take = cn >= kSplitRows;
+                    if constexpr (D <= 4) take = take && cell_near<D>(gv, cc, active, qx, side, lim);
+                    return take ? split_slices(cn) : 0u;
+                };
+                uint32_t total = 0, base, cc;
+                for (uint64_t e = e0; e < e1; e += kWave) total += wave_sum(slices(e + lane, cc));
+                if (total != 0 && split_reserve(sq, total, base)) {
+                    tasks += total;
+                    for (uint64_t e = e0; e < e1; e += kWave) {
+                        const uint32_t want = slices(e + lane, cc);
+                        split_write(sq, base, want, (uint32_t)c, qb, cc);
+                    }
+                } else if (total != 0) {
+                    stream(true);
+                }
+            }
+            if ((uint32_t)lane < nq) sq.hits[st + qb + lane] = mycnt;
         }
         const bool is_core = (uint32_t)lane < nq && !((active >> lane) & 1ull);
         if ((uint32_t)lane < nq) core[st + qb + lane] = is_core ? 1 : 0;
@@ -231,6 +267,7 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
     }
     if (lane == 0) {
         core_cnt[c] = m;
+        if (kSplit && tasks) sq.left[c] = tasks;  // the last of them settles the grid
         if constexpr (kStats) {
             CoreStats& sl = stats[c & (kStatSlots - 1)];
             atomicAdd(&sl.dists, ndist);
@@ -240,6 +277,111 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
     }
 }
 
+// The tasks core_mark_kernel split off: a wave per task counts the hits of the
+// batch's queries that are still open among the task's rows; the wave that
+// ends the last task of a grid settles the grid's flags and count.  A stream
+// of 3e5 points was 2,300 dependent steps on one wave, while its 150 tasks take
+// 16 steps each side by side (2M 2-D points at eps 5000: 1,384 -> 59 + 60 us;
+// 3-D at eps 2000: 377 -> 58 + 12 us).
+template <int D, bool kStats, bool kPacked, bool kWide>
+__global__ __launch_bounds__(kBlock) void core_tasks_kernel(GridView gv, uint8_t* __restrict__ core,
+                                                            uint32_t* __restrict__ core_cnt, CoreStats* stats,
+                                                            SplitQueue sq) {
+    constexpr int PW = packed_words<D>();
+    constexpr int QW = kPacked ? PW : D;
+    constexpr int S = row_stride(D);
+    constexpr int R = 2;
+    __shared__ __align__(16) int32_t s_q[kWavesPerBlock][kWave * S];
+    const int w = wave_id(), lane = lane_id();
+    const uint32_t count = min(*sq.count, sq.cap);
+    for (uint32_t i = blockIdx.x * kWavesPerBlock + w; i < count; i += gridDim.x * kWavesPerBlock) {
+        const uint4 task = sq.tasks[i];
+        const uint32_t c = uniform(task.x), qb = uniform(task.y), cc = uniform(task.z);
+        if (c == kNone) continue;
+        const Inst& I = cell_inst(gv, c);
+        const uint32_t st = gv.cell_start[c], k = gv.cell_start[c + 1] - st;
+        const uint32_t need = (uint32_t)I.minpts - k;
+        const typename Dist<kWide>::T T = inst_T<kWide>(I);
+        const uint32_t nq = min((uint32_t)kWave, k - qb);
+        const uint32_t row0 = gv.cell_start[cc] + uniform(task.w) * kSplitRows;
+        const uint32_t rows = min(kSplitRows, gv.cell_start[cc + 1] - row0);
+        const bool valid = (uint32_t)lane < nq;
+        const uint32_t s = st + qb + (valid ? lane : 0);
+        const uint32_t had = valid ? load_acq(&sq.hits[s]) : need;
+        uint64_t active = ballot(had < need);
+        {
+            int32_t qx[D];
+            load_row<D>(gv.crd, s, qx);
+            wave_sync();  // the batch before is done with these rows
+            if constexpr (kPacked) {
+                int32_t pq[PW];
+                pack_row<D>(qx, pq);
+                store_row<PW>(s_q[w], lane, pq);
+            } else {
+                store_row<D>(s_q[w], lane, qx);
+            }
+            wave_sync();
+        }
+        uint32_t mine = 0;
+        unsigned long long ndist = 0, npts = 0;
+        int32_t y[R][D];
+#pragma unroll
+        for (int u = 0; u < R; ++u) load_row<D>(gv.crd, row0 + min((uint32_t)(u * kWave + lane), rows - 1), y[u]);
+        for (uint32_t t0 = 0; t0 < rows && active; t0 += R * kWave) {
+            int32_t yn[R][D], yp[R][QW];
+            uint64_t tvm[R];
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                tvm[u] = ballot(t0 + u * kWave + lane < rows);
+                load_row<D>(gv.crd, row0 + min(t0 + (uint32_t)((R + u) * kWave + lane), rows - 1), yn[u]);
+                if constexpr (kPacked) {
+                    pack_row<D>(y[u], yp[u]);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < D; ++j) yp[u][j] = y[u][j];
+                }
+            }
+            const uint64_t act0 = uniform64(active);
+            for (uint64_t act = act0; act; act &= act - 1ull) {
+                const int qi = ffs64(act);
+                int32_t p[QW];
+                load_row<QW>(s_q[w], qi, p);
+                uint32_t h = 0;
+#pragma unroll
+                for (int u = 0; u < R; ++u) {
+                    if constexpr (kPacked)
+                        h += (uint32_t)popc64(ballot(sqdist_pk<D>(yp[u], p) <= T) & tvm[u]);
+                    else
+                        h += (uint32_t)popc64(ballot(sqdist_nb<D, kWide>(yp[u], p) <= T) & tvm[u]);
+                }
+                mine += lane == qi ? h : 0u;
+                if constexpr (kStats) ndist += min(rows - t0, (uint32_t)(R * kWave));
+            }
+            if constexpr (kStats) npts += min(rows - t0, (uint32_t)(R * kWave));
+            active = act0 & ~ballot(((act0 >> lane) & 1ull) && had + mine >= need);
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+#pragma unroll
+                for (int j = 0; j < D; ++j) y[u][j] = yn[u][j];
+        }
+        if (mine) atomicAdd(&sq.hits[s], mine);
+        if constexpr (kStats) {
+            if (lane == 0) {
+                CoreStats& sl = stats[c & (kStatSlots - 1)];
+                atomicAdd(&sl.dists, ndist);
+                atomicAdd(&sl.points, npts);
+            }
+        }
+        if (!split_last(sq, c)) continue;
+        uint32_t m = 0;
+        for (uint32_t q0 = 0; q0 < k; q0 += kWave) {
+            const bool in = q0 + lane < k && load_acq(&sq.hits[st + (q0 + lane < k ? q0 + lane : 0)]) >= need;
+            if (q0 + lane < k) core[st + q0 + lane] = in ? 1 : 0;
+            m += (uint32_t)popc64(ballot(in));
+        }
+        if (lane == 0) core_cnt[c] = m;
+    }
+}
 // Marking with neighbours as runs (runs.hpp): as core_mark_kernel, but a lane
 // owns a run of neighbouring grids, which is one contiguous range of points;
 // the own points come with the run of the own family and count like the others.
@@ -390,14 +532,19 @@ __global__ __launch_bounds__(kBlock) void core_mark_runs_kernel(GridView gv, Run
 
 template <bool kStats, bool kPacked, int R, bool kWide>
 hipError_t launch_core_mark_as(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, uint8_t* core,
-                               uint32_t* core_cnt, CoreStats* stats, bool prune, hipStream_t st) {
+                               uint32_t* core_cnt, CoreStats* stats, const SplitQueue* split, hipStream_t st) {
     const unsigned blocks = grid_for(g.ncell, kWavesPerBlock);
-    if (prune)
-        GD_DISPATCH_D(g.D, (core_mark_kernel<D, kStats, kPacked, R, kWide, true>
-                            <<<grid_of(blocks), dim3(kBlock), 0, st>>>(g, nei_off, nei, core, core_cnt, stats)));
+    if (split)
+        GD_DISPATCH_D(g.D, ({
+                          core_mark_kernel<D, kStats, kPacked, R, kWide, true><<<grid_of(blocks), dim3(kBlock), 0, st>>>(
+                              g, nei_off, nei, core, core_cnt, stats, *split);
+                          core_tasks_kernel<D, kStats, kPacked, kWide>
+                              <<<dim3(kSplitBlocks), dim3(kBlock), 0, st>>>(g, core, core_cnt, stats, *split);
+                      }));
     else
         GD_DISPATCH_D(g.D, (core_mark_kernel<D, kStats, kPacked, R, kWide, false>
-                            <<<grid_of(blocks), dim3(kBlock), 0, st>>>(g, nei_off, nei, core, core_cnt, stats)));
+                            <<<grid_of(blocks), dim3(kBlock), 0, st>>>(g, nei_off, nei, core, core_cnt, stats,
+                                                                       SplitQueue{})));
     return hipGetLastError();
 }
 
@@ -417,29 +564,28 @@ hipError_t launch_core_mark_runs(const GridView& g, const RunSource& rs, uint8_t
 
 hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const RunSource* runs,
                             uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
-                            bool prune, hipStream_t st) {
+                            const SplitQueue* split, hipStream_t st) {
     if (g.ncell == 0) return hipSuccess;
     const bool packed = core_mark_packed(max_eps);
     const bool two = min_minpts > kWave / 2;
     if (runs) {
-        if (stats || prune || max_eps > GD_EPS_MAX) return hipErrorInvalidValue;
+        if (stats || split || max_eps > GD_EPS_MAX) return hipErrorInvalidValue;
         if (packed && two) return launch_core_mark_runs<true, 2>(g, *runs, core, core_cnt, st);
         if (packed) return launch_core_mark_runs<true, 1>(g, *runs, core, core_cnt, st);
         if (two) return launch_core_mark_runs<false, 2>(g, *runs, core, core_cnt, st);
         return launch_core_mark_runs<false, 1>(g, *runs, core, core_cnt, st);
     }
-    prune = prune && g.D <= 4;
     // the counting variant takes the same steps as the timed one
     if (max_eps > GD_EPS_MAX) {  // 64-bit distances, one row per step
-        if (stats) return launch_core_mark_as<true, false, 1, true>(g, nei_off, nei, core, core_cnt, stats, prune, st);
-        return launch_core_mark_as<false, false, 1, true>(g, nei_off, nei, core, core_cnt, stats, prune, st);
+        if (stats) return launch_core_mark_as<true, false, 1, true>(g, nei_off, nei, core, core_cnt, stats, split, st);
+        return launch_core_mark_as<false, false, 1, true>(g, nei_off, nei, core, core_cnt, stats, split, st);
     }
-    if (stats && two) return launch_core_mark_as<true, false, 2, false>(g, nei_off, nei, core, core_cnt, stats, prune, st);
-    if (stats) return launch_core_mark_as<true, false, 1, false>(g, nei_off, nei, core, core_cnt, stats, prune, st);
-    if (packed && two) return launch_core_mark_as<false, true, 2, false>(g, nei_off, nei, core, core_cnt, stats, prune, st);
-    if (packed) return launch_core_mark_as<false, true, 1, false>(g, nei_off, nei, core, core_cnt, stats, prune, st);
-    if (two) return launch_core_mark_as<false, false, 2, false>(g, nei_off, nei, core, core_cnt, stats, prune, st);
-    return launch_core_mark_as<false, false, 1, false>(g, nei_off, nei, core, core_cnt, stats, prune, st);
+    if (stats && two) return launch_core_mark_as<true, false, 2, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
+    if (stats) return launch_core_mark_as<true, false, 1, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
+    if (packed && two) return launch_core_mark_as<false, true, 2, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
+    if (packed) return launch_core_mark_as<false, true, 1, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
+    if (two) return launch_core_mark_as<false, false, 2, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
+    return launch_core_mark_as<false, false, 1, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
 }
 
 // Side rows of grid c: its core count if it also holds non-core points.

@@ -87,7 +87,7 @@ struct Header {
     uint32_t ncell;       // |Gs| over the batch
     uint32_t level_count[kMaxLevels];
     uint32_t counts[5];   // core points, core grids, max core points per grid, dense grids, tiny core grids
-    uint32_t pad;
+    uint32_t split[2];    // tasks of core marking and of the border search (SplitQueue)
     uint64_t nei_total;
 };
 
@@ -307,17 +307,35 @@ struct CoreStats {
     unsigned long long points;  // candidate points streamed (once per batch of 64 queries)
     unsigned long long grids;   // neighbour grids opened
 };
+// Streams of a few sparse grids through neighbours of thousands of points,
+// split into tasks of kSplitRows rows that a second kernel spreads over the
+// GPU: (grid, first query of the batch, neighbour grid, slice).
+constexpr uint32_t kSplitRows = 2048;
+// Mean points per grid from which core marking and the border search split:
+// the variant's registers cost where nothing is split (core marking at 161 and
+// 227 points per grid 99 -> 141 and 75 -> 104 us), and pay from about 300 (5-D at
+// 307 and 677 points per grid 201 -> 165 and 389 -> 165 us).
+constexpr int64_t kSplitMean = 256;
+constexpr unsigned kSplitBlocks = 2048;  // workgroups of the kernels that work off the tasks
+struct SplitQueue {
+    uint4* tasks;
+    uint32_t cap;
+    uint32_t* count;  // reserved so far (may pass cap: the reserver then streams by itself)
+    uint32_t* left;   // per grid with tasks: how many are not done yet
+    uint32_t* hits;   // core marking: hits of each point of a sparse grid so far
+    uint64_t* best;   // border search: best (input index, label) of each non-core point so far
+};
 // Core flags (sorted order) and m_i per grid.  max_eps: the largest eps in
 // the batch (small ones allow packed 16-bit coordinate differences);
 // min_minpts: the smallest MinPts in the batch (large ones take two
-// candidate rows per lane per step).  prune (used at d <= 4): test large
-// neighbour grids' cells against the open queries before streaming them,
-// for data whose grids hold a thousand points and more.
+// candidate rows per lane per step).  split (or nullptr): for data of
+// kSplitMean points per grid and more; large neighbours then also have their
+// cells tested against the open queries first (d <= 4).
 // runs (or nullptr): neighbours as runs instead of lists (then without stats,
-// prune and eps above GD_EPS_MAX).
+// split and eps above GD_EPS_MAX).
 hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const RunSource* runs,
                             uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
-                            bool prune, hipStream_t st);
+                            const SplitQueue* split, hipStream_t st);
 // Whether core marking compares coordinates as packed 16-bit differences
 // for a batch whose largest eps is max_eps (exact for eps <= 10000: points
 // of neighbouring grids differ by less than 2.13 eps per coordinate).
@@ -434,10 +452,11 @@ hipError_t launch_border_walk(const GridView& g, const CoreOut& c, const TreeVie
 // lanes: 16 serves four grids per wave side by side; otherwise a wave per
 // grid (a wave checks 64 grids when there are millions of them).
 // runs (or nullptr): neighbours as runs instead of lists (eps <= GD_EPS_MAX;
-// family_min: scratch of one word per level-(D-1) node).
+// family_min: scratch of one word per level-(D-1) node).  split (or nullptr): as
+// for launch_core_mark (with a wave per grid).
 hipError_t launch_output(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
                          const RunSource* runs, const int32_t* cell_label, bool wide, int lanes, uint32_t* family_min,
-                         hipStream_t st);
+                         const SplitQueue* split, hipStream_t st);
 // All-core grids: output in input order through an identifier -> label hash
 // table of 2^bits slots (+1) in `table` (output_table_bytes).  keys_in: the
 // identifiers in input order, shifted up by key_lo bits (the packed-row
