@@ -121,6 +121,7 @@ struct gd_ctx {
     bool last_wide = false;        // the last eager call took 64-bit distances
     bool last_runs = false;        // the last eager call found neighbours as runs (no lists per grid)
     bool last_by_level = false;    // ... built its lists level by level
+    bool last_ordered = false;     // ... by offset
     int64_t last_nodes[kMaxLevels] = {};  // its tree nodes per level, lanes per node and
     int last_lanes[kMaxLevels] = {};      // largest node-list total per buffer
     uint64_t last_ents[2] = {};
@@ -303,6 +304,7 @@ struct Plan {
     bool walk;         // consumers walk the grid tree (lists only for big core sets)
     bool runs;         // neighbours as runs: node lists instead of neighbour lists
     bool by_level;     // neighbour lists built level by level
+    bool ordered;      // by offset
     uint64_t ents[2];            // entries per node-list buffer
     int64_t nodes[kMaxLevels];   // tree nodes per level
     int lanes[kMaxLevels];       // lanes per node in the build
@@ -747,13 +749,19 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     // the counters of the work done on them.  A bounded workspace and 64-bit
     // distances keep the lists.  In two and three dimensions the lists are
     // short, and the same levels end in them (nodes.hip); in two dimensions
-    // that takes no further memory.
+    // that takes no further memory.  So do the lists of more dimensions, in
+    // either order: the walks of neighbors.hip are left to bounded workspaces
+    // and to ordered lists in up to three dimensions, where the eight-lane walk
+    // is as fast and needs no read-back (10M 3-D points: 58 us).
     bool runs = plan ? plan->runs
                      : D >= kMinRunD && sparse && ctx->nei_query == kNeiAuto && ctx->nei_mode == 0 && !ctx->bfs &&
                            !stats && !ctx->proposal_on && !bounded && !wide && !split && ncell < kMaxRunNodes;
+    const bool ordered = plan ? plan->ordered
+                              : ncell <= kOrderedMaxGrids &&
+                                    (ctx->nei_query == kNeiTree || (ctx->nei_query == kNeiAuto && !sparse));
     bool by_level = plan ? plan->by_level
-                         : (D == 2 || (D == 3 && !bounded)) && !(!ctx->bfs && ctx->nei_mode == 2) &&
-                               (ctx->nei_query == kNeiTreeWalkOrder || (ctx->nei_query == kNeiAuto && sparse)) &&
+                         : !runs && D >= (ordered ? kMinRunD : 2) && (D == 2 || !bounded) &&
+                               !(!ctx->bfs && ctx->nei_mode == 2) && ctx->nei_query != kNeiHash &&
                                ncell < kMaxRunNodes;
 
     // ---- Algorithm 2 (grid tree) and Algorithm 3 (Nei for every grid)
@@ -858,6 +866,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         nl.off[1 - fin] = (uint64_t*)L.nei_up;
         nl.cnt = L.side_off;
         nl.up = grid_up;
+        nl.ordered = ordered;
         int rc2;
         int64_t nodes[kMaxLevels];
         for (int l = 0; l < kMaxLevels; ++l) nodes[l] = plan ? plan->nodes[l] : ncell;
@@ -883,7 +892,11 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         }
         for (int l = 2; l <= last; ++l) {
             // (a grid of three dimensions has at most 25 parents' entries)
-            const int lanes = plan ? plan->lanes[l] : visits <= 12 ? 8 : visits <= 24 || l == D ? 16 : kWave;
+            const int lanes = plan                     ? plan->lanes[l]
+                              : l == D && D >= kMinRunD ? kWave
+                              : visits <= 12            ? 8
+                              : visits <= 24 || l == D  ? 16
+                                                        : kWave;
             if (plan) GD_TRY(launch_plan_check(Hd, 3, l, plan->nodes[l], st));
             GD_TRY(launch_level_count(g, t, nl, l, nodes[l], lanes, L.partial, st));
             if (plan) {
@@ -913,7 +926,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         if (last == D) {
             nei = nl.ent[fin];
             if (plan) nei_total = plan->ents[fin];
-            lists_up = true;
+            lists_up = !ordered;
         } else {
             rsrc.t = t;
             rsrc.excl = nl.excl;
@@ -941,6 +954,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     const RunSource* rs = runs ? &rsrc : nullptr;
     ctx->last.neighbor_walk = walk ? 1 : 0;
     if (!plan) {
+        ctx->last_ordered = ordered;
         ctx->last_runs = runs;
         ctx->last_by_level = by_level;
     }
@@ -962,7 +976,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         sq.count = &Hd->split[0];
         sq.left = (uint32_t*)L.cell_label;
         sq.hits = L.list;
-        GD_TRY(launch_core_mark(g, L.nei_off, nei, rs, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
+        GD_TRY(launch_core_mark(g, L.nei_off, nei, by_level && ordered ? grid_up : nullptr, rs, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
                                 max_eps, min_minpts, split ? &sq : nullptr, st));
     }
     ctx->mark(P_CORE_MARK, 1);
@@ -1314,6 +1328,7 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
     p.walk = ctx->last_walk;
     p.runs = ctx->last_runs;
     p.by_level = ctx->last_by_level;
+    p.ordered = ctx->last_ordered;
     const bool levels = p.runs || p.by_level;
     if (levels) {
         for (int k = 0; k < 2; ++k) p.ents[k] = ctx->last_ents[k] + ctx->last_ents[k] / 16 + 4096;

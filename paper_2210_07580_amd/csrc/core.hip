@@ -80,7 +80,8 @@ __device__ __forceinline__ uint32_t sqdist_pk(const int32_t (&a)[packed_words<D>
 // first 64 candidates and a second row would only add distance tests.
 template <int D, bool kStats, bool kPacked, int R, bool kWide, bool kSplit>
 __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const uint64_t* __restrict__ nei_off,
-                                                           const uint32_t* __restrict__ nei, uint8_t* __restrict__ core,
+                                                           const uint32_t* __restrict__ nei,
+                                                           const uint2* __restrict__ mid, uint8_t* __restrict__ core,
                                                            uint32_t* __restrict__ core_cnt, CoreStats* stats,
                                                            SplitQueue sq) {
     constexpr int PW = packed_words<D>();
@@ -111,6 +112,17 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
         return;
     }
     const uint32_t need = minpts - k;
+    // The neighbours at offset 0 lead the list in ascending order; the 64
+    // around the grid's own place among them are the nearest in the first
+    // dimensions, so the stream starts there and takes the rest of the
+    // offset after (7-D lists of hundreds of entries: 160 -> 67 us; the merge
+    // wants the ascending order, 1.3 against 2.9 ms with the nearest first).
+    uint32_t first = 0, zeros = 0;
+    if (mid) {
+        const uint2 m = mid[c];
+        zeros = m.y;
+        first = m.x > kWave / 2 ? m.x - kWave / 2 : 0u;
+    }
     const double side = kSplit && D <= 4 ? (double)I.eps / sqrt((double)I.d) : 0.0;
     const double lim = (double)I.eps * (double)I.eps * (1.0 + 1e-9) + 1.0;
     unsigned long long ndist = 0, npts = 0, ncells = 0;
@@ -138,7 +150,9 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
             for (uint64_t e = e0; e < e1 && active; e += kWave) {
                 const uint64_t idx = e + lane;
                 const bool v = idx < e1;
-                const uint32_t cc = v ? nei[idx] : 0u;
+                uint64_t at = idx;
+                if (idx - e0 < zeros) at = idx - e0 + first < zeros ? idx + first : idx + first - zeros;
+                const uint32_t cc = v ? nei[at] : 0u;
                 const uint32_t cs = v ? gv.cell_start[cc] : 0u;
                 uint32_t cn = v ? gv.cell_start[cc + 1] - cs : 0u;
                 if constexpr (kSplit) {
@@ -531,19 +545,20 @@ __global__ __launch_bounds__(kBlock) void core_mark_runs_kernel(GridView gv, Run
 }
 
 template <bool kStats, bool kPacked, int R, bool kWide>
-hipError_t launch_core_mark_as(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, uint8_t* core,
+hipError_t launch_core_mark_as(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const uint2* mid,
+                               uint8_t* core,
                                uint32_t* core_cnt, CoreStats* stats, const SplitQueue* split, hipStream_t st) {
     const unsigned blocks = grid_for(g.ncell, kWavesPerBlock);
     if (split)
         GD_DISPATCH_D(g.D, ({
                           core_mark_kernel<D, kStats, kPacked, R, kWide, true><<<grid_of(blocks), dim3(kBlock), 0, st>>>(
-                              g, nei_off, nei, core, core_cnt, stats, *split);
+                              g, nei_off, nei, mid, core, core_cnt, stats, *split);
                           core_tasks_kernel<D, kStats, kPacked, kWide>
                               <<<dim3(kSplitBlocks), dim3(kBlock), 0, st>>>(g, core, core_cnt, stats, *split);
                       }));
     else
         GD_DISPATCH_D(g.D, (core_mark_kernel<D, kStats, kPacked, R, kWide, false>
-                            <<<grid_of(blocks), dim3(kBlock), 0, st>>>(g, nei_off, nei, core, core_cnt, stats,
+                            <<<grid_of(blocks), dim3(kBlock), 0, st>>>(g, nei_off, nei, mid, core, core_cnt, stats,
                                                                        SplitQueue{})));
     return hipGetLastError();
 }
@@ -562,7 +577,8 @@ hipError_t launch_core_mark_runs(const GridView& g, const RunSource& rs, uint8_t
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const RunSource* runs,
+hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const uint2* mid,
+                            const RunSource* runs,
                             uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
                             const SplitQueue* split, hipStream_t st) {
     if (g.ncell == 0) return hipSuccess;
@@ -577,15 +593,15 @@ hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const ui
     }
     // the counting variant takes the same steps as the timed one
     if (max_eps > GD_EPS_MAX) {  // 64-bit distances, one row per step
-        if (stats) return launch_core_mark_as<true, false, 1, true>(g, nei_off, nei, core, core_cnt, stats, split, st);
-        return launch_core_mark_as<false, false, 1, true>(g, nei_off, nei, core, core_cnt, stats, split, st);
+        if (stats) return launch_core_mark_as<true, false, 1, true>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+        return launch_core_mark_as<false, false, 1, true>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
     }
-    if (stats && two) return launch_core_mark_as<true, false, 2, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
-    if (stats) return launch_core_mark_as<true, false, 1, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
-    if (packed && two) return launch_core_mark_as<false, true, 2, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
-    if (packed) return launch_core_mark_as<false, true, 1, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
-    if (two) return launch_core_mark_as<false, false, 2, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
-    return launch_core_mark_as<false, false, 1, false>(g, nei_off, nei, core, core_cnt, stats, split, st);
+    if (stats && two) return launch_core_mark_as<true, false, 2, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+    if (stats) return launch_core_mark_as<true, false, 1, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+    if (packed && two) return launch_core_mark_as<false, true, 2, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+    if (packed) return launch_core_mark_as<false, true, 1, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+    if (two) return launch_core_mark_as<false, false, 2, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+    return launch_core_mark_as<false, false, 1, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
 }
 
 // Side rows of grid c: its core count if it also holds non-core points.

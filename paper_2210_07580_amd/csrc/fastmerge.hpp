@@ -131,7 +131,9 @@ __device__ __forceinline__ void load_point(const PointSet& s, uint32_t pos, int3
     load_row<D>(s.rows, (int64_t)s.base + pos, x);
 }
 
-constexpr uint32_t kUnroll = 4;  // words of a set whose loads are issued together
+// words of a set whose loads are issued together (wider rows take more registers)
+template <int D>
+constexpr uint32_t kUnrollOf = D <= 4 ? 4 : 2;
 
 // Loads the point of this lane in word w (position clamped into the set so
 // the address is always valid; callers ignore lanes whose bit is clear).
@@ -186,17 +188,17 @@ __device__ __forceinline__ typename Dist<kWide>::T nearest(const PointSet& s, co
     int32_t br[D];
 #pragma unroll
     for (int k = 0; k < D; ++k) br[k] = 0;
-    for (uint32_t w0 = 0; w0 < s.words; w0 += kUnroll) {
-        uint64_t mk[kUnroll];
-        int32_t y[kUnroll][D];
+    for (uint32_t w0 = 0; w0 < s.words; w0 += kUnrollOf<D>) {
+        uint64_t mk[kUnrollOf<D>];
+        int32_t y[kUnrollOf<D>][D];
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
+        for (uint32_t u = 0; u < kUnrollOf<D>; ++u) {
             const uint32_t w = w0 + u;
             mk[u] = w < s.words ? s.alive[w] : 0ull;
             if (mk[u]) load_lane_point<D>(s, w, y[u]);
         }
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
+        for (uint32_t u = 0; u < kUnrollOf<D>; ++u) {
             ndist += (unsigned long long)popc64(mk[u]);
             if ((mk[u] >> lane) & 1ull) {
                 uint32_t dd = 0;
@@ -251,17 +253,17 @@ __device__ __forceinline__ bool pruning(const PointSet& a, const PointSet& b, co
     // lambda over the live points of b
     float cmin = 2.f;
     bool off = false;
-    for (uint32_t w0 = 0; w0 < b.words; w0 += kUnroll) {
-        uint64_t mk[kUnroll];
-        int32_t yy[kUnroll][D];
+    for (uint32_t w0 = 0; w0 < b.words; w0 += kUnrollOf<D>) {
+        uint64_t mk[kUnrollOf<D>];
+        int32_t yy[kUnrollOf<D>][D];
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
+        for (uint32_t u = 0; u < kUnrollOf<D>; ++u) {
             const uint32_t w = w0 + u;
             mk[u] = w < b.words ? b.alive[w] : 0ull;
             if (mk[u]) load_lane_point<D>(b, w, yy[u]);
         }
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
+        for (uint32_t u = 0; u < kUnrollOf<D>; ++u) {
             ndist += (unsigned long long)popc64(mk[u]);
             if (!((mk[u] >> lane) & 1ull)) continue;
             int32_t py[D];
@@ -297,17 +299,17 @@ __device__ __forceinline__ bool pruning(const PointSet& a, const PointSet& b, co
     cmin = wave_min_f32(cmin);
     const float thr = cmin - kAngleMargin;
     uint64_t any = 0;
-    for (uint32_t w0 = 0; w0 < a.words; w0 += kUnroll) {
-        uint64_t mk[kUnroll];
-        int32_t xx[kUnroll][D];
+    for (uint32_t w0 = 0; w0 < a.words; w0 += kUnrollOf<D>) {
+        uint64_t mk[kUnrollOf<D>];
+        int32_t xx[kUnrollOf<D>][D];
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
+        for (uint32_t u = 0; u < kUnrollOf<D>; ++u) {
             const uint32_t w = w0 + u;
             mk[u] = w < a.words ? a.alive[w] : 0ull;
             if (mk[u]) load_lane_point<D>(a, w, xx[u]);
         }
 #pragma unroll
-        for (uint32_t u = 0; u < kUnroll; ++u) {
+        for (uint32_t u = 0; u < kUnrollOf<D>; ++u) {
             if (!mk[u]) continue;
             ndist += (unsigned long long)popc64(mk[u]);
             bool keep = false;

@@ -217,13 +217,16 @@ struct NodeLists {
     uint32_t* cnt;              // scratch: one word per node
     uint32_t* near;             // entries of each node's list that touch it, listed first (or nullptr)
     uint2* up;                  // level D: see launch_nei_fill's nei_up
+    bool ordered;               // level D: lists by offset, ascending within one, instead of in walk order;
+                                // up is then (place of the grid itself among the neighbours at offset
+                                // 0, their number)
 };
 // Places around a level-1 node that hold all its level-1 neighbours (windows of +-3 keys).
 constexpr int kNear = 7;
 // Entries hold a node above 6 bits.
 constexpr int64_t kMaxRunNodes = (int64_t)1 << 26;
 // Level l (2 .. D): list lengths and offsets, total into the header
-// (nei_total); then the lists, for l = D those of the grids, in walk order.  nodes: nodes of level l (or an upper bound);
+// (nei_total); then the lists, for l = D those of the grids.  nodes: nodes of level l (or an upper bound);
 // lanes: 8, 16 or 64 per node (by the length of the parents' lists).
 hipError_t launch_level_count(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
                               int lanes, uint64_t* partial, hipStream_t st);
@@ -244,6 +247,7 @@ struct RunSource {
 // The query that produces the lists: the grid tree with offset-ordered lists
 // (walk order above 2^20 grids), the grid tree in walk order always, or
 // direct hashing of every candidate identifier (offset-ordered).
+constexpr int64_t kOrderedMaxGrids = 1 << 20;  // more grids: lists in walk order
 enum NeiQueryKind { kNeiTree = 0, kNeiTreeWalkOrder = 1, kNeiHash = 2 };
 // Option value of GD_OPT_NEIGHBOR_QUERY 0: the tree in offset order or walk
 // order by the grids' mean size (resolved on the host per call).
@@ -333,7 +337,9 @@ struct SplitQueue {
 // cells tested against the open queries first (d <= 4).
 // runs (or nullptr): neighbours as runs instead of lists (then without stats,
 // split and eps above GD_EPS_MAX).
-hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const RunSource* runs,
+// mid (or nullptr): NodeLists::up of ordered lists.
+hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const uint2* mid,
+                            const RunSource* runs,
                             uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
                             const SplitQueue* split, hipStream_t st);
 // Whether core marking compares coordinates as packed 16-bit differences

@@ -36,9 +36,7 @@ namespace gd {
 // lane and costs more than it saves.)  Lanes follow the query order, so the
 // lists come out as one query would emit them.
 constexpr int kSplit = 8;
-constexpr int64_t kSplitMaxGrids = 1 << 20;
-
-inline int nei_lanes(int64_t ncell) { return ncell <= kSplitMaxGrids ? kSplit : 1; }
+inline int nei_lanes(int64_t ncell) { return ncell <= kOrderedMaxGrids ? kSplit : 1; }
 
 // Algorithm 3 on the grid tree.
 struct TreeQuery {

@@ -18,7 +18,9 @@
 // lane and round rather than each lane its own run (6.3 -> 5.7 ms).  The lists
 // of the grids themselves in two and three dimensions: 43 -> 35 us for 20k
 // points in two, 131 -> 79 us in three (the read-back between the passes
-// included), even at millions of grids.
+// included), even at millions of grids; lists by offset of 2M points in seven
+// dimensions (5,892 and 10,380 grids) 1,430 -> 250 and 1,456 -> 265 us, in five
+// (6,310) 304 -> 145.
 #include <algorithm>
 
 #include "launch.hpp"
@@ -49,17 +51,24 @@ struct LevelArgs {
     const uint64_t* off;        // pass 2: where each list goes
     uint32_t* ent;
     uint64_t cap;
-    uint2* up;                  // the last level: range of the larger grids in each list
+    uint2* up;                  // the last level: range of the larger grids in each list, or (kOrdered)
+                                // the own grid's place among those at offset 0, and their number
+    const int32_t* ck0;         // instance of each grid (count > 1)
+    int count;                  // instances
+    int first;                  // l == 2: the places around a parent from -first on, then the others
     Header* hdr;
 };
 
 // kFirst: l == 2, whose parents' neighbours are the kNear places around them.
 // kGrids: l == D, entries are grid indices and the own grid is left out.
-template <int S, bool kFirst, bool kGrids, bool kFill>
+// kOrdered (kGrids): lists by offset; the entries are gone through twice, for
+// the length of each offset's part and to place them.
+template <int S, bool kFirst, bool kGrids, bool kFill, bool kOrdered = false>
 __global__ __launch_bounds__(kBlock) void level_kernel(LevelArgs A) {
     constexpr int G = kWave / S;
     // pass 2 of long lists: the chunk's runs, written out one entry per lane
-    constexpr bool kFlat = kFill && !kGrids && S == kWave;
+    constexpr bool kFlat = kFill && S == kWave;
+    static_assert(!kOrdered || (kFlat && kGrids), "ordered lists are written entry by entry");
     __shared__ uint32_t s_at[kFlat ? kWavesPerBlock : 1][kWave];    // first child of a lane's run, minus its place
     __shared__ uint32_t s_how[kFlat ? kWavesPerBlock : 1][kWave];   // the entry's low bits
     __shared__ uint32_t s_head[kFlat ? kWavesPerBlock : 1][kWave];  // lane + 1 of the run that starts here
@@ -103,96 +112,139 @@ __global__ __launch_bounds__(kBlock) void level_kernel(LevelArgs A) {
     uint32_t total = 0, nears = 0;
     uint32_t own = 0, above = 0;  // kGrids: entries before the own grid, entries above it (this lane's)
     const uint64_t pos0 = pos;
-    for (uint64_t e = e0; e < e1; e += S) {
-        bool in = e + sub < e1;
-        uint32_t b = 0;
-        int budget = 1, touch = 0;
-        if constexpr (kFirst) {
-            const int64_t x = (int64_t)p + near_step(sub);
-            in = in && x >= (int64_t)lo1 && x < (int64_t)hi1;
-            b = in ? (uint32_t)x : p;
-            const int dl = A.pkey[b] - k1;
-            const int ad = dl < 0 ? -dl : dl;
-            in = in && ad <= walk_window(dk);
-            const int gap = ad > 0 ? ad - 1 : 0;
-            budget = dk - gap * gap;
-            touch = touch_step(0, ad);
-        } else if (in) {
-            const uint32_t v = A.pent[e + sub];
-            b = entry_node(v);
-            budget = entry_budget(v);
-            touch = entry_touch(v);
-        }
-        uint32_t c0 = 0, c1 = 0, lo, hi, mn;
-        if (in) node_children(A.child, b, c0, c1);
-        child_window<!kGrids && !kFlat>(A.key, c0, c1, k, walk_window(budget), lo, hi, mn);
-        uint32_t m = hi - lo;
-        if (!split || touch == kApart) mn = 0;
-        if constexpr (!kFill) {
-            total += m;
-            nears += mn;
-        } else if constexpr (kFlat) {
-            const int w = wave_id();
-            const uint32_t incl = wave_incl_scan(m), excl = incl - m, tot = last_lane(incl);
-            s_at[w][lane] = lo - excl;
-            s_how[w][lane] = node_entry(0u, touch, budget);
-            uint32_t carry = 0;
-            for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
-                // the run of each place: see core_mark_runs_kernel
-                s_head[w][lane] = 0;
-                wave_sync();
-                if (m != 0 && excl >= t0 && excl < t0 + kWave) s_head[w][excl - t0] = (uint32_t)lane + 1u;
-                wave_sync();
-                uint32_t j = wave_max_scan(s_head[w][lane]);
-                j = j ? j : carry;
-                carry = last_lane(j);
-                j = (j ? j : 1u) - 1u;
-                const bool v = t0 + lane < tot;
-                const uint32_t x = v ? s_at[w][j] + t0 + lane : (uint32_t)a;
-                const uint32_t how = s_how[w][j];
-                const int dl = A.key[x] - k;
-                const int ad = dl < 0 ? -dl : dl;
-                const int gap = ad > 0 ? ad - 1 : 0;
-                const int t = touch_step(entry_touch(how), ad);
-                const uint32_t y = node_entry(x, t, entry_budget(how) - gap * gap);
-                const uint64_t nm = ballot(v && split && t != kApart), fm = ballot(v) & ~nm, lt = lanemask_lt();
-                const bool nr = (nm >> lane) & 1ull;
-                uint64_t& fpos = split ? far : pos;
-                const uint64_t to = nr ? pos + popc64(nm & lt) : fpos + popc64(fm & lt);
-                if (v) A.ent[to] = y;
-                fpos += popc64(fm);
-                if (split) pos += popc64(nm);
+    uint32_t part[kMaxD] = {};  // kOrdered: length, then next place, of each offset's part
+    uint32_t zeros = 0;         // and the length of the first
+    if constexpr (kOrdered) dk = A.inst[A.count == 1 ? 0 : A.ck0[a]].d;
+    for (int pass = kOrdered ? 0 : 1; pass < 2; ++pass) {
+        for (uint64_t e = e0; e < e1; e += S) {
+            if (kOrdered && pass == 1 && e == e0) {
+                uint32_t run = 0;
+                zeros = part[0];
+#pragma unroll
+                for (int o = 0; o < kMaxD; ++o) {
+                    const uint32_t m = part[o];
+                    part[o] = run;
+                    run += m;
+                }
             }
-            wave_sync();
-        } else {
-            // the own grid is written nowhere
-            if (kGrids && in && b == p) --m;
-            const uint32_t f = m - mn;
-            const uint32_t fi = group_sum_scan<S>(f), ni = split ? group_sum_scan<S>(mn) : 0u;
-            uint64_t wf = (split ? far : pos) + (fi - f), wn = pos + (ni - mn);
-            for (uint32_t x = lo; x < hi; ++x) {
-                if constexpr (kGrids) {
-                    if (x == (uint32_t)a) {
-                        own = (uint32_t)(wf - pos0);
-                    } else {
-                        A.ent[wf++] = x;
-                        above += x > (uint32_t)a ? 1u : 0u;
+            bool in = e + sub < e1;
+            uint32_t b = 0;
+            int budget = 1, touch = 0;
+            if constexpr (kFirst) {
+                const int64_t x = (int64_t)p + near_step(sub, A.first);
+                in = in && x >= (int64_t)lo1 && x < (int64_t)hi1;
+                b = in ? (uint32_t)x : p;
+                const int dl = A.pkey[b] - k1;
+                const int ad = dl < 0 ? -dl : dl;
+                in = in && ad <= walk_window(dk);
+                const int gap = ad > 0 ? ad - 1 : 0;
+                budget = dk - gap * gap;
+                touch = touch_step(0, ad);
+            } else if (in) {
+                const uint32_t v = A.pent[e + sub];
+                b = entry_node(v);
+                budget = entry_budget(v);
+                touch = entry_touch(v);
+            }
+            uint32_t c0 = 0, c1 = 0, lo, hi, mn;
+            if (in) node_children(A.child, b, c0, c1);
+            child_window<!kGrids && !kFlat>(A.key, c0, c1, k, walk_window(budget), lo, hi, mn);
+            uint32_t m = hi - lo;
+            if (!split || touch == kApart) mn = 0;
+            if constexpr (!kFill) {
+                total += m;
+                nears += mn;
+            } else if constexpr (kFlat) {
+                const int w = wave_id();
+                const uint32_t incl = wave_incl_scan(m), excl = incl - m, tot = last_lane(incl);
+                s_at[w][lane] = lo - excl;
+                s_how[w][lane] = node_entry(0u, touch, budget);
+                uint32_t carry = 0;
+                for (uint32_t t0 = 0; t0 < tot; t0 += kWave) {
+                    // the run of each place: see core_mark_runs_kernel
+                    s_head[w][lane] = 0;
+                    wave_sync();
+                    if (m != 0 && excl >= t0 && excl < t0 + kWave) s_head[w][excl - t0] = (uint32_t)lane + 1u;
+                    wave_sync();
+                    uint32_t j = wave_max_scan(s_head[w][lane]);
+                    j = j ? j : carry;
+                    carry = last_lane(j);
+                    j = (j ? j : 1u) - 1u;
+                    bool v = t0 + lane < tot;
+                    const uint32_t x = v ? s_at[w][j] + t0 + lane : (uint32_t)a;
+                    const uint64_t lt = lanemask_lt();
+                    if constexpr (kGrids && !kOrdered) {
+                        const uint64_t sm = ballot(v && x == (uint32_t)a);
+                        v = v && x != (uint32_t)a;
+                        const uint64_t vm = ballot(v);
+                        if (v) A.ent[pos + popc64(vm & lt)] = x;
+                        above += v && x > (uint32_t)a ? 1u : 0u;
+                        if (sm && lane == 0) own = (uint32_t)(pos - pos0) + (uint32_t)popc64(vm & ((sm & -sm) - 1ull));
+                        pos += popc64(vm);
+                        continue;
                     }
-                } else {
+                    const uint32_t how = s_how[w][j];
                     const int dl = A.key[x] - k;
                     const int ad = dl < 0 ? -dl : dl;
                     const int gap = ad > 0 ? ad - 1 : 0;
-                    const int t = touch_step(touch, ad);
-                    uint64_t& to = split && t != kApart ? wn : wf;
-                    A.ent[to++] = node_entry(x, t, budget - gap * gap);
+                    const int left = entry_budget(how) - gap * gap;
+                    if constexpr (kOrdered) {
+                        const bool self = v && x == (uint32_t)a;
+                    const int off = v && !self ? dk - left : kMaxD;
+                    const uint64_t sm = ballot(self);
+                    if (pass == 1 && sm) own = part[0] + (uint32_t)popc64(ballot(off == 0) & ((sm & -sm) - 1ull));
+                        uint32_t at = 0;
+#pragma unroll
+                        for (int o = 0; o < kMaxD; ++o) {
+                            if (o >= dk) continue;
+                            const uint64_t om = ballot(off == o);
+                            if (off == o) at = part[o] + (uint32_t)popc64(om & lt);
+                            part[o] += (uint32_t)popc64(om);
+                        }
+                        if (pass == 1 && off != kMaxD) A.ent[pos0 + at] = x;
+                        continue;
+                    }
+                    const int t = touch_step(entry_touch(how), ad);
+                    const uint32_t y = node_entry(x, t, left);
+                    const uint64_t nm = ballot(v && split && t != kApart), fm = ballot(v) & ~nm;
+                    const bool nr = (nm >> lane) & 1ull;
+                    uint64_t& fpos = split ? far : pos;
+                    const uint64_t to = nr ? pos + popc64(nm & lt) : fpos + popc64(fm & lt);
+                    if (v) A.ent[to] = y;
+                    fpos += popc64(fm);
+                    if (split) pos += popc64(nm);
                 }
-            }
-            const uint32_t ft = __shfl(fi, S - 1, S);
-            if (split) {
-                far += ft;
-                pos += __shfl(ni, S - 1, S);
+                wave_sync();
             } else {
-                pos += ft;
+                // the own grid is written nowhere
+                if (kGrids && in && b == p) --m;
+                const uint32_t f = m - mn;
+                const uint32_t fi = group_sum_scan<S>(f), ni = split ? group_sum_scan<S>(mn) : 0u;
+                uint64_t wf = (split ? far : pos) + (fi - f), wn = pos + (ni - mn);
+                for (uint32_t x = lo; x < hi; ++x) {
+                    if constexpr (kGrids) {
+                        if (x == (uint32_t)a) {
+                            own = (uint32_t)(wf - pos0);
+                        } else {
+                            A.ent[wf++] = x;
+                            above += x > (uint32_t)a ? 1u : 0u;
+                        }
+                    } else {
+                        const int dl = A.key[x] - k;
+                        const int ad = dl < 0 ? -dl : dl;
+                        const int gap = ad > 0 ? ad - 1 : 0;
+                        const int t = touch_step(touch, ad);
+                        uint64_t& to = split && t != kApart ? wn : wf;
+                        A.ent[to++] = node_entry(x, t, budget - gap * gap);
+                    }
+                }
+                const uint32_t ft = __shfl(fi, S - 1, S);
+                if (split) {
+                    far += ft;
+                    pos += __shfl(ni, S - 1, S);
+                } else {
+                    pos += ft;
+                }
             }
         }
     }
@@ -206,6 +258,8 @@ __global__ __launch_bounds__(kBlock) void level_kernel(LevelArgs A) {
             A.cnt[a] = total - (kGrids ? 1u : 0u);
             if (split) A.near[a] = nears;
         }
+    } else if constexpr (kOrdered) {
+        if (lane == 0) A.up[a] = make_uint2(own, zeros);
     } else if constexpr (kGrids) {
 #pragma unroll
         for (int o = S / 2; o > 0; o >>= 1) {
@@ -255,12 +309,16 @@ LevelArgs level_args(const GridView& g, const TreeView& t, const NodeLists& nl, 
     A.ent = nl.ent[l & 1];
     A.cap = nl.cap[l & 1];
     A.up = nl.up;
+    A.ck0 = g.ck;
+    A.count = g.b.count;
+    A.first = nl.ordered ? kNear / 2 : 0;
     A.hdr = g.b.hdr;
     return A;
 }
 
 template <bool kFill>
-hipError_t launch_level(const GridView& g, const LevelArgs& A, int l, int64_t nodes, int lanes, hipStream_t st) {
+hipError_t launch_level(const GridView& g, const LevelArgs& A, int l, int64_t nodes, int lanes, bool ordered,
+                        hipStream_t st) {
     const dim3 threads(kBlock);
     auto blocks = [&](int S) { return grid_of((nodes * S + kBlock - 1) / kBlock); };
     const bool grids = l == g.D;
@@ -270,8 +328,12 @@ hipError_t launch_level(const GridView& g, const LevelArgs& A, int l, int64_t no
         level_kernel<8, true, false, kFill><<<blocks(8), threads, 0, st>>>(A);
     else if (grids && lanes == 8)
         level_kernel<8, false, true, kFill><<<blocks(8), threads, 0, st>>>(A);
-    else if (grids)
+    else if (grids && lanes == 16)
         level_kernel<16, false, true, kFill><<<blocks(16), threads, 0, st>>>(A);
+    else if (grids && ordered && kFill)
+        level_kernel<kWave, false, true, kFill, kFill><<<blocks(kWave), threads, 0, st>>>(A);
+    else if (grids)
+        level_kernel<kWave, false, true, kFill><<<blocks(kWave), threads, 0, st>>>(A);
     else if (lanes <= 16)
         level_kernel<16, false, false, kFill><<<blocks(16), threads, 0, st>>>(A);
     else
@@ -285,7 +347,7 @@ hipError_t launch_level_count(const GridView& g, const TreeView& t, const NodeLi
                               int lanes, uint64_t* partial, hipStream_t st) {
     if (nodes <= 0) return hipSuccess;
     const LevelArgs A = level_args(g, t, nl, l);
-    const hipError_t e = launch_level<false>(g, A, l, nodes, lanes, st);
+    const hipError_t e = launch_level<false>(g, A, l, nodes, lanes, nl.ordered, st);
     if (e != hipSuccess) return e;
     return scan_apply<uint64_t>(NodeTotal{nl.cnt, A.nodes}, nodes + 1,
                                 NodeOffWriter{nl.off[l & 1], A.nodes, &g.b.hdr->nei_total}, (uint64_t*)nullptr, partial,
@@ -295,7 +357,7 @@ hipError_t launch_level_count(const GridView& g, const TreeView& t, const NodeLi
 hipError_t launch_level_fill(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
                              int lanes, hipStream_t st) {
     if (nodes <= 0) return hipSuccess;
-    return launch_level<true>(g, level_args(g, t, nl, l), l, nodes, lanes, st);
+    return launch_level<true>(g, level_args(g, t, nl, l), l, nodes, lanes, nl.ordered, st);
 }
 
 }  // namespace gd

@@ -46,8 +46,9 @@ __device__ __forceinline__ int touch_step(int touch, int ad) {
     return touch == kApart || ad > 1 ? kApart : min(touch + ad, kTouch);
 }
 
-// Candidate j (0..kNear-1) around a level-1 node: 0, +1, +2, +3, -1, -2, -3.
-__device__ __forceinline__ int near_step(int j) { return j <= 3 ? j : 3 - j; }
+// Candidate j (0..kNear-1) around a level-1 node: from -first on upwards, then
+// the others downwards (first 0: 0, +1, +2, +3, -1, -2, -3; first 3: -3 .. +3).
+__device__ __forceinline__ int near_step(int j, int first) { return j - first <= kNear / 2 ? j - first : kNear / 2 - j; }
 
 // Prefix sum within groups of S lanes.
 template <int S>

@@ -160,3 +160,25 @@ def test_limits_and_options_keep_their_paths(G):
     assert np.array_equal(lab.cpu().numpy(), ref[0]) and np.array_equal(core.cpu().numpy(), ref[1])
     assert want.stats()["neighbor_entries"] == entries
     want.close()
+
+
+@pytest.mark.parametrize("d,cells", [(4, 5), (5, 4), (6, 3)])
+@pytest.mark.parametrize("minpts", [4, 30])
+def test_dense_grids_from_four_dimensions(G, d, cells, minpts):
+    # about twenty points per grid: lists by offset built level by level, and
+    # (from five dimensions on) the big-set merge in two launches
+    side = 50.0
+    n = 20 * cells ** d
+    x = uniform(d, n, d, int(cells * side))
+    eps = int(side * np.sqrt(d)) + 1
+    ctx = check(G, x, eps, minpts, [(G.GD_OPT_NEIGHBOR_MODE, 1)])
+    assert ctx.stats()["core_grids"] >= 512 and n >= 8 * ctx.stats()["grids"]
+    _, _, ids = ctx.debug_grids()
+    off, nei = ctx.debug_neighbors()
+    want, _ = steps.neighbor_grids(ids)
+    for g in range(0, len(ids), max(1, len(ids) // 60)):
+        got = nei[off[g]:off[g + 1]].astype(np.int64)
+        order = sorted(want[g].tolist(), key=lambda h: (steps.grid_offset(ids[g], ids[h]), h))
+        assert got.tolist() == order, f"grid {g}"
+    ctx.close()
+    check(G, x, eps, minpts, [(G.GD_OPT_GRAPH, 2)]).close()
