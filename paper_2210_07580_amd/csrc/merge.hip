@@ -422,7 +422,8 @@ __global__ __launch_bounds__(kBlock, (kLearned || D >= 5) ? 4 : 6) void merge_bi
                                                            const uint32_t* __restrict__ nei, RunSource rs,
                                                            const uint32_t* __restrict__ ldf,
                                                            const uint4* __restrict__ rank, int64_t r0, int64_t r1,
-                                                           const uint32_t* split, uint32_t words, HugeQueue huge,
+                                                           int64_t skip, int64_t take, const uint32_t* split,
+                                                           uint32_t words, HugeQueue huge,
                                                            uint32_t* parent, MergeStats* stats, Proposal prop) {
     extern __shared__ uint64_t smem[];
     using Weights = typename std::conditional<kLearned, MlpMfma, float>::type;
@@ -438,7 +439,9 @@ __global__ __launch_bounds__(kBlock, (kLearned || D >= 5) ? 4 : 6) void merge_bi
     const int wpb = (int)(blockDim.x / kWave);
     const int w = wave_id();
     // with a device split the big core sets start right after the tiny ones
-    const int64_t r = (split ? (int64_t)*split : r0) + block_id() * wpb + w;
+    const int64_t nth = block_id() * wpb + w;
+    const int64_t r = (split ? (int64_t)*split : r0) + skip + nth;
+    if (nth >= take) return;
     if (r >= r1 || r >= (int64_t)co.counts[1]) return;
     const uint32_t ci = ldf[r];
     // every load that depends on ci alone is issued before the first use
@@ -677,29 +680,53 @@ hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei
     while (wpb > 1 && (size_t)wpb * 2 * words * sizeof(uint64_t) > 65536) wpb >>= 1;
     const size_t lds = (size_t)wpb * 2 * words * sizeof(uint64_t);
     if (lds > 65536) return hipErrorInvalidValue;
-    const dim3 blocks = grid_of((ncc - b0 + wpb - 1) / wpb);
     // the scorer's weights take static LDS beside the bitmaps; if both do not
     // fit, or on the wide path, run without the proposal (the answers are the
     // same)
     const bool learned = prop.weights && !wide &&
                          lds + sizeof(MlpMfma) + kWavesPerBlock * (sizeof(MlpMfmaScratch) + sizeof(float2) * kWave) <=
                              65536;
-    if (runs) {
-        GD_DISPATCH_D(g.D, ({
-                          if constexpr (D >= kMinRunD)
-                              merge_big_kernel<D, false, false, true><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                                  g, c, nullptr, nullptr, *runs, ldf_list, rank, b0, ncc, split, words, huge, parent,
-                                  nullptr, prop);
-                      }));
-    } else if (learned) {
-        GD_DISPATCH_D(g.D, (merge_big_kernel<D, true, false, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                               g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
-    } else if (wide) {
-        GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, true, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                               g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
-    } else {
-        GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, false, false><<<blocks, dim3(wpb * kWave), lds, st>>>(
-                               g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, split, words, huge, parent, stats, prop)));
+    // The visiting order only helps where later waves start after earlier ones
+    // ended: the denser grids' pairs are then mostly joined already.  With
+    // fewer grids than the GPU holds waves all of them start at once and the
+    // densest test everything, on the longest waves; two launches put the
+    // denser half behind the sparser.  Taken where the lists are long (five
+    // dimensions and more): 7-D with 5,892 and 3,758 core grids 670 -> 272 and 740 ->
+    // 417 us, 5-D with 2,755, 1,543 and 984 580 -> 410, 615 -> 455 and 650 -> 560 us; 5-D
+    // with 6,310 370 -> 400 us, and in two and three dimensions the second launch's
+    // own tail costs more as often as not (2M points at eps 1000 284 -> 391 us).
+    const int64_t all = ncc - b0;
+    const int parts = g.D >= 5 && n_small != -1 && all >= 512 && all <= 6000 ? 2 : 1;
+    auto launch = [&](int64_t skip, int64_t take) -> hipError_t {
+        const dim3 blocks = grid_of((take + wpb - 1) / wpb), threads(wpb * kWave);
+        if (runs) {
+            GD_DISPATCH_D(g.D, ({
+                              if constexpr (D >= kMinRunD)
+                                  merge_big_kernel<D, false, false, true><<<blocks, threads, lds, st>>>(
+                                      g, c, nullptr, nullptr, *runs, ldf_list, rank, b0, ncc, skip, take, split, words,
+                                      huge, parent, nullptr, prop);
+                          }));
+        } else if (learned) {
+            GD_DISPATCH_D(g.D, (merge_big_kernel<D, true, false, false><<<blocks, threads, lds, st>>>(
+                                   g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, skip, take, split, words,
+                                   huge, parent, stats, prop)));
+        } else if (wide) {
+            GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, true, false><<<blocks, threads, lds, st>>>(
+                                   g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, skip, take, split, words,
+                                   huge, parent, stats, prop)));
+        } else {
+            GD_DISPATCH_D(g.D, (merge_big_kernel<D, false, false, false><<<blocks, threads, lds, st>>>(
+                                   g, c, nei_off, nei, RunSource{}, ldf_list, rank, b0, ncc, skip, take, split, words,
+                                   huge, parent, stats, prop)));
+        }
+        return hipGetLastError();
+    };
+    for (int p = 0; p < parts; ++p) {
+        const int64_t lo = all * p / parts, hi = all * (p + 1) / parts;
+        if (lo < hi) {
+            const hipError_t e = launch(lo, hi - lo);
+            if (e != hipSuccess) return e;
+        }
     }
     return hipGetLastError();
 }
