@@ -104,7 +104,9 @@ struct gd_ctx {
     size_t bump_cap = 0, bump_used = 0;
     char* scratch = nullptr;  // this device's scratch array (hipGetSymbolAddress at gd_create)
     Header* hdr_dev = nullptr;
-    Header* hdr_host = nullptr;  // pinned
+    Header* hdr_host = nullptr;  // pinned: the header, then (kSeqWord words on) the number of its last publication
+    uint32_t* hdr_map = nullptr; // the same memory as the device writes it
+    uint32_t seq = 0;
     StatBlock* stats_dev = nullptr;
     StatBlock* stats_host = nullptr;  // pinned
     Inst* inst_dev = nullptr;
@@ -419,9 +421,38 @@ Layout carve(char* base, int64_t n, int D, uint32_t tiles, int key_bytes, bool e
     return L;
 }
 
+// The counts a phase left in the header, to host memory.  A copy command and a
+// stream synchronisation take about twice the time from the phase's last kernel
+// to the host's next launch that this takes: the kernel stores the header and
+// then its number into pinned memory, and the host watches the number (a call
+// of a thousand points, five read-backs: 217 -> 207 us).  A phase of more than
+// kWatch is waited for with the stream, which also reports a failed kernel.
+constexpr int kSeqWord = 32;
+static_assert(sizeof(Header) <= kSeqWord * sizeof(uint32_t) && sizeof(Header) / sizeof(uint32_t) <= kWave, "one wave");
+constexpr std::chrono::microseconds kWatch{500};
+
+__global__ void publish_kernel(const Header* hdr, uint32_t* host, uint32_t seq) {
+    constexpr int words = (int)(sizeof(Header) / sizeof(uint32_t));
+    if (threadIdx.x < words)
+        __hip_atomic_store(host + threadIdx.x, reinterpret_cast<const uint32_t*>(hdr)[threadIdx.x], __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    if (threadIdx.x == 0) __hip_atomic_store(host + kSeqWord, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 int readback(gd_ctx* ctx, hipStream_t st) {
-    GD_TRY(hipMemcpyAsync(ctx->hdr_host, ctx->hdr_dev, sizeof(Header), hipMemcpyDeviceToHost, st));
-    GD_TRY(hipStreamSynchronize(st));
+    const uint32_t seq = ++ctx->seq;
+    const uint32_t* number = reinterpret_cast<const uint32_t*>(ctx->hdr_host) + kSeqWord;
+    publish_kernel<<<1, kWave, 0, st>>>(ctx->hdr_dev, ctx->hdr_map, seq);
+    GD_TRY(hipGetLastError());
+    const auto until = std::chrono::steady_clock::now() + kWatch;
+    for (uint32_t n = 0; __atomic_load_n(number, __ATOMIC_ACQUIRE) != seq; ++n) {
+        if (n % 256 != 255 || std::chrono::steady_clock::now() < until) continue;
+        GD_TRY(hipStreamSynchronize(st));
+        if (__atomic_load_n(number, __ATOMIC_ACQUIRE) != seq)
+            return ctx->fail(GD_EDEVICE, "the device header was not published");
+        break;
+    }
     return GD_OK;
 }
 
@@ -1134,6 +1165,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         return GD_OK;
     }
     if ((rc = readback(ctx, st))) return rc;
+    GD_TRY(hipStreamSynchronize(st));  // the call is synchronous on its stream
     if (H->err & kErrMergeRunaway) return ctx->fail(GD_EDEVICE, "merge step exceeded its iteration bound");
     if (H->err & (kErrNeiOverflow | kErrCoreCap))
         return ctx->fail(GD_EDEVICE, "internal capacity check failed (error bits 0x%x)", H->err);
@@ -1524,7 +1556,8 @@ int gd_create(gd_ctx** out, int device) {
     {
         DeviceGuard guard(device);
         ok = guard.ok && hipMalloc(&ctx->hdr_dev, sizeof(Header)) == hipSuccess &&
-             hipHostMalloc(&ctx->hdr_host, sizeof(Header), hipHostMallocDefault) == hipSuccess &&
+             hipHostMalloc(&ctx->hdr_host, (kSeqWord + 1) * sizeof(uint32_t), hipHostMallocDefault) == hipSuccess &&
+             hipHostGetDevicePointer((void**)&ctx->hdr_map, ctx->hdr_host, 0) == hipSuccess &&
              hipMalloc(&ctx->stats_dev, sizeof(StatBlock)) == hipSuccess &&
              hipHostMalloc(&ctx->stats_host, sizeof(StatBlock), hipHostMallocDefault) == hipSuccess &&
              hipMalloc(&ctx->proposal_dev, sizeof(__half) * kParams) == hipSuccess &&
@@ -1532,6 +1565,7 @@ int gd_create(gd_ctx** out, int device) {
              ensure_inst_capacity(ctx, 16) == GD_OK;
         // with the device current: this device's copy of the scratch array
         if (ok) ctx->scratch = scratch_address(device);
+        if (ok) std::memset(ctx->hdr_host, 0, (kSeqWord + 1) * sizeof(uint32_t));
         if (ok) {
             ctx->events_ok = true;
             for (int p = 0; p < P_COUNT; ++p)
