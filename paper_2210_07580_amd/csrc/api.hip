@@ -1125,7 +1125,9 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
                    ctx->cur->arena.cap + ctx->cur->nei.cap + ctx->cur->sumbuf.cap + ctx->cur->huge.cap)))
         return rc;
     ctx->mark(P_OUTPUT, 0);
-    if (kbytes == 4)
+    if (n <= kOutputSmall)
+        GD_TRY(launch_output_small(g, co, L.cell_label, st));
+    else if (kbytes == 4)
         GD_TRY(launch_output_direct<uint32_t>(g, co, (const uint32_t*)L.keys_a, (const uint32_t*)skeys, L.cell_label,
                                               ctx->cur->table.p, hbits, 0, st));
     else if (kbytes == 8)

@@ -473,6 +473,9 @@ hipError_t launch_output_direct(const GridView& g, const CoreOut& c, const K* ke
 size_t output_table_bytes(int bits, int key_bytes);
 // All-core grids of identifiers wider than 64 bits: output through the
 // sort permutation (no hash table).
+// The same for calls of at most kOutputSmall points, any identifiers.
+constexpr int64_t kOutputSmall = 1 << 17;
+hipError_t launch_output_small(const GridView& g, const CoreOut& c, const int32_t* cell_label, hipStream_t st);
 hipError_t launch_output_allcore(const GridView& g, const CoreOut& c, const int32_t* cell_label, hipStream_t st);
 
 }  // namespace gd

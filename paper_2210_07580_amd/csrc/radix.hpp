@@ -261,6 +261,131 @@ __global__ __launch_bounds__(kBlock) void radix_scatter_kernel(const K* __restri
     }
 }
 
+// A short sort in one launch: one workgroup of 1024 threads holds the keys and
+// values in registers (wave w the w-th run of 64 kItems of them, so that ranks
+// follow input order), ranks them per pass as radix_scatter_kernel does and
+// exchanges them through LDS; the last pass stores through `out`.  A short call
+// is bound by its launches (about 5 us each): three per pass become one for
+// all passes: a call of a thousand points 207 -> 199 us, the core grids' order of
+// 1,931 grids in a call of 300k points 398 -> 381 us.  With sixteen entries a
+// thread a pass of 10,000 takes 16 us, more than the three launches (the call
+// 253 -> 260 us), so the line is the 4096 entries of four a thread.
+constexpr int kSmallSortThreads = 1024;
+constexpr int kSmallSortWaves = kSmallSortThreads / kWave;
+constexpr int kSmallSortItems = 4;
+constexpr int64_t kSmallSortMax = (int64_t)kSmallSortThreads * kSmallSortItems;
+
+template <typename K, typename V, typename Out>
+__global__ __launch_bounds__(kSmallSortThreads) void radix_small_kernel(const K* __restrict__ keys,
+                                                                        const V* __restrict__ vals, Out out, int n,
+                                                                        int lo, int rbits, int passes, int iota) {
+    constexpr int kMaxBins = radix_max_bins<K>();
+    constexpr int kItems = kSmallSortItems;
+    constexpr int kPerWave = kWave * kItems;
+    __shared__ __align__(16) unsigned char raw[kSmallSortMax * (sizeof(K) > sizeof(V) ? sizeof(K) : sizeof(V))];
+    K* const xk = reinterpret_cast<K*>(raw);
+    V* const xv = reinterpret_cast<V*>(raw);
+    __shared__ uint32_t wcnt[kSmallSortWaves][kMaxBins];  // keys per (wave, digit), then first slot
+    __shared__ uint32_t wsum[kMaxBins / kWave];
+    const int t = threadIdx.x, w = wave_id(), lane = lane_id();
+    const uint64_t lt = lanemask_lt();
+    const int bins = 1 << rbits;
+    K k[kItems];
+    V v[kItems];
+#pragma unroll
+    for (int it = 0; it < kItems; ++it) {
+        const int i = w * kPerWave + it * kWave + lane;
+        k[it] = i < n ? keys[i] : K(0);
+        v[it] = i < n ? (iota ? (V)i : vals[i]) : V(0);
+    }
+    out.begin();
+    for (int p = 0, shift = lo; p < passes; ++p, shift += rbits) {
+        for (int i = t; i < kSmallSortWaves * kMaxBins; i += kSmallSortThreads) (&wcnt[0][0])[i] = 0;
+        __syncthreads();
+        uint32_t dr[kItems];  // digit << 16 | rank within the wave
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            dr[it] = 0;
+            const int i0 = w * kPerWave + it * kWave;
+            if (i0 >= n) continue;
+            const bool valid = i0 + lane < n;
+            const uint32_t dg = (uint32_t)(k[it] >> shift) & ((uint32_t)bins - 1u);
+            const uint64_t vm = ballot(valid);
+            uint32_t plo = (uint32_t)vm, phi = (uint32_t)(vm >> 32);
+            for (int b = 0; b < rbits; ++b) {
+                const uint32_t x = (uint32_t)(((int32_t)(dg << (31 - b))) >> 31);
+                const uint64_t m = ballot(x != 0u);
+                plo &= ~((uint32_t)m ^ x);
+                phi &= ~((uint32_t)(m >> 32) ^ x);
+            }
+            const uint64_t peers = ((uint64_t)phi << 32) | plo;
+            const uint32_t before = valid ? wcnt[w][dg] : 0u;
+            wave_sync();
+            if (valid && (peers & lt) == 0) wcnt[w][dg] = before + (uint32_t)popc64(peers);
+            wave_sync();
+            dr[it] = (dg << 16) | (before + (uint32_t)popc64(peers & lt));
+        }
+        __syncthreads();
+        // thread t < 256: first slot of digit t in each wave
+        uint32_t total = 0, incl = 0;
+        if (t < kMaxBins) {
+            if (t < bins)
+                for (int ww = 0; ww < kSmallSortWaves; ++ww) total += wcnt[ww][t];
+            incl = wave_incl_scan(total);
+            if (lane == kWave - 1) wsum[w] = incl;
+        }
+        __syncthreads();
+        if (t < bins) {
+            uint32_t acc = incl - total;
+            for (int ww = 0; ww < w; ++ww) acc += wsum[ww];
+            for (int ww = 0; ww < kSmallSortWaves; ++ww) {
+                const uint32_t c = wcnt[ww][t];
+                wcnt[ww][t] = acc;
+                acc += c;
+            }
+        }
+        __syncthreads();
+        const bool last = p == passes - 1;
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const int i = w * kPerWave + it * kWave + lane;
+            dr[it] = wcnt[w][dr[it] >> 16] + (dr[it] & 0xFFFFu);
+            if (i < n) {
+                if (last)
+                    out.store(dr[it], k[it], v[it]);
+                else
+                    xk[dr[it]] = k[it];
+            }
+        }
+        if (last) break;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const int i = w * kPerWave + it * kWave + lane;
+            if (i < n) k[it] = xk[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it)
+            if (w * kPerWave + it * kWave + lane < n) xv[dr[it]] = v[it];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kItems; ++it) {
+            const int i = w * kPerWave + it * kWave + lane;
+            if (i < n) v[it] = xv[i];
+        }
+    }
+}
+
+// Launches it; `out` is bound to the sorted keys and values.
+template <typename K, typename V, typename Out>
+hipError_t radix_sort_small(const K* keys, const V* vals, Out out, int64_t n, int lo, int rbits, int passes, bool iota,
+                            hipStream_t st) {
+    radix_small_kernel<K, V, Out><<<1, kSmallSortThreads, 0, st>>>(keys, vals, out, (int)n, lo, rbits, passes,
+                                                                   iota ? 1 : 0);
+    return hipGetLastError();
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void iota_kernel(T* v, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -299,6 +424,22 @@ hipError_t radix_sort_pairs(K* keys, V* vals, K* keys_alt, V* vals_alt, int64_t 
     bool fused = false;
     const int passes = bits <= 0 ? 0 : (bits + radix_max_bits<K>() - 1) / radix_max_bits<K>();
     const int rbits = passes ? (bits + passes - 1) / passes : 0;
+    if (passes > 0 && n > 0 && n <= kSmallSortMax) {
+        hipError_t e;
+        if (last) {
+            Last o = *last;
+            o.bind(kout, vout);
+            e = radix_sort_small<K, V>(kin, vin, o, n, lo, rbits, passes, iota, st);
+        } else {
+            PairOut<K, V> o;
+            o.bind(kout, vout);
+            e = radix_sort_small<K, V>(kin, vin, o, n, lo, rbits, passes, iota, st);
+        }
+        out->keys = kout;
+        out->vals = vout;
+        out->last_fused = last != nullptr;
+        return e;
+    }
     for (int p = 0, shift = lo; p < passes; ++p, shift += rbits) {
         if (n == 0) break;
         const int64_t bins = (int64_t)1 << rbits;
