@@ -86,8 +86,8 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
                                                            SplitQueue sq) {
     constexpr int PW = packed_words<D>();
     constexpr int S = row_stride(D);
-    __shared__ uint32_t s_start[kWavesPerBlock][kWave];
-    __shared__ uint32_t s_excl[kWavesPerBlock][kWave];
+    __shared__ uint32_t s_row[kWavesPerBlock][kWave];   // first row of each lane's grid, minus its place
+    __shared__ uint32_t s_head[kWavesPerBlock][kWave];  // its place, or (R = 2) lane + 1 of the grid that starts at this candidate
     __shared__ __align__(16) int32_t s_q[kWavesPerBlock][kWave * S];  // the query rows of the batch
     const int w = wave_id(), lane = lane_id();
     const int64_t c = xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w;
@@ -169,25 +169,44 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
                 }
                 const uint32_t incl = wave_incl_scan(cn);
                 const uint32_t tot = last_lane(incl);
-                s_start[w][lane] = cs;
-                s_excl[w][lane] = incl - cn;
-                wave_sync();
-                // row of flat candidate t (t < tot): binary search over the
-                // chunk's 64 grids
-                auto cand_row = [&](uint32_t t) -> uint32_t {
-                    int j = 0;
+                const uint32_t excl = incl - cn;
+                s_row[w][lane] = cs - excl;
+                if constexpr (R == 1) {
+                    s_head[w][lane] = excl;
+                    wave_sync();
+                }
+                // Row of flat candidate t0 + lane.  Long streams (R = 2): the
+                // grids that start within the step mark their first candidate,
+                // a running maximum over the lanes gives each candidate its
+                // grid, and the last one carries over to the next step (10M
+                // 3-D points 98 -> 93 us).  Short ones: a binary search over the
+                // chunk's 64 grids (the batch of 256 2.21 against 2.29 ms).
+                uint32_t carry = 0;
+                auto cand_row = [&](uint32_t t0) -> uint32_t {
+                    if constexpr (R == 1) {
+                        int j = 0;
 #pragma unroll
-                    for (int step = 32; step > 0; step >>= 1)
-                        if (s_excl[w][j + step] <= t) j += step;
-                    return s_start[w][j] + (t - s_excl[w][j]);
+                        for (int step = 32; step > 0; step >>= 1)
+                            if (s_head[w][j + step] <= t0 + lane) j += step;
+                        return s_row[w][j] + t0 + lane;
+                    }
+                    s_head[w][lane] = 0;
+                    wave_sync();
+                    if (cn != 0 && excl >= t0 && excl < t0 + kWave) s_head[w][excl - t0] = (uint32_t)lane + 1u;
+                    wave_sync();
+                    uint32_t own = wave_max_scan(s_head[w][lane]);
+                    own = own ? own : carry;
+                    carry = last_lane(own);
+                    return s_row[w][(own ? own : 1u) - 1u] + t0 + lane;
                 };
                 // R candidates per lane per step (64 R per step), and the next
                 // step's candidates load while this one is evaluated
                 int32_t y[R][D];
 #pragma unroll
                 for (int u = 0; u < R; ++u) {
-                    const uint32_t t = (uint32_t)(u * kWave + lane);
-                    load_row<D>(gv.crd, t < tot ? cand_row(t) : st, y[u]);
+                    uint32_t r = st;
+                    if ((uint32_t)(u * kWave) < tot) r = cand_row((uint32_t)(u * kWave));
+                    load_row<D>(gv.crd, (uint32_t)(u * kWave + lane) < tot ? r : st, y[u]);
                 }
                 for (uint32_t t0 = 0; t0 < tot && active; t0 += R * kWave) {
                     uint64_t tvm[R];
@@ -196,8 +215,10 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
                     int32_t yn[R][D];
 #pragma unroll
                     for (int u = 0; u < R; ++u) {
-                        const uint32_t tn = t0 + (R + u) * kWave + lane;
-                        load_row<D>(gv.crd, tn < tot ? cand_row(tn) : st, yn[u]);
+                        const uint32_t tn = t0 + (R + u) * kWave;
+                        uint32_t r = st;
+                        if (tn < tot) r = cand_row(tn);
+                        load_row<D>(gv.crd, tn + lane < tot ? r : st, yn[u]);
                     }
                     int32_t yp[R][PW];
                     if constexpr (kPacked) {
