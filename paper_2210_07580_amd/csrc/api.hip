@@ -1008,7 +1008,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         sq.left = (uint32_t*)L.cell_label;
         sq.hits = L.list;
         GD_TRY(launch_core_mark(g, L.nei_off, nei, by_level && ordered ? grid_up : nullptr, rs, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
-                                max_eps, min_minpts, split ? &sq : nullptr, st));
+                                max_eps, min_minpts, split ? &sq : nullptr, small_lanes, st));
     }
     ctx->mark(P_CORE_MARK, 1);
     CoreOut co{};

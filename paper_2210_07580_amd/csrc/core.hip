@@ -73,6 +73,9 @@ __device__ __forceinline__ uint32_t sqdist_pk(const int32_t (&a)[packed_words<D>
     return (uint32_t)acc;
 }
 
+// Candidates of one list step above which a grid leaves its group of 16 lanes.
+constexpr uint32_t kGroupStream = 256;
+
 // R: candidate rows per lane per step.  The slowest grids stream dozens of
 // steps one after another, each a chain of dependent rounds, so with a large
 // MinPts (a query needs more hits than one 64-candidate step can give) a
@@ -417,6 +420,169 @@ __global__ __launch_bounds__(kBlock) void core_tasks_kernel(GridView gv, uint8_t
         if (lane == 0) core_cnt[c] = m;
     }
 }
+// One grid with fewer than MinPts points, marked by S lanes (16: a quarter of a
+// wave, 64: all of it) whose first lane is g0.  As core_mark_kernel, with every
+// scan, mask and count taken within the group; a step takes two candidates per
+// lane.  Returns false, with nothing written, if a group of 16 meets a long
+// stream or more points than lanes: those want a whole wave.
+template <int S, int D, bool kPacked>
+__device__ __forceinline__ bool mark_grid(const GridView& gv, const uint32_t* __restrict__ nei, uint32_t st, uint32_t k,
+                                          uint64_t e0, uint64_t e1, uint32_t need, uint32_t T, int g0, int sub,
+                                          uint32_t* row, uint32_t* place, int32_t* qrow, uint8_t* __restrict__ core,
+                                          uint32_t& m) {
+    constexpr int R = 2;
+    constexpr int PW = packed_words<D>();
+    constexpr int QW = kPacked ? PW : D;
+    constexpr uint64_t kAll = S == kWave ? ~0ull : (1ull << (S & 63)) - 1ull;
+    auto group = [&](bool x) -> uint64_t { return (ballot(x) >> g0) & kAll; };
+    m = 0;
+    if (S < kWave && k > (uint32_t)S) return false;
+    for (uint32_t qb = 0; qb < k; qb += S) {
+        const uint32_t nq = min((uint32_t)S, k - qb);
+        uint64_t active = nq == (uint32_t)kWave ? ~0ull : (1ull << nq) - 1ull;
+        {
+            int32_t qx[D];
+            load_row<D>(gv.crd, (uint32_t)sub < nq ? st + qb + sub : st, qx);
+            if constexpr (kPacked) {
+                int32_t pq[PW];
+                pack_row<D>(qx, pq);
+                store_row<PW>(qrow, sub, pq);
+            } else {
+                store_row<D>(qrow, sub, qx);
+            }
+        }
+        uint32_t mycnt = 0;  // lane i of the group: hits of query i
+        for (uint64_t e = e0; e < e1 && active; e += S) {
+            uint32_t cs = 0, cn = 0;
+            if (e + sub < e1) {
+                const uint32_t cc = nei[e + sub];
+                cs = gv.cell_start[cc];
+                cn = gv.cell_start[cc + 1] - cs;
+            }
+            uint32_t incl = cn;
+            if constexpr (S == kWave) {
+                incl = wave_incl_scan(incl);
+            } else {
+                incl += dpp<kRowShr + 1>(0u, incl);
+                incl += dpp<kRowShr + 2>(0u, incl);
+                incl += dpp<kRowShr + 4>(0u, incl);
+                incl += dpp<kRowShr + 8>(0u, incl);
+            }
+            const uint32_t tot = __shfl(incl, S - 1, S);
+            if (S < kWave && tot > kGroupStream) return false;
+            row[sub] = cs - (incl - cn);
+            place[sub] = incl - cn;
+            wave_sync();
+            for (uint32_t t0 = 0; t0 < tot && active; t0 += R * S) {
+                int32_t y[R][QW];
+                bool in[R];
+#pragma unroll
+                for (int u = 0; u < R; ++u) {
+                    const uint32_t t = t0 + u * S + sub;
+                    in[u] = t < tot;
+                    int j = 0;
+#pragma unroll
+                    for (int step = S / 2; step > 0; step >>= 1)
+                        if (place[j + step] <= t) j += step;
+                    int32_t x[D];
+                    load_row<D>(gv.crd, in[u] ? row[j] + t : st, x);
+                    if constexpr (kPacked) {
+                        pack_row<D>(x, y[u]);
+                    } else {
+#pragma unroll
+                        for (int d = 0; d < D; ++d) y[u][d] = x[d];
+                    }
+                }
+                uint32_t hits = 0;
+                for (uint64_t act = active; act; act &= act - 1ull) {
+                    const int q = ffs64(act);
+                    int32_t p[QW];
+                    load_row<QW>(qrow, q, p);
+                    uint32_t h = 0;
+#pragma unroll
+                    for (int u = 0; u < R; ++u) {
+                        if constexpr (kPacked)
+                            h += (uint32_t)popc64(group(in[u] && sqdist_pk<D>(y[u], p) <= T));
+                        else
+                            h += (uint32_t)popc64(group(in[u] && sqdist_nb<D, false>(y[u], p) <= T));
+                    }
+                    hits = sub == q ? h : hits;
+                }
+                mycnt += hits;
+                active &= ~group(mycnt >= need);
+            }
+            wave_sync();
+        }
+        const bool is_core = (uint32_t)sub < nq && !((active >> sub) & 1ull);
+        if ((uint32_t)sub < nq) core[st + qb + sub] = is_core ? 1 : 0;
+        m += (uint32_t)popc64(group(is_core));
+    }
+    return true;
+}
+
+// Marking with 16 lanes per grid, four grids side by side in a wave, for short
+// lists and small grids (the rule of the other small-grid kernels): a grid of a
+// few noise points with a few neighbours fills a quarter of a wave's lanes at
+// best, and the kernel is bound by the instructions and dependent loads of each
+// wave.  Grids that want more are taken by the whole wave one after another.
+// Lists of 40 and grids of 32 points on
+// average: the batch of 256 2,255 -> 1,514 us, 2M 3-D points in small clusters
+// 105 -> 58, 1M 2-D noise beside lumps of 1e5 303 -> 109; without the whole wave
+// the last of these shapes went up to 520 from 390 us.  MinPts above 32 stays
+// with a wave per grid (60: 368 us there, 671 here).
+template <int D, bool kPacked>
+__global__ __launch_bounds__(kBlock) void core_mark_group_kernel(GridView gv, const uint64_t* __restrict__ nei_off,
+                                                                 const uint32_t* __restrict__ nei,
+                                                                 uint8_t* __restrict__ core,
+                                                                 uint32_t* __restrict__ core_cnt) {
+    constexpr int S = 16, G = kWave / S;
+    constexpr int Q = row_stride(kPacked ? packed_words<D>() : D);
+    __shared__ uint32_t s_row[kWavesPerBlock][kWave];    // first row of each lane's grid, minus its place
+    __shared__ uint32_t s_place[kWavesPerBlock][kWave];  // its place
+    __shared__ __align__(16) int32_t s_q[kWavesPerBlock][kWave * Q];
+    const int w = wave_id(), lane = lane_id();
+    const int grp = lane / S, sub = lane % S, g0 = grp * S;
+    const int64_t c = (xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w) * G + grp;
+    bool whole = false;  // the grid waits for the whole wave
+    uint32_t st = 0, k = 0, need = 0, T = 0;
+    uint64_t e0 = 0, e1 = 0;
+    if (c < (int64_t)*gv.ncell_dev) {
+        const Inst& I = cell_inst(gv, c);
+        st = gv.cell_start[c];
+        k = gv.cell_start[c + 1] - st;
+        e0 = nei_off[c];
+        e1 = nei_off[c + 1];
+        T = I.T;
+        if (kPacked && I.eps > kPackedEpsMax) {
+            // a replayed graph met a larger eps than it was captured for: the
+            // packed differences could wrap, so the run is discarded
+            if (sub == 0) atomicOr(&gv.b.hdr->err, kErrPlan);
+        } else if (k >= (uint32_t)I.minpts) {
+            for (uint32_t i = sub; i < k; i += S) core[st + i] = 1;
+            if (sub == 0) core_cnt[c] = k;
+        } else {
+            need = (uint32_t)I.minpts - k;
+            uint32_t m;
+            if (mark_grid<S, D, kPacked>(gv, nei, st, k, e0, e1, need, T, g0, sub, &s_row[w][g0], &s_place[w][g0],
+                                         &s_q[w][g0 * Q], core, m)) {
+                if (sub == 0) core_cnt[c] = m;
+            } else {
+                whole = true;
+            }
+        }
+    }
+    for (uint64_t todo = ballot(whole && sub == 0); todo; todo &= todo - 1ull) {
+        const int src = ffs64(todo);
+        wave_sync();
+        auto lo = [&](uint32_t v) -> uint32_t { return (uint32_t)__builtin_amdgcn_readlane((int)v, src); };
+        auto wide = [&](uint64_t v) -> uint64_t { return (uint64_t)lo((uint32_t)(v >> 32)) << 32 | lo((uint32_t)v); };
+        uint32_t m;
+        mark_grid<kWave, D, kPacked>(gv, nei, lo(st), lo(k), wide(e0), wide(e1), lo(need), lo(T), 0, lane, s_row[w],
+                                     s_place[w], s_q[w], core, m);
+        if (lane == src) core_cnt[c] = m;
+    }
+}
+
 // Marking with neighbours as runs (runs.hpp): as core_mark_kernel, but a lane
 // owns a run of neighbouring grids, which is one contiguous range of points;
 // the own points come with the run of the own family and count like the others.
@@ -601,7 +767,7 @@ hipError_t launch_core_mark_runs(const GridView& g, const RunSource& rs, uint8_t
 hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const uint2* mid,
                             const RunSource* runs,
                             uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
-                            const SplitQueue* split, hipStream_t st) {
+                            const SplitQueue* split, int lanes, hipStream_t st) {
     if (g.ncell == 0) return hipSuccess;
     const bool packed = core_mark_packed(max_eps);
     const bool two = min_minpts > kWave / 2;
@@ -611,6 +777,16 @@ hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const ui
         if (packed) return launch_core_mark_runs<true, 1>(g, *runs, core, core_cnt, st);
         if (two) return launch_core_mark_runs<false, 2>(g, *runs, core, core_cnt, st);
         return launch_core_mark_runs<false, 1>(g, *runs, core, core_cnt, st);
+    }
+    if (lanes == 16 && !two && !stats && !split && max_eps <= GD_EPS_MAX) {
+        const dim3 blocks = grid_of((g.ncell + 4 * kWavesPerBlock - 1) / (4 * kWavesPerBlock));
+        if (packed)
+            GD_DISPATCH_D(g.D, (core_mark_group_kernel<D, true><<<blocks, dim3(kBlock), 0, st>>>(g, nei_off, nei, core,
+                                                                                               core_cnt)));
+        else
+            GD_DISPATCH_D(g.D, (core_mark_group_kernel<D, false><<<blocks, dim3(kBlock), 0, st>>>(g, nei_off, nei, core,
+                                                                                                core_cnt)));
+        return hipGetLastError();
     }
     // the counting variant takes the same steps as the timed one
     if (max_eps > GD_EPS_MAX) {  // 64-bit distances, one row per step

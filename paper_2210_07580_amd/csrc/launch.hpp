@@ -337,11 +337,12 @@ struct SplitQueue {
 // cells tested against the open queries first (d <= 4).
 // runs (or nullptr): neighbours as runs instead of lists (then without stats,
 // split and eps above GD_EPS_MAX).
-// mid (or nullptr): NodeLists::up of ordered lists.
+// mid (or nullptr): NodeLists::up of ordered lists.  lanes: 16 serves four grids
+// per wave (lists, MinPts up to 32, eps up to GD_EPS_MAX, no stats, no split).
 hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const uint2* mid,
                             const RunSource* runs,
                             uint8_t* core, uint32_t* core_cnt, CoreStats* stats, int64_t max_eps, int64_t min_minpts,
-                            const SplitQueue* split, hipStream_t st);
+                            const SplitQueue* split, int lanes, hipStream_t st);
 // Whether core marking compares coordinates as packed 16-bit differences
 // for a batch whose largest eps is max_eps (exact for eps <= 10000: points
 // of neighbouring grids differ by less than 2.13 eps per coordinate).
