@@ -51,10 +51,10 @@ PHASE_KERNELS = {
                    "(one instance with packed values: the last pass also writes the sorted rows)"],
     "gather": ["unpack_kernel or unpack64_kernel (rows rebuilt in order; gather_kernel when the low bits do "
                "not fit)"],
-    "core_mark": ["core_mark_kernel"],
-    "merge": ["merge_small_kernel", "merge_big_kernel"],
+    "core_mark": ["core_mark_kernel (core_mark_group_kernel for small grids, core_mark_runs_kernel on sparse data)"],
+    "merge": ["merge_small_kernel (merge_family_kernel on sparse data)", "merge_big_kernel"],
     "output": ["hash_clear_kernel", "hash_build_kernel", "output_direct_kernel", "output_kernel"],
-    "nei_fill": ["nei_fill_kernel"],
+    "nei_fill": ["level_kernel of the last level (nei_fill_kernel where lists come from walks)"],
 }
 
 

@@ -274,8 +274,8 @@ typedef enum {
                                  at most 2^20 grids whatever their size.
                                  The result is the same for every query.      */
     GD_OPT_GRID_LANES = 12,   /* lanes per grid in the kernels that serve
-                                 small grids (the merging of tiny core sets,
-                                 border assignment):
+                                 small grids (core marking, the merging of
+                                 tiny core sets, border assignment):
                                  0 (default) chooses from the mean list length
                                  and grid size (16 when they are at most 40
                                  entries and 32 points, else 64), 16 (four

@@ -989,8 +989,8 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         ctx->last_runs = runs;
         ctx->last_by_level = by_level;
     }
-    // lanes per grid in the kernels that serve small grids (tiny-set merge,
-    // border points): short lists leave most of a wave per grid idle
+    // lanes per grid in the kernels that serve small grids (core marking,
+    // tiny-set merge, border points): short lists leave most of a wave per grid idle
     const uint64_t grids = (uint64_t)std::max<int64_t>(ncell, 1);
     const bool few = nei_total <= 40 * grids;
     const int small_lanes = ctx->grid_lanes ? ctx->grid_lanes : few && (uint64_t)n <= 32 * grids ? 16 : 64;
@@ -1007,8 +1007,9 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         sq.count = &Hd->split[0];
         sq.left = (uint32_t*)L.cell_label;
         sq.hits = L.list;
-        GD_TRY(launch_core_mark(g, L.nei_off, nei, by_level && ordered ? grid_up : nullptr, rs, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr,
-                                max_eps, min_minpts, split ? &sq : nullptr, small_lanes, st));
+        GD_TRY(launch_core_mark(g, L.nei_off, nei, by_level && ordered ? grid_up : nullptr, rs, L.core, L.core_cnt,
+                                stats ? ctx->stats_dev->core : nullptr, max_eps, min_minpts, split ? &sq : nullptr,
+                                small_lanes, st));
     }
     ctx->mark(P_CORE_MARK, 1);
     CoreOut co{};

@@ -6,7 +6,9 @@
 // all core uses its sorted rows as they are, so only grids that mix core and
 // non-core points copy anything.
 //
-// Marking runs one wave per grid.  A grid with at least MinPts points is all
+// Marking runs one wave per grid (core_mark_group_kernel: four grids per wave
+// where grids and lists are small; core_mark_runs_kernel: neighbours as runs;
+// core_tasks_kernel: long streams of few large grids split up).  A grid with at least MinPts points is all
 // core (its diameter is below eps).  In a sparser grid every point already
 // has the grid's own points as neighbours; the wave then streams the points
 // of Nei(g), nearest grids first, as one flat list: each lane owns one
@@ -733,8 +735,8 @@ __global__ __launch_bounds__(kBlock) void core_mark_runs_kernel(GridView gv, Run
 
 template <bool kStats, bool kPacked, int R, bool kWide>
 hipError_t launch_core_mark_as(const GridView& g, const uint64_t* nei_off, const uint32_t* nei, const uint2* mid,
-                               uint8_t* core,
-                               uint32_t* core_cnt, CoreStats* stats, const SplitQueue* split, hipStream_t st) {
+                               uint8_t* core, uint32_t* core_cnt, CoreStats* stats, const SplitQueue* split,
+                               hipStream_t st) {
     const unsigned blocks = grid_for(g.ncell, kWavesPerBlock);
     if (split)
         GD_DISPATCH_D(g.D, ({
@@ -788,17 +790,20 @@ hipError_t launch_core_mark(const GridView& g, const uint64_t* nei_off, const ui
                                                                                                 core_cnt)));
         return hipGetLastError();
     }
-    // the counting variant takes the same steps as the timed one
+    // the counting variant takes the same steps as the timed one (of a wave per grid)
+    auto mark = [&](auto launch) { return launch(g, nei_off, nei, mid, core, core_cnt, stats, split, st); };
     if (max_eps > GD_EPS_MAX) {  // 64-bit distances, one row per step
-        if (stats) return launch_core_mark_as<true, false, 1, true>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
-        return launch_core_mark_as<false, false, 1, true>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+        return stats ? mark(launch_core_mark_as<true, false, 1, true>)
+                     : mark(launch_core_mark_as<false, false, 1, true>);
     }
-    if (stats && two) return launch_core_mark_as<true, false, 2, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
-    if (stats) return launch_core_mark_as<true, false, 1, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
-    if (packed && two) return launch_core_mark_as<false, true, 2, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
-    if (packed) return launch_core_mark_as<false, true, 1, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
-    if (two) return launch_core_mark_as<false, false, 2, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
-    return launch_core_mark_as<false, false, 1, false>(g, nei_off, nei, mid, core, core_cnt, stats, split, st);
+    if (stats)
+        return two ? mark(launch_core_mark_as<true, false, 2, false>)
+                   : mark(launch_core_mark_as<true, false, 1, false>);
+    if (packed)
+        return two ? mark(launch_core_mark_as<false, true, 2, false>)
+                   : mark(launch_core_mark_as<false, true, 1, false>);
+    return two ? mark(launch_core_mark_as<false, false, 2, false>)
+               : mark(launch_core_mark_as<false, false, 1, false>);
 }
 
 // Side rows of grid c: its core count if it also holds non-core points.

@@ -1,5 +1,8 @@
 // Non-empty neighbouring grids query (Section 4.2.2, Algorithm 3, Eq. (2)),
-// written out as lists Nei(g).
+// written out as lists Nei(g), one walk per grid.  Most calls build their lists
+// level by level instead (nodes.hip) or read neighbours as runs (runs.hpp); the
+// walks here serve workspaces that do not hold the node lists, D = 1, more
+// than 2^26 grids, and the comparison with direct hashing.
 //
 // Two queries produce the same sets:
 //   the grid tree (Algorithm 3): each grid walks the tree level by level
