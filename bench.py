@@ -54,7 +54,7 @@ PHASE_KERNELS = {
     "core_mark": ["core_mark_kernel (core_mark_group_kernel for small grids, core_mark_runs_kernel on sparse data)"],
     "merge": ["merge_small_kernel (merge_family_kernel on sparse data)", "merge_big_kernel"],
     "output": ["hash_clear_kernel", "hash_build_kernel", "output_direct_kernel", "output_kernel"],
-    "nei_fill": ["level_kernel of the last level (nei_fill_kernel where lists come from walks)"],
+    "nei_fill": ["nei_fill_kernel (lists in walk order and of four dimensions and more: level_kernel)"],
 }
 
 

@@ -1,8 +1,9 @@
 // Non-empty neighbouring grids query (Section 4.2.2, Algorithm 3, Eq. (2)),
-// written out as lists Nei(g), one walk per grid.  Most calls build their lists
-// level by level instead (nodes.hip) or read neighbours as runs (runs.hpp); the
-// walks here serve workspaces that do not hold the node lists, D = 1, more
-// than 2^26 grids, and the comparison with direct hashing.
+// written out as lists Nei(g), one walk per grid.  They serve lists ordered by
+// offset in up to three dimensions, D = 1, workspaces that do not hold node
+// lists, more than 2^26 grids, and the comparison with direct hashing; the other
+// calls build their lists level by level (nodes.hip) or read neighbours as
+// runs (runs.hpp).
 //
 // Two queries produce the same sets:
 //   the grid tree (Algorithm 3): each grid walks the tree level by level
