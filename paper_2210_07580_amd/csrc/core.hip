@@ -128,15 +128,13 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
         zeros = m.y;
         first = m.x > kWave / 2 ? m.x - kWave / 2 : 0u;
     }
-    const double side = kSplit && D <= 4 ? (double)I.eps / sqrt((double)I.d) : 0.0;
-    const double lim = (double)I.eps * (double)I.eps * (1.0 + 1e-9) + 1.0;
     unsigned long long ndist = 0, npts = 0, ncells = 0;
     uint32_t m = 0, tasks = 0;
     for (uint32_t qb = 0; qb < k; qb += kWave) {
         const uint32_t nq = min((uint32_t)kWave, k - qb);
         uint64_t active = nq == (uint32_t)kWave ? ~0ull : ((1ull << nq) - 1ull);
-        int32_t qx[D];
         {
+            int32_t qx[D];
             load_row<D>(gv.crd, (uint32_t)lane < nq ? st + qb + lane : st, qx);
             if constexpr (kPacked) {
                 int32_t pq[PW];
@@ -164,12 +162,6 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
                     if ((cn >= kSplitRows) != large) {
                         later |= cn >= kSplitRows;
                         cn = 0;
-                    }
-                    // a grid of 16 steps or more is dropped when no open query
-                    // comes within eps of its cell, since the noise points of a
-                    // sparse grid stream every neighbour
-                    if constexpr (D <= 4) {
-                        if (cn >= 16u * kWave && !cell_near<D>(gv, cc, active, qx, side, lim)) cn = 0;
                     }
                 }
                 const uint32_t incl = wave_incl_scan(cn);
@@ -280,6 +272,14 @@ __global__ __launch_bounds__(kBlock) void core_mark_kernel(GridView gv, const ui
         stream(false);
         if constexpr (kSplit) {
             if (active && ballot(later)) {
+                // the noise points of a sparse grid stream every neighbour, but a
+                // large grid counts only if an open query comes within eps of
+                // its cell; the rows are read again here, since kept through
+                // the stream they cost it registers
+                const double side = (double)I.eps / sqrt((double)I.d);
+                const double lim = (double)I.eps * (double)I.eps * (1.0 + 1e-9) + 1.0;
+                int32_t qx[D];
+                load_row<D>(gv.crd, (uint32_t)lane < nq ? st + qb + lane : st, qx);
                 auto slices = [&](uint64_t idx, uint32_t& cc) -> uint32_t {
                     cc = idx < e1 ? nei[idx] : 0u;
                     const uint32_t cn = idx < e1 ? gv.cell_start[cc + 1] - gv.cell_start[cc] : 0u;

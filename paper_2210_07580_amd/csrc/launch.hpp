@@ -316,9 +316,9 @@ struct CoreStats {
 // GPU: (grid, first query of the batch, neighbour grid, slice).
 constexpr uint32_t kSplitRows = 2048;
 // Mean points per grid from which core marking and the border search split:
-// the variant's registers cost where nothing is split (core marking at 161 and
-// 227 points per grid 99 -> 141 and 75 -> 104 us), and pay from about 300 (5-D at
-// 307 and 677 points per grid 201 -> 165 and 389 -> 165 us).
+// the variant's registers cost where little is split (3-D at 274 points per grid:
+// core marking 86 -> 92 us), and it pays from about 300 (3-D at 359 and 485 123 ->
+// 92 and 166 -> 88 us; 5-D at 307 and 677 201 -> 165 and 389 -> 165 us).
 constexpr int64_t kSplitMean = 256;
 constexpr unsigned kSplitBlocks = 2048;  // workgroups of the kernels that work off the tasks
 struct SplitQueue {
