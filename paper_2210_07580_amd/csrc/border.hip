@@ -325,7 +325,7 @@ template <int D, bool kWide>
 __global__ __launch_bounds__(kBlock) void border_tasks_kernel(GridView gv, CoreOut co,
                                                               const int32_t* __restrict__ cell_label, SplitQueue sq) {
     const int w = wave_id(), lane = lane_id();
-    const uint32_t count = min(*sq.count, sq.cap);
+    const uint32_t count = split_used(*sq.count, sq.cap);
     for (uint32_t i = blockIdx.x * kWavesPerBlock + w; i < count; i += gridDim.x * kWavesPerBlock) {
         const uint4 task = sq.tasks[i];
         const uint32_t c = uniform(task.x), qb = uniform(task.y), cc = uniform(task.z);

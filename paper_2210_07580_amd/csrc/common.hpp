@@ -396,15 +396,15 @@ __device__ __forceinline__ bool cell_near(const GridView& gv, uint32_t cc, uint6
     return near;
 }
 
-// Reserves `total` (uniform) tasks from *base on; if they do not fit, the slots
+// Reserves `total` (uniform) tasks from base on; if they do not fit, the slots
 // short of the end are marked empty and the caller does the work itself.
 __device__ __forceinline__ bool split_reserve(const SplitQueue& sq, uint32_t total, uint32_t& base) {
-    base = 0;
-    if (lane_id() == 0) base = atomicAdd(sq.count, total);
-    base = readlane(base, 0);
-    if (base <= sq.cap && total <= sq.cap - base) return true;
-    for (uint64_t at = (uint64_t)base + lane_id(); at < sq.cap && at < (uint64_t)base + total; at += kWave)
-        sq.tasks[at] = make_uint4(kNone, 0u, 0u, 0u);
+    SplitCount before = 0;
+    if (lane_id() == 0) before = atomicAdd(sq.count, (SplitCount)total);
+    before = uniform64(before);
+    base = (uint32_t)before;
+    if (split_fits(before, total, sq.cap)) return true;
+    for (SplitCount at = before + lane_id(); at < sq.cap; at += kWave) sq.tasks[at] = make_uint4(kNone, 0u, 0u, 0u);
     return false;
 }
 // Writes `want` (per lane) slices of neighbour cc as tasks from base on, which
@@ -415,7 +415,6 @@ __device__ __forceinline__ void split_write(const SplitQueue& sq, uint32_t& base
     for (uint32_t i = 0; i < want; ++i) sq.tasks[base + (incl - want) + i] = make_uint4(c, qb, cc, i);
     base += last_lane(incl);
 }
-__device__ __forceinline__ uint32_t split_slices(uint32_t rows) { return (rows + kSplitRows - 1) / kSplitRows; }
 // Whether this task was the last of grid c's (its results before are visible
 // to the wave then).  Called by a whole wave.
 __device__ __forceinline__ bool split_last(const SplitQueue& sq, uint32_t c) {

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(kBlock) void core_tasks_kernel(GridView gv, uint8_t
     constexpr int R = 2;
     __shared__ __align__(16) int32_t s_q[kWavesPerBlock][kWave * S];
     const int w = wave_id(), lane = lane_id();
-    const uint32_t count = min(*sq.count, sq.cap);
+    const uint32_t count = split_used(*sq.count, sq.cap);
     for (uint32_t i = blockIdx.x * kWavesPerBlock + w; i < count; i += gridDim.x * kWavesPerBlock) {
         const uint4 task = sq.tasks[i];
         const uint32_t c = uniform(task.x), qb = uniform(task.y), cc = uniform(task.z);

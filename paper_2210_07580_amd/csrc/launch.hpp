@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "gritdbscan.h"
+#include "split.hpp"
 
 namespace gd {
 
@@ -87,7 +88,7 @@ struct Header {
     uint32_t ncell;       // |Gs| over the batch
     uint32_t level_count[kMaxLevels];
     uint32_t counts[5];   // core points, core grids, max core points per grid, dense grids, tiny core grids
-    uint32_t split[2];    // tasks of core marking and of the border search (SplitQueue)
+    SplitCount split[2];  // tasks asked for by core marking and by the border search (SplitQueue)
     uint64_t nei_total;
 };
 
@@ -314,7 +315,6 @@ struct CoreStats {
 // Streams of a few sparse grids through neighbours of thousands of points,
 // split into tasks of kSplitRows rows that a second kernel spreads over the
 // GPU: (grid, first query of the batch, neighbour grid, slice).
-constexpr uint32_t kSplitRows = 2048;
 // Mean points per grid from which core marking and the border search split:
 // the variant's registers cost where little is split (3-D at 274 points per grid:
 // core marking 86 -> 92 us), and it pays from about 300 (3-D at 359 and 485 123 ->
@@ -324,7 +324,7 @@ constexpr unsigned kSplitBlocks = 2048;  // workgroups of the kernels that work 
 struct SplitQueue {
     uint4* tasks;
     uint32_t cap;
-    uint32_t* count;  // reserved so far (may pass cap: the reserver then streams by itself)
+    SplitCount* count;  // asked for so far (beyond cap the wave that asks streams by itself)
     uint32_t* left;   // per grid with tasks: how many are not done yet
     uint32_t* hits;   // core marking: hits of each point of a sparse grid so far
     uint64_t* best;   // border search: best (input index, label) of each non-core point so far
