@@ -1356,19 +1356,19 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
         const int pb = pack64_width(ctx, count);
         if (pb > 0 && kb + D * pb <= 64) p.key_bits = std::min(p.key_bits, 64 - D * pb);
     }
-    p.ncell = std::min<int64_t>(n, e.grids + e.grids / 16 + 1024);
+    p.runs = ctx->last_runs;
+    p.by_level = ctx->last_by_level;
+    const bool levels = p.runs || p.by_level;
+    p.ncell = planned_grids(n, e.grids, levels);
     p.nei = (uint64_t)e.neighbor_entries + (uint64_t)e.neighbor_entries / 16 + 4096;
     p.ncc = std::min<int64_t>(p.ncell, e.core_grids + e.core_grids / 16 + 256);
     p.max_core = std::min<int64_t>(std::min<int64_t>(n, kMaxCoreBits), ctx->last_max_core + ctx->last_max_core / 16 + 64);
     p.walk = ctx->last_walk;
-    p.runs = ctx->last_runs;
-    p.by_level = ctx->last_by_level;
     p.ordered = ctx->last_ordered;
-    const bool levels = p.runs || p.by_level;
     if (levels) {
         for (int k = 0; k < 2; ++k) p.ents[k] = ctx->last_ents[k] + ctx->last_ents[k] / 16 + 4096;
         for (int l = 0; l < kMaxLevels; ++l) {
-            p.nodes[l] = std::min<int64_t>(p.ncell, ctx->last_nodes[l] + ctx->last_nodes[l] / 16 + 1024);
+            p.nodes[l] = planned_nodes(p.ncell, ctx->last_nodes[l]);
             p.lanes[l] = ctx->last_lanes[l];
         }
     }

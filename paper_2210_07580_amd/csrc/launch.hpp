@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "gritdbscan.h"
+#include "plan.hpp"
 #include "split.hpp"
 
 namespace gd {
@@ -224,8 +225,6 @@ struct NodeLists {
 };
 // Places around a level-1 node that hold all its level-1 neighbours (windows of +-3 keys).
 constexpr int kNear = 7;
-// Entries hold a node above 6 bits.
-constexpr int64_t kMaxRunNodes = (int64_t)1 << 26;
 // Level l (2 .. D): list lengths and offsets, total into the header
 // (nei_total); then the lists, for l = D those of the grids.  nodes: nodes of level l (or an upper bound);
 // lanes: 8, 16 or 64 per node (by the length of the parents' lists).
