@@ -379,6 +379,15 @@ int gd_debug_neighbors(gd_ctx *ctx, uint64_t *offsets, uint32_t *neighbors);
 int gd_debug_core(gd_ctx *ctx, uint8_t *core_flags_sorted, int32_t *grid_label);
 
 /*
+ * gd_debug_limits: smaller limits for later calls on this context, so that
+ * a test reaches what happens beyond them (results stay the same).
+ *   split_slots     slots of the queue of split streams (core marking and the
+ *                   border search beside few large grids); -1 (default): as
+ *                   many as the workspace holds
+ */
+int gd_debug_limits(gd_ctx *ctx, int64_t split_slots);
+
+/*
  * gd_merge_test: FastMerging (Algorithm 5 with Pruning, Algorithm 4) on
  * caller-given point sets, one answer per pair: 1 iff MinDist(A, B) <= eps
  * (Theorem 2).

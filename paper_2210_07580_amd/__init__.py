@@ -62,7 +62,7 @@ class Instance(ctypes.Structure):
 _lib = None
 
 EXPORTS = ("gd_create", "gd_destroy", "dbscan", "dbscan_noalloc", "dbscan_batched", "gd_set_option", "gd_get_stats",
-           "gd_debug_grids", "gd_debug_neighbors", "gd_debug_core", "gd_merge_test",
+           "gd_debug_grids", "gd_debug_neighbors", "gd_debug_core", "gd_debug_limits", "gd_merge_test",
            "gd_get_phase_times", "gd_phase_name", "gd_set_proposal", "gd_proposal_harvest",
            "gd_mlp_train", "gd_mlp_grad", "gd_mlp_forward", "gd_last_error", "gd_status_string", "gd_autotune",
            "gd_set_tuning_file")
@@ -100,6 +100,8 @@ def load_library(path: str = LIB_PATH):
     lib.gd_debug_neighbors.restype = ctypes.c_int
     lib.gd_debug_core.argtypes = [vp, vp, vp]
     lib.gd_debug_core.restype = ctypes.c_int
+    lib.gd_debug_limits.argtypes = [vp, i64]
+    lib.gd_debug_limits.restype = ctypes.c_int
     lib.gd_merge_test.argtypes = [vp, vp, i64, i32, dbl, vp, i64, vp, vp, vp]
     lib.gd_merge_test.restype = ctypes.c_int
     lib.gd_get_phase_times.argtypes = [vp, vp, i32]
@@ -364,6 +366,10 @@ class Context:
         lab = np.empty(st["grids"], np.int32)
         self._check(lib.gd_debug_core(self._h, core.ctypes.data, lab.ctypes.data))
         return core, lab
+
+    def debug_limits(self, split_slots: int = -1):
+        """Smaller limits for later calls, for tests of what happens beyond them."""
+        self._check(load_library().gd_debug_limits(self._h, int(split_slots)))
 
     def merge_test(self, points_soa, pairs, eps, with_iterations: bool = False, stream=None):
         """FastMerging on pairs of point runs.  ``points_soa``: torch int32

@@ -113,6 +113,7 @@ struct gd_ctx {
     Inst* inst_host = nullptr;  // pinned
     int inst_cap = 0;
     int64_t ws_limit = 0;
+    int64_t split_slots = -1;      // gd_debug_limits: slots of the queue of split streams (-1: what fits)
     bool stats = false;
     bool ldf = true;               // LDF order (merge_order 1) or identifier order (0)
     bool bfs = false;              // the BFS order of Algorithm 6 (merge_order 2)
@@ -769,6 +770,9 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     // large grids: streams of thousands of points split into tasks (the queue
     // and its counts lie in arrays of the steps that follow)
     const bool split = n >= kSplitMean * std::max<int64_t>(ncell, 1);
+    auto split_slots = [&](int64_t fit) {
+        return (uint32_t)(ctx->split_slots < 0 ? fit : std::min(fit, ctx->split_slots));
+    };
     // offset order pays for itself through core marking's early exit only
     // when grids hold several points; sparse grids take walk order, and so do
     // more than 2^19 grids, whose ordered fill (scattered over the offset
@@ -1003,7 +1007,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     {
         SplitQueue sq{};
         sq.tasks = L.rank;
-        sq.cap = (uint32_t)n;
+        sq.cap = split_slots(n);
         sq.count = &Hd->split[0];
         sq.left = (uint32_t*)L.cell_label;
         sq.hits = L.list;
@@ -1143,7 +1147,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         SplitQueue sq{};
         sq.best = (uint64_t*)L.rank;
         sq.tasks = L.rank + (n + 1) / 2;
-        sq.cap = (uint32_t)(n / 2);
+        sq.cap = split_slots(n / 2);
         sq.count = &Hd->split[1];
         sq.left = L.root_min;
         GD_TRY(launch_output(g, co, L.nei_off, nei, rs, L.cell_label, wide, small_lanes, free_words,
@@ -1333,6 +1337,7 @@ std::vector<int64_t> batch_signature(const gd_ctx* ctx, int count) {
     sig.push_back(ctx->grid_lanes);
     sig.push_back(ctx->nei_mode);
     sig.push_back(ctx->nei_query);
+    sig.push_back(ctx->split_slots);
     sig.push_back(ctx->pack_rows ? (ctx->fuse_rows ? 1 : 2) : 0);
     for (int k = 0; k < count; ++k) {
         sig.push_back(ctx->inst_host[k].n);
@@ -1887,6 +1892,12 @@ int gd_debug_core(gd_ctx* ctx, uint8_t* core_flags_sorted, int32_t* grid_label) 
     int rc;
     if ((rc = copy_d2h(ctx, core_flags_sorted, ctx->last_core, ctx->last_n))) return rc;
     return copy_d2h(ctx, grid_label, ctx->last_cell_label, sizeof(int32_t) * ctx->last_ncell);
+}
+
+int gd_debug_limits(gd_ctx* ctx, int64_t split_slots) {
+    if (!ctx) return GD_EINVAL;
+    ctx->split_slots = split_slots;
+    return GD_OK;
 }
 
 int gd_merge_test(gd_ctx* ctx, const int32_t* points, int64_t m, int32_t d, double eps, const uint32_t* pairs,
