@@ -384,8 +384,11 @@ int gd_debug_core(gd_ctx *ctx, uint8_t *core_flags_sorted, int32_t *grid_label);
  *   split_slots     slots of the queue of split streams (core marking and the
  *                   border search beside few large grids); -1 (default): as
  *                   many as the workspace holds
+ *   device_bytes    bytes of device memory that the context's buffers may
+ *                   take before an allocation fails as hipMalloc does when
+ *                   the device is full; -1 (default): no limit
  */
-int gd_debug_limits(gd_ctx *ctx, int64_t split_slots);
+int gd_debug_limits(gd_ctx *ctx, int64_t split_slots, int64_t device_bytes);
 
 /*
  * gd_merge_test: FastMerging (Algorithm 5 with Pruning, Algorithm 4) on

@@ -100,7 +100,7 @@ def load_library(path: str = LIB_PATH):
     lib.gd_debug_neighbors.restype = ctypes.c_int
     lib.gd_debug_core.argtypes = [vp, vp, vp]
     lib.gd_debug_core.restype = ctypes.c_int
-    lib.gd_debug_limits.argtypes = [vp, i64]
+    lib.gd_debug_limits.argtypes = [vp, i64, i64]
     lib.gd_debug_limits.restype = ctypes.c_int
     lib.gd_merge_test.argtypes = [vp, vp, i64, i32, dbl, vp, i64, vp, vp, vp]
     lib.gd_merge_test.restype = ctypes.c_int
@@ -367,9 +367,9 @@ class Context:
         self._check(lib.gd_debug_core(self._h, core.ctypes.data, lab.ctypes.data))
         return core, lab
 
-    def debug_limits(self, split_slots: int = -1):
+    def debug_limits(self, split_slots: int = -1, device_bytes: int = -1):
         """Smaller limits for later calls, for tests of what happens beyond them."""
-        self._check(load_library().gd_debug_limits(self._h, int(split_slots)))
+        self._check(load_library().gd_debug_limits(self._h, int(split_slots), int(device_bytes)))
 
     def merge_test(self, points_soa, pairs, eps, with_iterations: bool = False, stream=None):
         """FastMerging on pairs of point runs.  ``points_soa``: torch int32

@@ -114,6 +114,7 @@ struct gd_ctx {
     int inst_cap = 0;
     int64_t ws_limit = 0;
     int64_t split_slots = -1;      // gd_debug_limits: slots of the queue of split streams (-1: what fits)
+    int64_t device_bytes = -1;     // and bytes that device allocations may take (-1: no limit)
     bool stats = false;
     bool ldf = true;               // LDF order (merge_order 1) or identifier order (0)
     bool bfs = false;              // the BFS order of Algorithm 6 (merge_order 2)
@@ -240,6 +241,16 @@ struct Carve {
     }
 };
 
+// hipMalloc for the context's buffers, within gd_debug_limits.
+hipError_t device_alloc(gd_ctx* ctx, void** p, size_t bytes) {
+    size_t held = 0;
+    for (const DevBuf* b : {&ctx->own.arena, &ctx->own.nei, &ctx->own.mid, &ctx->own.table, &ctx->own.sumbuf,
+                            &ctx->own.huge})
+        held += b->cap;
+    if (ctx->device_bytes >= 0 && held + bytes > (size_t)ctx->device_bytes) return hipErrorOutOfMemory;
+    return hipMalloc(p, bytes);
+}
+
 int grow(gd_ctx* ctx, DevBuf& b, size_t need, size_t other_held) {
     if (need <= b.cap) return GD_OK;
     if (ctx->bump_base) {
@@ -265,7 +276,7 @@ int grow(gd_ctx* ctx, DevBuf& b, size_t need, size_t other_held) {
     }
     const size_t sz = need + need / 8;  // some headroom for the next call
     ++ctx->generation;                  // a captured graph that used the old buffer is stale
-    if (hipMalloc(&b.p, sz) != hipSuccess) {
+    if (device_alloc(ctx, &b.p, sz) != hipSuccess) {
         (void)hipGetLastError();
         b.p = nullptr;
         return ctx->fail(GD_ENOMEM, "hipMalloc of %zu bytes failed", sz);
@@ -1252,24 +1263,27 @@ void drop_graph(gd_ctx* ctx) {
 
 int ensure_inst_capacity(gd_ctx* ctx, int count) {
     if (count <= ctx->inst_cap) return GD_OK;
-    (void)count_entries(ctx);  // the last call's counts read the table that goes
+    // the new tables first: without them the context, and what the last call
+    // left in it, stay as they are
+    const int cap = std::max(count, 16);
+    Inst *dev = nullptr, *host = nullptr;
+    if (device_alloc(ctx, (void**)&dev, sizeof(Inst) * cap) != hipSuccess ||
+        hipHostMalloc(&host, sizeof(Inst) * cap, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        if (dev) (void)hipFree(dev);
+        return ctx->fail(GD_ENOMEM, "instance table allocation failed");
+    }
+    // the views of the last call read the table that goes; a captured graph
+    // reads it through the old pointers (its copy node from the pinned host
+    // table, every kernel from the device table): it must never run again
+    ctx->have_last = false;
     ctx->lists = gd_ctx::Lists{};
-    // a captured graph reads the instance table through the old pointers
-    // (its copy node from the pinned host table, every kernel from the
-    // device table): it must never run again
     drop_graph(ctx);
     ++ctx->generation;
     if (ctx->inst_dev) (void)hipFree(ctx->inst_dev);
     if (ctx->inst_host) (void)hipHostFree(ctx->inst_host);
-    ctx->inst_dev = nullptr;
-    ctx->inst_host = nullptr;
-    ctx->inst_cap = 0;
-    const int cap = std::max(count, 16);
-    if (hipMalloc(&ctx->inst_dev, sizeof(Inst) * cap) != hipSuccess ||
-        hipHostMalloc(&ctx->inst_host, sizeof(Inst) * cap, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return ctx->fail(GD_ENOMEM, "instance table allocation failed");
-    }
+    ctx->inst_dev = dev;
+    ctx->inst_host = host;
     ctx->inst_cap = cap;
     return GD_OK;
 }
@@ -1894,9 +1908,10 @@ int gd_debug_core(gd_ctx* ctx, uint8_t* core_flags_sorted, int32_t* grid_label) 
     return copy_d2h(ctx, grid_label, ctx->last_cell_label, sizeof(int32_t) * ctx->last_ncell);
 }
 
-int gd_debug_limits(gd_ctx* ctx, int64_t split_slots) {
+int gd_debug_limits(gd_ctx* ctx, int64_t split_slots, int64_t device_bytes) {
     if (!ctx) return GD_EINVAL;
     ctx->split_slots = split_slots;
+    ctx->device_bytes = device_bytes;
     return GD_OK;
 }
 

@@ -43,4 +43,4 @@ def test_full_queue(G, d, slots, minpts, eps):
 
 
 def test_limits_need_a_context(G):
-    assert G.load_library().gd_debug_limits(None, 0) == G.GD_EINVAL
+    assert G.load_library().gd_debug_limits(None, 0, -1) == G.GD_EINVAL
