@@ -42,7 +42,7 @@ struct DevBuf {
 struct Bufs {
     DevBuf arena;   // everything sized by the batch's points and dimension
     DevBuf nei;     // the neighbour lists (or the families' node lists), sized by their total
-    DevBuf mid;     // node lists of every other tree level while they are built
+    DevBuf mid;     // node lists of every other tree level while they are built (unbounded workspaces)
     DevBuf table;   // identifier -> label hash table of the output pass
     DevBuf sumbuf;  // CellSummary per grid (learned proposal)
     DevBuf huge;    // queue and device-memory bitmaps for core sets beyond the LDS bitmaps
@@ -114,6 +114,7 @@ struct gd_ctx {
     int inst_cap = 0;
     int64_t ws_limit = 0;
     int64_t split_slots = -1;      // gd_debug_limits: slots of the queue of split streams (-1: what fits)
+    bool mid_used = false;         // own.mid holds lists that are still needed
     int64_t device_bytes = -1;     // and bytes that device allocations may take (-1: no limit)
     bool stats = false;
     bool ldf = true;               // LDF order (merge_order 1) or identifier order (0)
@@ -241,15 +242,43 @@ struct Carve {
     }
 };
 
-// hipMalloc for the context's buffers, within gd_debug_limits.
-hipError_t device_alloc(gd_ctx* ctx, void** p, size_t bytes) {
-    size_t held = 0;
-    for (const DevBuf* b : {&ctx->own.arena, &ctx->own.nei, &ctx->own.mid, &ctx->own.table, &ctx->own.sumbuf,
-                            &ctx->own.huge})
-        held += b->cap;
-    if (ctx->device_bytes >= 0 && held + bytes > (size_t)ctx->device_bytes) return hipErrorOutOfMemory;
-    return hipMalloc(p, bytes);
+void release(gd_ctx* ctx, DevBuf& b) {
+    if (!b.p) return;
+    (void)hipFree(b.p);
+    b = DevBuf{};
+    ++ctx->generation;
 }
+
+// hipMalloc for the context's buffers, within gd_debug_limits.  On a full
+// device the node lists that an earlier step left behind go first.
+hipError_t device_alloc(gd_ctx* ctx, void** p, size_t bytes) {
+    auto held = [&]() {
+        size_t sum = 0;
+        for (const DevBuf* b : {&ctx->own.arena, &ctx->own.nei, &ctx->own.mid, &ctx->own.table, &ctx->own.sumbuf,
+                                &ctx->own.huge})
+            sum += b->cap;
+        return sum;
+    };
+    auto allocate = [&]() {
+        if (ctx->device_bytes >= 0 && held() + bytes > (size_t)ctx->device_bytes) return hipErrorOutOfMemory;
+        return hipMalloc(p, bytes);
+    };
+    hipError_t e = allocate();
+    if (e != hipSuccess && ctx->own.mid.p && !ctx->mid_used) {
+        (void)hipGetLastError();
+        release(ctx, ctx->own.mid);
+        e = allocate();
+    }
+    return e;
+}
+
+// While node lists are built, or a run that builds them is captured.
+struct MidUse {
+    gd_ctx* ctx;
+    const bool before;
+    explicit MidUse(gd_ctx* c) : ctx(c), before(c->mid_used) { ctx->mid_used = true; }
+    ~MidUse() { ctx->mid_used = before; }
+};
 
 int grow(gd_ctx* ctx, DevBuf& b, size_t need, size_t other_held) {
     if (need <= b.cap) return GD_OK;
@@ -283,13 +312,6 @@ int grow(gd_ctx* ctx, DevBuf& b, size_t need, size_t other_held) {
     }
     b.cap = sz;
     return GD_OK;
-}
-
-void release(gd_ctx* ctx, DevBuf& b) {
-    if (!b.p) return;
-    (void)hipFree(b.p);
-    b = DevBuf{};
-    ++ctx->generation;
 }
 
 // The context's own stream (graph replays, counts and lists asked for after
@@ -873,17 +895,11 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         nei_total = plan ? plan->nei : H->nei_total;
         if (!plan && (rc2 = grow(ctx, ctx->cur->nei, (size_t)std::max<uint64_t>(nei_total, 1) * sizeof(uint32_t),
                                  ctx->cur->arena.cap))) {
-            // the node lists of an earlier call are in the way of these
-            if (rc2 == GD_ENOMEM && ctx->cur->mid.p) {
-                release(ctx, ctx->cur->mid);
-                ctx->err.clear();
-                rc2 = grow(ctx, ctx->cur->nei, (size_t)nei_total * sizeof(uint32_t), ctx->cur->arena.cap);
-            }
             if (fallback && rc2 == GD_ENOMEM) {
                 ctx->err.clear();
                 return kListsDoNotFit;
             }
-            if (rc2) return rc2;
+            return rc2;
         }
         nei = (uint32_t*)ctx->cur->nei.p;
         ctx->mark(P_NEI_FILL, 0);
@@ -900,6 +916,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     uint2* const grid_up = D == 2 ? L.nei_up : (uint2*)L.off_counts;
     double visits = kNear;  // entries per list of the level before (level 1: places around a node)
     auto build_levels = [&](int last) -> int {
+        MidUse use(ctx);
         NodeLists nl{};
         for (int l = 1; l < D; ++l) nl.par[l] = tpar[l];
         nl.excl = L.level_excl + (int64_t)(D - 1) * (g.ncell + 1);
@@ -1402,6 +1419,7 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
         }
     } inval{ctx, gen0};
     const int fin = (p.runs ? D - 1 : D) & 1;
+    MidUse use(ctx);
     if (grow(ctx, ctx->cur->nei, (size_t)std::max<uint64_t>(levels ? p.ents[fin] : p.nei, 1) * sizeof(uint32_t),
              ctx->cur->arena.cap) ||
         (levels && grow(ctx, ctx->cur->mid, (size_t)p.ents[1 - fin] * sizeof(uint32_t), ctx->cur->arena.cap)) ||
@@ -1844,6 +1862,10 @@ int gd_set_option(gd_ctx* ctx, int option, int64_t value) {
         case GD_OPT_WORKSPACE_LIMIT:
             if (value < 0) return ctx->fail(GD_EINVAL, "workspace limit must be >= 0");
             ctx->ws_limit = value;
+            if (value > 0) {  // bounded calls build no node lists
+                DeviceGuard guard(ctx->device);
+                release(ctx, ctx->own.mid);
+            }
             return GD_OK;
         default: return ctx->fail(GD_EINVAL, "unknown option %d", option);
     }

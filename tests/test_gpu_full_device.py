@@ -59,3 +59,48 @@ def test_batch_table_that_does_not_fit(G, d):
         assert np.array_equal(got[0].cpu().numpy(), lab) and np.array_equal(got[1].cpu().numpy(), core)
     ctx.close()
     ref.close()
+
+
+def node_list_call(ctx, n=20_000):
+    # six dimensions: the lists of the level above the families' own take megabytes
+    check(ctx, uniform(6, n, 6, 1000), 200, 5)
+
+
+def test_a_workspace_limit_gives_the_node_lists_back(G):
+    ctx = G.Context(0)
+    node_list_call(ctx)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    ctx.set_option(G.GD_OPT_WORKSPACE_LIMIT, 1 << 30)
+    assert torch.cuda.mem_get_info()[0] >= free + (1 << 20)
+    node_list_call(ctx)
+    ctx.set_option(G.GD_OPT_WORKSPACE_LIMIT, 0)
+    node_list_call(ctx)
+    ctx.close()
+
+
+def test_node_lists_make_room_for_a_later_call(G):
+    # what a fresh context can do with so much memory, one that built node
+    # lists before (smaller than the later call's own lists) can do too
+    x = uniform(2, 400_000, 2, 30_000)
+
+    def fits(limit, before):
+        ctx = G.Context(0)
+        if before:
+            node_list_call(ctx, 4000)
+        ctx.debug_limits(device_bytes=limit)
+        try:
+            check(ctx, x, 100, 4)
+            return True
+        except G.GDError as e:
+            assert e.status == G.GD_ENOMEM
+            return False
+        finally:
+            ctx.close()
+
+    lo, hi = 1 << 20, 1 << 29
+    assert not fits(lo, False) and fits(hi, False)
+    while hi - lo > 1 << 16:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if fits(mid, False) else (mid, hi)
+    assert fits(hi, True)
