@@ -997,6 +997,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
             rsrc.ent = nl.ent[fin];
             rsrc.near = nl.near;
             rsrc.families = nodes[D - 1];
+            rsrc.long_families = plan || H->long_families;
         }
         return GD_OK;
     };

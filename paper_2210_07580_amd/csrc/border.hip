@@ -548,15 +548,34 @@ __global__ __launch_bounds__(kBlock) void output_kernel(GridView gv, CoreOut co,
     }
 }
 
-// Smallest core index of each family's grids (kNone: no core point).
+// Smallest core index of each family's grids (kNone: no core point).  A thread
+// looks through the first kFamilyGrids of its family, family_min_rest_kernel
+// folds the others in.
 __global__ __launch_bounds__(kBlock) void family_min_kernel(const uint32_t* families, const uint32_t* __restrict__ child,
                                                             const uint32_t* __restrict__ cell_min_core,
                                                             uint32_t* __restrict__ family_min) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= (int64_t)*families) return;
+    const uint32_t c0 = child[p], c1 = min(child[p + 1], c0 + kFamilyGrids);
     uint32_t m = kNone;
-    for (uint32_t c = child[p]; c < child[p + 1]; ++c) m = min(m, cell_min_core[c]);
+    for (uint32_t c = c0; c < c1; ++c) m = min(m, cell_min_core[c]);
     family_min[p] = m;
+}
+
+__global__ __launch_bounds__(kBlock) void family_min_rest_kernel(const uint32_t* ncell, const uint32_t* __restrict__ excl,
+                                                                 const uint32_t* __restrict__ child,
+                                                                 const uint32_t* __restrict__ cell_min_core,
+                                                                 uint32_t* family_min) {
+    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    uint32_t f = 0, m = kNone;
+    if (c < (int64_t)*ncell && family_rest(excl, child, (uint32_t)c, f)) m = cell_min_core[c];
+    for (uint64_t todo = ballot(m != kNone); todo;) {
+        const uint32_t p = readlane(f, ffs64(todo));
+        const bool same = m != kNone && f == p;
+        const uint32_t least = wave_min_u32(same ? m : kNone);
+        todo &= ~ballot(same);
+        if (lane_id() == 0) atomicMin(&family_min[p], least);
+    }
 }
 
 // Border and noise points with neighbours as runs (runs.hpp), a wave for the
@@ -704,6 +723,9 @@ hipError_t launch_output(const GridView& g, const CoreOut& c, const uint64_t* ne
         if (wide) return hipErrorInvalidValue;
         family_min_kernel<<<dim3(grid_for(runs->families)), dim3(kBlock), 0, st>>>(
             runs->t.level_count + (g.D - 1), runs->t.child[g.D - 1], c.cell_min_core, family_min);
+        if (runs->long_families)
+            family_min_rest_kernel<<<dim3(grid_for(g.ncell)), dim3(kBlock), 0, st>>>(
+                g.ncell_dev, runs->excl, runs->t.child[g.D - 1], c.cell_min_core, family_min);
         GD_DISPATCH_D(g.D, ({
                           if constexpr (D >= kMinRunD) {
                               if (g.ncell >= kBorderGroupMinGrids)

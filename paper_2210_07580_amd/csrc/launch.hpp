@@ -89,6 +89,8 @@ struct Header {
     uint32_t ncell;       // |Gs| over the batch
     uint32_t level_count[kMaxLevels];
     uint32_t counts[5];   // core points, core grids, max core points per grid, dense grids, tiny core grids
+    uint32_t long_families; // a level-(D-1) node has more than kFamilyGrids grids
+    uint32_t pad;
     SplitCount split[2];  // tasks asked for by core marking and by the border search (SplitQueue)
     uint64_t nei_total;
 };
@@ -203,7 +205,7 @@ hipError_t launch_cells(const Batch& b, const K* skeys, uint32_t* partial, uint3
 // Grid tree levels over the sorted grids.  level_excl: D x (ncell+1) scratch;
 // partial: scan scratch of 64-bit words (passed as the u32 view).
 // tpar (or nullptr): per level 1 .. D-1, where each node's parent (its index
-// in the level above) goes.
+// in the level above) goes; then the header's long_families is set, too.
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
                        uint32_t* const* tchild, uint32_t* const* tpar, hipStream_t st);
 
@@ -241,7 +243,11 @@ struct RunSource {
     const uint32_t* ent;
     const uint32_t* near;   // entries of p's list that touch, listed first
     int64_t families;       // nodes of level D-1 (or an upper bound)
+    bool long_families;     // one may have more than kFamilyGrids grids
 };
+// Grids of a family that the thread or wave of the family takes; those behind
+// them are spread over others.
+constexpr uint32_t kFamilyGrids = 64;
 
 // ---- neighbors.hip (Algorithm 3)
 // The query that produces the lists: the grid tree with offset-ordered lists

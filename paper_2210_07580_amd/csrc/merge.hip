@@ -197,6 +197,10 @@ __global__ __launch_bounds__(kBlock) void merge_small_kernel(GridView gv, CoreOu
 // dozen dependent loads, and one family seldom has more than a few.  A lane
 // skips a pair of grids already in one set and decides the others by their
 // distances (FastMerging's answer, Theorem 2).
+// A family may be as long as the data are wide: what one thread or wave does for
+// a family covers its first kFamilyGrids grids, and where a longer family exists
+// further waves take the others, 64 grids each (a call of 16,384 grids on one
+// line in five dimensions: 23.1 -> 0.44 ms; 128 lines of 1,024 grids in seven 6.0 -> 1.2).
 // 10M 5-D points: 33.2 -> 10.9 ms for the tiny sets (2.9 + 3.0 + 4.9 ms for the
 // three phases; a first phase over all touching grids and none in between took
 // 13.8, one over faces and then everything 24.7 ms).  Bound by the latency of
@@ -211,8 +215,9 @@ __global__ __launch_bounds__(kBlock) void family_root_kernel(const uint32_t* fam
                                                              uint32_t* __restrict__ family_root) {
     const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (p >= (int64_t)*families) return;
+    const uint32_t c0 = child[p], c1 = min(child[p + 1], c0 + kFamilyGrids);
     uint32_t root = kFamilyEmpty;
-    for (uint32_t c = child[p]; c < child[p + 1] && root != kFamilyMixed; ++c) {
+    for (uint32_t c = c0; c < c1 && root != kFamilyMixed; ++c) {
         const uint4 q = rank[c];
         if (q.x == kNone || q.z > kSmallSet) continue;
         const uint32_t r = uf_find(parent, c);
@@ -221,19 +226,44 @@ __global__ __launch_bounds__(kBlock) void family_root_kernel(const uint32_t* fam
     family_root[p] = root;
 }
 
+// The grids behind the first kFamilyGrids of their family, folded in.
+__global__ __launch_bounds__(kBlock) void family_root_rest_kernel(const uint32_t* ncell, const uint32_t* __restrict__ excl,
+                                                                  const uint32_t* __restrict__ child,
+                                                                  const uint4* __restrict__ rank, uint32_t* parent,
+                                                                  uint32_t* family_root) {
+    const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    uint32_t f = 0, root = kFamilyEmpty;
+    if (c < (int64_t)*ncell && family_rest(excl, child, (uint32_t)c, f)) {
+        const uint4 q = rank[c];
+        if (q.x != kNone && q.z <= kSmallSet) root = uf_find(parent, (uint32_t)c);
+    }
+    for (uint64_t todo = ballot(root != kFamilyEmpty); todo;) {
+        const uint32_t p = readlane(f, ffs64(todo)), first = readlane(root, ffs64(todo));
+        const uint64_t same = ballot(root != kFamilyEmpty && f == p);
+        const uint32_t mark = ballot(root != first) & same ? kFamilyMixed : first;
+        todo &= ~same;
+        if (lane_id() == 0) {
+            const uint32_t old = atomicCAS(&family_root[p], kFamilyEmpty, mark);
+            if (old != kFamilyEmpty && old != mark) store_rel(&family_root[p], kFamilyMixed);
+        }
+    }
+}
+
 template <int D, int kPhase>
 __global__ __launch_bounds__(kBlock) void merge_family_kernel(GridView gv, CoreOut co, RunSource rs,
                                                               const uint4* __restrict__ rank,
                                                               const uint32_t* __restrict__ family_root,
-                                                              uint32_t* parent) {
+                                                              uint32_t* parent, int64_t family_waves) {
     __shared__ uint2 queue[kWavesPerBlock][2 * kWave];  // (grid, entry)
     const int w = wave_id(), lane = lane_id();
     const uint32_t* __restrict__ child = rs.t.child[D - 1];
     const int32_t* __restrict__ key = rs.t.key[D];
     const int64_t families = rs.t.level_count[D - 1];
-    const int64_t f0 = (xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w) * kFamilies;
+    const int64_t wave = xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w;
+    const int64_t f0 = wave * kFamilies;
     const int64_t f1 = min(f0 + kFamilies, families);
-    if (f0 >= f1) return;
+    const int64_t g0 = (wave - family_waves) * kWave;  // the waves behind: grids that are not their family's first
+    if (wave < family_waves ? f0 >= f1 : g0 >= (int64_t)*gv.ncell_dev) return;
     // Every load that does not need an earlier one's result is issued ahead of
     // its use: the pair is bound by the length of its chain of loads.
     auto pair = [&](uint32_t a, uint32_t v) {
@@ -301,6 +331,61 @@ __global__ __launch_bounds__(kBlock) void merge_family_kernel(GridView gv, CoreO
         queue[w][lane] = nx;
         held = held > (uint32_t)kWave ? held - kWave : 0u;
     };
+    auto record = [&](uint32_t c) {  // rank and size of grid c's core set
+        const uint4 q = rank[c];
+        return make_uint2(q.x, q.z);
+    };
+    // the grids cb + i of family p (bits i of `grids`) with its entries [e0, e1),
+    // of which v_first are the first 64, one per lane; rp: the family's mark
+    auto serve = [&](uint32_t p, uint32_t cb, uint64_t grids, uint64_t e0, uint64_t e1, uint32_t v_first,
+                     uint32_t rp) {
+        for (uint64_t e = e0; e < e1; e += kWave) {
+            bool keep = false;
+            uint32_t v = v_first;
+            if (e + lane < e1) {
+                if (e != e0) v = rs.ent[e + lane];
+                const uint32_t b = entry_node(v);
+                if (b >= p) {
+                    keep = kPhase == kPhaseAll || entry_touch(v) <= kPhase;
+                    if (kPhase != kPhaseFace && keep) {
+                        const uint32_t rb = family_root[b];
+                        keep = rb != kFamilyEmpty && (rb == kFamilyMixed || rb != rp);
+                        // two marked families: their sets may have been joined since
+                        if (keep && rb != kFamilyMixed && rp != kFamilyMixed)
+                            keep = uf_peek(parent, rp) != uf_peek(parent, rb);
+                    }
+                }
+            }
+            const uint64_t m = ballot(keep);
+            if (!m) continue;
+            const uint32_t at = (uint32_t)popc64(m & lanemask_lt());
+            for (uint64_t g = grids; g; g &= g - 1ull) {
+                if (keep) queue[w][held + at] = make_uint2(cb + ffs64(g), v);
+                held += (uint32_t)popc64(m);
+                if (held >= (uint32_t)kWave) drain();
+            }
+        }
+    };
+    if (wave >= family_waves) {
+        static_assert(kFamilyGrids == kWave, "the family's own wave takes a record per lane");
+        const int64_t c = g0 + lane;
+        uint32_t f = 0;
+        bool mine = false;
+        if (c < (int64_t)*gv.ncell_dev) mine = family_rest(rs.excl, child, (uint32_t)c, f);
+        if (!ballot(mine)) return;
+        const uint2 q = mine ? record((uint32_t)c) : make_uint2(kNone, 0u);
+        mine = q.x != kNone && q.y <= kSmallSet;
+        for (uint64_t todo = ballot(mine); todo;) {
+            const uint32_t p = readlane(f, ffs64(todo));
+            const uint64_t grids = ballot(mine && f == p);
+            todo &= ~grids;
+            const uint64_t e0 = rs.off[p], e1 = kPhase == kPhaseAll ? rs.off[p + 1] : e0 + rs.near[p];
+            serve(p, (uint32_t)g0, grids, e0, e1, e0 + lane < e1 ? rs.ent[e0 + lane] : 0u,
+                  kPhase == kPhaseFace ? kFamilyMixed : family_root[p]);
+        }
+        if (held) drain();
+        return;
+    }
     // lane i holds family f0 + i: its grids, its entries of this phase, its mark
     const int nf = (int)(f1 - f0);
     uint32_t fc0 = 0, fc1 = 0, froot = 0;
@@ -320,10 +405,6 @@ __global__ __launch_bounds__(kBlock) void merge_family_kernel(GridView gv, CoreO
     // before is worked on
     uint32_t v_next = 0;
     uint2 q_next = make_uint2(kNone, 0u);
-    auto record = [&](uint32_t c) {  // rank and size of grid c's core set
-        const uint4 q = rank[c];
-        return make_uint2(q.x, q.z);
-    };
     auto prefetch = [&](int i) {
         const uint64_t e = lane64(fe0, i) + lane;
         const uint32_t c = readlane(fc0, i) + lane;
@@ -338,40 +419,8 @@ __global__ __launch_bounds__(kBlock) void merge_family_kernel(GridView gv, CoreO
         const uint32_t p = (uint32_t)(f0 + i);
         const uint32_t rp = readlane(froot, i);
         if (kPhase != kPhaseFace && rp == kFamilyEmpty) continue;
-        const uint32_t c0 = readlane(fc0, i), c1 = readlane(fc1, i);
-        const uint64_t e0 = lane64(fe0, i), e1 = lane64(fe1, i);
-        for (uint32_t cb = c0; cb < c1; cb += kWave) {  // the family's grids, 64 at a time
-            uint2 q = q_first;
-            if (cb != c0) q = cb + lane < c1 ? record(cb + lane) : make_uint2(kNone, 0u);
-            const uint64_t grids = ballot(q.x != kNone && q.y <= kSmallSet);
-            if (!grids) continue;
-            for (uint64_t e = e0; e < e1; e += kWave) {
-                bool keep = false;
-                uint32_t v = v_first;
-                if (e + lane < e1) {
-                    if (e != e0) v = rs.ent[e + lane];
-                    const uint32_t b = entry_node(v);
-                    if (b >= p) {
-                        keep = kPhase == kPhaseAll || entry_touch(v) <= kPhase;
-                        if (kPhase != kPhaseFace && keep) {
-                            const uint32_t rb = family_root[b];
-                            keep = rb != kFamilyEmpty && (rb == kFamilyMixed || rb != rp);
-                            // two marked families: their sets may have been joined since
-                            if (keep && rb != kFamilyMixed && rp != kFamilyMixed)
-                                keep = uf_peek(parent, rp) != uf_peek(parent, rb);
-                        }
-                    }
-                }
-                const uint64_t m = ballot(keep);
-                if (!m) continue;
-                const uint32_t at = (uint32_t)popc64(m & lanemask_lt());
-                for (uint64_t g = grids; g; g &= g - 1ull) {
-                    if (keep) queue[w][held + at] = make_uint2(cb + ffs64(g), v);
-                    held += (uint32_t)popc64(m);
-                    if (held >= (uint32_t)kWave) drain();
-                }
-            }
-        }
+        const uint64_t grids = ballot(q_first.x != kNone && q_first.y <= kSmallSet);
+        if (grids) serve(p, readlane(fc0, i), grids, lane64(fe0, i), lane64(fe1, i), v_first, rp);
     }
     if (held) drain();
 }
@@ -638,22 +687,28 @@ hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei
         const int64_t per_block = (int64_t)kWavesPerBlock * (kWave / S);
         const dim3 blocks = grid_of((s1 + per_block - 1) / per_block), threads(kBlock);
         if (runs) {
-            const dim3 fam = grid_of((runs->families + kWavesPerBlock * kFamilies - 1) / (kWavesPerBlock * kFamilies));
+            const int64_t per_block = (int64_t)kWavesPerBlock * kFamilies;
+            const int64_t family_waves = (runs->families + per_block - 1) / per_block * kWavesPerBlock;
+            const int64_t rest = runs->long_families ? grid_for(g.ncell, kWavesPerBlock * kWave) : 0;
+            const dim3 fam = grid_of(family_waves / kWavesPerBlock + rest);
             auto mark = [&](int D) {
                 family_root_kernel<<<dim3(grid_for(runs->families)), threads, 0, st>>>(
                     runs->t.level_count + (D - 1), runs->t.child[D - 1], rank, parent, family_root);
+                if (rest)
+                    family_root_rest_kernel<<<dim3(grid_for(g.ncell)), threads, 0, st>>>(
+                        g.ncell_dev, runs->excl, runs->t.child[D - 1], rank, parent, family_root);
             };
             auto phases = [&]() -> hipError_t {
                 GD_DISPATCH_D(g.D, ({
                                   if constexpr (D >= kMinRunD) {
-                                      merge_family_kernel<D, kPhaseFace>
-                                          <<<fam, threads, 0, st>>>(g, c, *runs, rank, family_root, parent);
+                                      merge_family_kernel<D, kPhaseFace><<<fam, threads, 0, st>>>(
+                                          g, c, *runs, rank, family_root, parent, family_waves);
                                       mark(D);
-                                      merge_family_kernel<D, kPhaseEdge>
-                                          <<<fam, threads, 0, st>>>(g, c, *runs, rank, family_root, parent);
+                                      merge_family_kernel<D, kPhaseEdge><<<fam, threads, 0, st>>>(
+                                          g, c, *runs, rank, family_root, parent, family_waves);
                                       mark(D);
-                                      merge_family_kernel<D, kPhaseAll>
-                                          <<<fam, threads, 0, st>>>(g, c, *runs, rank, family_root, parent);
+                                      merge_family_kernel<D, kPhaseAll><<<fam, threads, 0, st>>>(
+                                          g, c, *runs, rank, family_root, parent, family_waves);
                                   }
                               }));
                 return hipGetLastError();

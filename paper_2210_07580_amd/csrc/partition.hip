@@ -848,6 +848,7 @@ struct TreeBuild {
     uint32_t* child[kMaxLevels];
     const uint32_t* excl[kMaxLevels];  // per level: nodes before grid c (c in [0, ncell])
     uint32_t* par[kMaxLevels];         // per level: each node's parent (nullptr: not kept)
+    uint32_t* long_families;           // set where a node of the last of these levels has many grids
 };
 
 __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict__ ck, int64_t stride,
@@ -859,7 +860,12 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
         if (c == ncell || tb.excl[l][c + 1] != tb.excl[l][c]) {
             const uint32_t a = tb.excl[l][c];
             if (c < ncell) tb.key[l][a] = ck[(int64_t)l * stride + c];
-            if (c < ncell && l > 0 && tb.par[l]) tb.par[l][a] = tb.excl[l - 1][c + 1] - 1;
+            if (c < ncell && l > 0 && tb.par[l]) {
+                tb.par[l][a] = tb.excl[l - 1][c + 1] - 1;
+                // the node's grids start here: does it hold the one kFamilyGrids on?
+                if (l + 2 == levels && c + kFamilyGrids < ncell && tb.excl[l][c + kFamilyGrids + 1] == a + 1)
+                    store_rel(tb.long_families, 1u);
+            }
             // children: the level-(l+1) node that starts at grid c; the last level's nodes are the grids
             tb.child[l][a] = (l + 2 < levels) ? tb.excl[l + 1][c] : (uint32_t)c;
         }
@@ -871,6 +877,7 @@ hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partia
     const int levels = g.D + 1;
     uint32_t* level_count = g.b.hdr->level_count;
     TreeBuild tb{};
+    tb.long_families = &g.b.hdr->long_families;
     for (int l = 0; l + 1 < levels; ++l) {
         tb.key[l] = tkey[l];
         tb.child[l] = tchild[l];

@@ -72,6 +72,13 @@ __device__ __forceinline__ uint32_t group_sum_scan(uint32_t v) {
     }
 }
 
+// Whether grid c lies behind the first kFamilyGrids of its family f.
+__device__ __forceinline__ bool family_rest(const uint32_t* __restrict__ excl, const uint32_t* __restrict__ child,
+                                            uint32_t c, uint32_t& f) {
+    f = excl[c + 1] - 1;
+    return c - child[f] >= kFamilyGrids;
+}
+
 struct __attribute__((packed, aligned(4))) Words2 {
     uint32_t v[2];
 };

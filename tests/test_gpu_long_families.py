@@ -1,0 +1,95 @@
+"""Data that are long in their last dimension: families of the grid tree (grids
+that share all keys but the last) around the 64 grids that one thread or wave
+takes and far beyond, eager and replayed, against the oracle; and their cost."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def G():
+    import paper_2210_07580_amd as G
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return G
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda()
+
+
+def lines(seed, d, length, rows, per, gaps):
+    """`rows` lines of `length` grids of side 50 with up to `per` points each, a
+    fifth of the grids of every other line left empty where gaps are asked for."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for r in range(rows):
+        at = np.arange(length)
+        if gaps and r % 2:
+            at = at[rng.random(length) < 0.8]
+        at = np.repeat(at, rng.integers(1, per + 1, size=len(at)))
+        x = rng.random((len(at), d)) * 49
+        x[:, 0] += 50 * (r % 5)
+        x[:, 1] += 50 * (r // 5)
+        x[:, -1] += 50 * at
+        out.append(x)
+    x = np.floor(np.concatenate(out)).astype(np.int32)
+    x = np.concatenate([np.zeros((1, d), np.int32), x])
+    return x[rng.permutation(len(x))]
+
+
+@pytest.mark.parametrize("length", [63, 64, 65, 128, 129, 700])
+@pytest.mark.parametrize("d,rows,per,minpts,gaps", [(4, 1, 2, 3, False), (4, 12, 3, 5, True), (5, 7, 12, 9, True),
+                                                    (8, 3, 2, 2, True), (6, 9, 1, 4, True)])
+def test_lines(G, length, d, rows, per, minpts, gaps):
+    print(f"case d={d} rows={rows} length={length}", flush=True)
+    x = lines(length + d, d, length, rows, per, gaps)
+    eps = int(50 * np.sqrt(d))
+    want = oracle.dbscan(x, eps, minpts)
+    ctx = G.Context(0)
+    ctx.set_option(G.GD_OPT_GRAPH, 2)
+    for call in range(3):
+        lab, core = ctx.dbscan(dev(x), eps, minpts)
+        assert np.array_equal(core.cpu().numpy(), want[1]), f"call {call}"
+        assert np.array_equal(lab.cpu().numpy(), want[0]), f"call {call}"
+    assert ctx.stats()["graph_replays"] == 1
+    ctx.close()
+
+
+def test_a_replay_meets_longer_families_than_the_call_before(G):
+    d, eps = 5, int(50 * np.sqrt(5))
+    ctx = G.Context(0)
+    ctx.set_option(G.GD_OPT_GRAPH, 2)
+    short = lines(1, d, 40, 20, 1, False)
+    long = lines(1, d, 400, 2, 1, False)[:len(short)]
+    for x in (short, short, long, long, short):
+        want = oracle.dbscan(x, eps, 3)
+        lab, core = ctx.dbscan(dev(x), eps, 3)
+        assert np.array_equal(core.cpu().numpy(), want[1]) and np.array_equal(lab.cpu().numpy(), want[0])
+    ctx.close()
+
+
+def test_one_long_line_costs_no_more_than_its_points(G):
+    # 16,000 grids in one family: one thread or wave after another grid took
+    # 57 times what the lists per grid take (which this allows ten times)
+    x = dev(lines(2, 5, 16_000, 1, 2, False))
+    best = {}
+    for mode in (0, 1):
+        ctx = G.Context(0)
+        ctx.set_option(G.GD_OPT_NEIGHBOR_MODE, mode)
+        for call in range(6):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            ctx.dbscan(x, 111, 3)
+            torch.cuda.synchronize()
+            if call:
+                best[mode] = min(best.get(mode, 1e9), time.perf_counter() - t)
+        ctx.close()
+    assert best[0] < 10 * best[1], best
