@@ -331,8 +331,10 @@ int gd_autotune(gd_ctx *ctx, const gd_instance *inst, int32_t count, void *strea
  */
 int gd_set_tuning_file(gd_ctx *ctx, const char *path);
 
-/* Copy the counters of the last successful dbscan() call (counting the entries
- * of its neighbour lists on the device if the call did not need them). */
+/* Copy the counters of the last successful dbscan() call.  After a call that
+ * did not need the neighbour lists (sparse grids from four dimensions on) the
+ * first gd_get_stats counts their entries on the device, which takes a few per
+ * cent to 40 % of the call's time and can fail with GD_EDEVICE. */
 int gd_get_stats(gd_ctx *ctx, gd_stats *out);
 
 /* Phases of dbscan() timed with GD_OPT_TIMING. */

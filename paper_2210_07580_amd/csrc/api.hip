@@ -183,7 +183,7 @@ struct gd_ctx {
         bool pending = false;  // neighbor_entries not counted yet
         bool missing = false;  // lists not written yet
         GridView g{};
-        TreeView t{};
+        RunSource runs{};      // (its node lists lie in own.nei)
         uint32_t* off_counts = nullptr;
         uint64_t* nei_off = nullptr;
         uint64_t* partial = nullptr;
@@ -498,18 +498,18 @@ NeiQuery walk_order_query(const TreeView& t) {
 }
 
 // After a call that found the neighbours as runs: counts sum |Nei(g)| into
-// the statistics (the call's tree is still in the workspace).
+// the statistics (the call's tree and node lists are still in the workspace).
 int count_entries(gd_ctx* ctx) {
     gd_ctx::Lists& a = ctx->lists;
     if (!a.pending) return GD_OK;
     DeviceGuard guard(ctx->device);
     if (!guard.ok || !own_stream(ctx)) return ctx->fail(GD_EDEVICE, "no stream to count the neighbour lists on");
     hipStream_t st = ctx->gstream;
-    GD_TRY(launch_nei_count(a.g, walk_order_query(a.t), a.off_counts, nullptr, nullptr, st));
-    GD_TRY(launch_nei_offsets(a.g, a.off_counts, a.nei_off, a.partial, st));
+    GD_TRY(fill<uint64_t>(&ctx->hdr_dev->run_total, 1, 0ull, st));
+    GD_TRY(launch_run_total(a.g, a.runs, st));
     int rc;
     if ((rc = readback(ctx, st))) return rc;
-    ctx->last.neighbor_entries = (int64_t)ctx->hdr_host->nei_total;
+    ctx->last.neighbor_entries = (int64_t)(ctx->hdr_host->run_total - ctx->hdr_host->ncell);
     a.pending = false;
     return GD_OK;
 }
@@ -523,9 +523,14 @@ int write_lists(gd_ctx* ctx) {
     const uint64_t total = (uint64_t)ctx->last.neighbor_entries;
     if ((rc = grow(ctx, ctx->own.nei, (size_t)std::max<uint64_t>(total, 1) * sizeof(uint32_t), ctx->own.arena.cap)))
         return rc;
-    GD_TRY(launch_nei_fill(a.g, walk_order_query(a.t), a.off_counts, nullptr, a.nei_off, (uint32_t*)ctx->own.nei.p,
-                           total, nullptr, a.nei_up, ctx->gstream));
-    GD_TRY(hipStreamSynchronize(ctx->gstream));
+    const NeiQuery nq = walk_order_query(a.runs.t);
+    if (!own_stream(ctx)) return ctx->fail(GD_EDEVICE, "no stream to write the neighbour lists on");
+    hipStream_t st = ctx->gstream;
+    GD_TRY(launch_nei_count(a.g, nq, a.off_counts, nullptr, nullptr, st));
+    GD_TRY(launch_nei_offsets(a.g, a.off_counts, a.nei_off, a.partial, st));
+    GD_TRY(launch_nei_fill(a.g, nq, a.off_counts, nullptr, a.nei_off, (uint32_t*)ctx->own.nei.p, total, nullptr,
+                           a.nei_up, st));
+    GD_TRY(hipStreamSynchronize(st));
     ctx->last_nei = (const uint32_t*)ctx->own.nei.p;
     ctx->last_nei_total = total;
     a.missing = false;
@@ -1187,7 +1192,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     if (runs) {
         lists.pending = lists.missing = true;
         lists.g = g;
-        lists.t = t;
+        lists.runs = rsrc;
         lists.off_counts = L.off_counts;
         lists.nei_off = L.nei_off;
         lists.partial = L.partial;
@@ -1420,9 +1425,14 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
         }
     } inval{ctx, gen0};
     const int fin = (p.runs ? D - 1 : D) & 1;
+    const size_t nei_bytes = (size_t)std::max<uint64_t>(levels ? p.ents[fin] : p.nei, 1) * sizeof(uint32_t);
+    // the node lists go when their buffer grows: what is counted in them first
+    if (nei_bytes > ctx->own.nei.cap && count_entries(ctx)) {
+        ctx->err = saved_err;
+        return;
+    }
     MidUse use(ctx);
-    if (grow(ctx, ctx->cur->nei, (size_t)std::max<uint64_t>(levels ? p.ents[fin] : p.nei, 1) * sizeof(uint32_t),
-             ctx->cur->arena.cap) ||
+    if (grow(ctx, ctx->cur->nei, nei_bytes, ctx->cur->arena.cap) ||
         (levels && grow(ctx, ctx->cur->mid, (size_t)p.ents[1 - fin] * sizeof(uint32_t), ctx->cur->arena.cap)) ||
         (p.key_bits <= 64 && grow(ctx, ctx->cur->table, output_table_bytes(table_bits(p.ncell), key_bytes_of(p.key_bits)),
                                   ctx->cur->arena.cap + ctx->cur->nei.cap)) ||

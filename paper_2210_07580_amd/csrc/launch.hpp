@@ -93,6 +93,7 @@ struct Header {
     uint32_t pad;
     SplitCount split[2];  // tasks asked for by core marking and by the border search (SplitQueue)
     uint64_t nei_total;
+    uint64_t run_total;   // launch_run_total
 };
 
 struct Batch {
@@ -245,6 +246,8 @@ struct RunSource {
     int64_t families;       // nodes of level D-1 (or an upper bound)
     bool long_families;     // one may have more than kFamilyGrids grids
 };
+// Adds sum |Nei(g)| + |Gs|, which the runs give without lists, to the header's run_total.
+hipError_t launch_run_total(const GridView& g, const RunSource& runs, hipStream_t st);
 // Grids of a family that the thread or wave of the family takes; those behind
 // them are spread over others.
 constexpr uint32_t kFamilyGrids = 64;

@@ -270,6 +270,68 @@ __global__ __launch_bounds__(kBlock) void level_kernel(LevelArgs A) {
     }
 }
 
+// Neighbours of all grids (their own included), counted in the runs: a wave takes
+// kCountFamilies families one after another (in the waves behind: 64 grids that
+// lie behind the first kFamilyGrids of theirs), a lane the entry, whose window is
+// searched for each of the family's grids.  Entries (p, b) and (b, p) count the
+// same pairs: those with b > p count twice.  A walk of the tree per grid takes
+// 18.8 ms where this takes 14.2 (10M 5-D points, 5.1e9 neighbours), 3.2 and 0.2
+// (2M 7-D).
+constexpr int kCountFamilies = 8;
+
+__global__ __launch_bounds__(kBlock) void run_total_kernel(const uint32_t* families, const uint32_t* ncell,
+                                                           RunSource rs, const uint32_t* __restrict__ child,
+                                                           const int32_t* __restrict__ key, int64_t family_waves,
+                                                           uint64_t* total) {
+    __shared__ uint64_t sums[kWavesPerBlock];
+    const int w = wave_id(), lane = lane_id();
+    const int64_t wave = xcd_runs<16>(block_id(), block_count()) * kWavesPerBlock + w;
+    uint64_t sum = 0;
+    auto count = [&](uint32_t p, uint32_t cb, uint32_t m) {  // grids [cb, cb + m) of family p, m at most 64
+        const int32_t keys = key[cb + min((uint32_t)lane, m - 1)];
+        const uint64_t e1 = rs.off[p + 1];
+        for (uint64_t e = rs.off[p]; e < e1; e += kWave) {
+            const uint32_t v = e + lane < e1 ? rs.ent[e + lane] : 0u;
+            const uint32_t b = entry_node(v);
+            const bool in = e + lane < e1 && b >= p;
+            if (!ballot(in)) continue;
+            uint32_t b0 = 0, b1 = 0, pairs = 0;
+            if (in) node_children(child, b, b0, b1);
+            for (uint32_t a = 0; a < m; ++a) {
+                uint32_t lo, hi;
+                child_window(key, b0, b1, readlane(keys, (int)a), walk_window(entry_budget(v)), lo, hi);
+                pairs += hi - lo;
+            }
+            sum += b == p ? (uint64_t)pairs : 2ull * pairs;
+        }
+    };
+    if (wave < family_waves) {
+        const int64_t f0 = wave * kCountFamilies, f1 = min(f0 + kCountFamilies, (int64_t)*families);
+        for (int64_t f = f0; f < f1; ++f) {
+            const uint32_t c0 = child[f];
+            count((uint32_t)f, c0, min(child[f + 1] - c0, kFamilyGrids));
+        }
+    } else {
+        const int64_t c = (wave - family_waves) * kWave + lane;
+        uint32_t f = 0;
+        const bool mine = c < (int64_t)*ncell && family_rest(rs.excl, child, (uint32_t)c, f);
+        for (uint64_t todo = ballot(mine); todo;) {
+            const int first = ffs64(todo);
+            const uint32_t p = readlane(f, first);
+            const uint64_t same = ballot(mine && f == p);
+            todo &= ~same;
+            count(p, (uint32_t)(c - lane) + (uint32_t)first, (uint32_t)popc64(same));
+        }
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) sums[w] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kWavesPerBlock; ++i) sum += sums[i];
+        if (sum) atomicAdd((unsigned long long*)total, (unsigned long long)sum);
+    }
+}
+
 struct NodeTotal {
     const uint32_t* cnt;
     const uint32_t* nodes;
@@ -342,6 +404,17 @@ hipError_t launch_level(const GridView& g, const LevelArgs& A, int l, int64_t no
 }
 
 }  // namespace
+
+hipError_t launch_run_total(const GridView& g, const RunSource& runs, hipStream_t st) {
+    if (g.ncell == 0) return hipSuccess;
+    const int64_t per_block = (int64_t)kWavesPerBlock * kCountFamilies;
+    const int64_t blocks = (runs.families + per_block - 1) / per_block;
+    const int64_t rest = runs.long_families ? grid_for(g.ncell, kWavesPerBlock * kWave) : 0;
+    run_total_kernel<<<grid_of(blocks + rest), dim3(kBlock), 0, st>>>(
+        runs.t.level_count + (g.D - 1), g.ncell_dev, runs, runs.t.child[g.D - 1], runs.t.key[g.D],
+        blocks * kWavesPerBlock, &g.b.hdr->run_total);
+    return hipGetLastError();
+}
 
 hipError_t launch_level_count(const GridView& g, const TreeView& t, const NodeLists& nl, int l, int64_t nodes,
                               int lanes, uint64_t* partial, hipStream_t st) {

@@ -59,8 +59,30 @@ def test_lines(G, length, d, rows, per, minpts, gaps):
         lab, core = ctx.dbscan(dev(x), eps, minpts)
         assert np.array_equal(core.cpu().numpy(), want[1]), f"call {call}"
         assert np.array_equal(lab.cpu().numpy(), want[0]), f"call {call}"
-    assert ctx.stats()["graph_replays"] == 1
+    st = ctx.stats()
+    assert st["graph_replays"] == 1
+    ref = G.Context(0)
+    ref.set_option(G.GD_OPT_NEIGHBOR_MODE, 1)
+    ref.dbscan(dev(x), eps, minpts)
+    assert st["neighbor_entries"] == ref.stats()["neighbor_entries"]
+    ref.close()
     ctx.close()
+
+
+def test_counts_outlive_the_capture_that_follows_a_call(G):
+    # the captured run's node lists get more room than the call's own, which
+    # the count of the call's neighbours reads
+    ctx, ref = G.Context(0), G.Context(0)
+    ctx.set_option(G.GD_OPT_GRAPH, 2)
+    ref.set_option(G.GD_OPT_NEIGHBOR_MODE, 1)
+    for length in (30, 100, 300):
+        x = lines(length, 5, length, 6, 2, True)
+        for c in (ctx, ref):
+            c.dbscan(dev(x), 111, 4)
+        assert ctx.stats()["graph_replays"] == 0
+        assert ctx.stats()["neighbor_entries"] == ref.stats()["neighbor_entries"]
+    ctx.close()
+    ref.close()
 
 
 def test_a_replay_meets_longer_families_than_the_call_before(G):
