@@ -146,7 +146,7 @@ struct gd_ctx {
     const int32_t* last_cell_label = nullptr;
     GridView last_g{};
     CoreOut last_co{};
-    int64_t last_max_core = 0;
+    int64_t last_max_core = 0, last_big = 0;
     bool last_summaries = false;
     // learned proposal
     __half* proposal_dev = nullptr;  // GD_MLP_PARAMS halves
@@ -336,6 +336,7 @@ struct Plan {
     int64_t ncell;     // grids
     uint64_t nei;      // neighbour-list entries
     int64_t ncc;       // core grids
+    int64_t big;       // core grids that are not tiny (no bound)
     int64_t max_core;  // largest core set
     bool walk;         // consumers walk the grid tree (lists only for big core sets)
     bool runs;         // neighbours as runs: node lists instead of neighbour lists
@@ -1141,11 +1142,12 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
             ctx->last_summaries = true;
         }
         const int64_t n_small = !ctx->ldf ? -1 : plan ? -2 : (int64_t)H->counts[4];
+        const int64_t n_big = plan ? plan->big : ncc - (int64_t)H->counts[4];
         if (walk)
             GD_TRY(launch_merge_walk(g, co, t, ldf, n_small, L.parent, stats ? ctx->stats_dev->merge : nullptr, wide,
                                      st));
         GD_TRY(launch_merge(g, co, L.nei_off, nei, !lists_up || walk ? nullptr : by_level ? grid_up : L.nei_up, rs,
-                            ldf, L.rank, ncc, n_small, max_core, ctx->merge_waves,
+                            ldf, L.rank, ncc, n_small, n_big, max_core, ctx->merge_waves,
                             small_lanes, walk,
                             hm.q, wide, L.parent, stats ? ctx->stats_dev->merge : nullptr,
                             ctx->proposal_on ? ctx->proposal_dev : nullptr, sum, free_words, st));
@@ -1235,6 +1237,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     ctx->last_g = g;
     ctx->last_co = co;
     ctx->last_max_core = max_core;
+    ctx->last_big = ncc - (int64_t)H->counts[4];
     ctx->last_key_bits = key_bits;
     ctx->last_walk = walk;
     ctx->last_wide = wide;
@@ -1404,6 +1407,7 @@ void capture_graph(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, std
     p.ncell = planned_grids(n, e.grids, levels);
     p.nei = (uint64_t)e.neighbor_entries + (uint64_t)e.neighbor_entries / 16 + 4096;
     p.ncc = std::min<int64_t>(p.ncell, e.core_grids + e.core_grids / 16 + 256);
+    p.big = ctx->last_big;
     p.max_core = std::min<int64_t>(std::min<int64_t>(n, kMaxCoreBits), ctx->last_max_core + ctx->last_max_core / 16 + 64);
     p.walk = ctx->last_walk;
     p.ordered = ctx->last_ordered;

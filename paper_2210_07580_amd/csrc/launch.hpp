@@ -396,6 +396,7 @@ struct CellSummary;
 // if the LDS bitmaps do not fit).  small_lanes: lanes per grid of the
 // tiny-set kernel (16: four grids per wave; else 64).  n_small: tiny core grids leading the
 // visiting order (-2: as many as the device count says, -1: not ordered).
+// n_big: core grids that are not tiny (planned runs: as many as the call before had).
 // tiny_done: the pairs of two tiny core sets were already merged (walk mode).
 // nei_up (optional, lists in walk order): each list's range of larger-index
 // neighbours (launch_nei_fill), the only ones the tiny-set kernel tests.
@@ -405,7 +406,7 @@ struct CellSummary;
 hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
                         const uint2* nei_up, const RunSource* runs,
                         const uint32_t* ldf_list, const uint4* rank, int64_t n_core_cells, int64_t n_small,
-                        int64_t max_core, int waves, int small_lanes, bool tiny_done, const HugeQueue& huge,
+                        int64_t n_big, int64_t max_core, int waves, int small_lanes, bool tiny_done, const HugeQueue& huge,
                         bool wide,
                         uint32_t* parent, MergeStats* stats, const __half* proposal, const CellSummary* sum,
                         uint32_t* family_root, hipStream_t st);

@@ -664,9 +664,15 @@ __global__ __launch_bounds__(kBlock, (kLearned || D >= 5) ? 4 : 6) void merge_bi
     if (stats && lane == 0) flush_stats(stats, r, n_pairs, n_skip, n_test, n_yes, n_iter, max_it, n_dist, n_pts);
 }
 
+// Waves of merge_big_kernel that the GPU holds from four or five dimensions on:
+// four on each of its 1,024 SIMDs.
+constexpr int64_t kBigResident = 4096;
+constexpr int64_t kBigHalvesMin = 768;
+
 hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei_off, const uint32_t* nei,
                         const uint2* nei_up, const RunSource* runs,
-                        const uint32_t* ldf_list, const uint4* rank, int64_t ncc, int64_t n_small, int64_t max_core,
+                        const uint32_t* ldf_list, const uint4* rank, int64_t ncc, int64_t n_small, int64_t n_big,
+                        int64_t max_core,
                         int waves, int small_lanes, bool tiny_done, const HugeQueue& huge, bool wide,
                         uint32_t* parent, MergeStats* stats, const __half* proposal, const CellSummary* sum,
                         uint32_t* family_root, hipStream_t st) {
@@ -743,15 +749,17 @@ hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei
                              65536;
     // The visiting order only helps where later waves start after earlier ones
     // ended: the denser grids' pairs are then mostly joined already.  With
-    // fewer grids than the GPU holds waves all of them start at once and the
-    // densest test everything, on the longest waves; two launches put the
-    // denser half behind the sparser.  Taken where the lists are long (five
-    // dimensions and more): 7-D with 5,892 and 3,758 core grids 670 -> 272 and 740 ->
-    // 417 us, 5-D with 2,755, 1,543 and 984 580 -> 410, 615 -> 455 and 650 -> 560 us; 5-D
-    // with 6,310 370 -> 400 us, and in two and three dimensions the second launch's
-    // own tail costs more as often as not (2M points at eps 1000 284 -> 391 us).
+    // fewer grids than a load or two of resident waves (kBigResident) most start at
+    // once and the densest test everything, on the longest waves; two launches
+    // put the denser half behind the sparser.  With less than about a wave per
+    // SIMD nothing contends, and the second launch adds its own tail.  Gain of the
+    // merge by the number of these grids, over sweeps of 60k to 3M points in five
+    // to eight dimensions: 1.01 for 600-800, 1.20 for 800-1024, 1.2-1.5 up to 8192,
+    // 1.12 to 10k, 0.99 beyond; in four 1.06-1.43 for 800-8192 and 0.96 beyond; in
+    // two and three, where lists are short, the second tail costs more as often
+    // as not (2M points at eps 1000 284 -> 391 us).
     const int64_t all = ncc - b0;
-    const int parts = g.D >= 5 && n_small != -1 && all >= 512 && all <= 6000 ? 2 : 1;
+    const bool halves = g.D >= 4 && n_small != -1 && n_big >= kBigHalvesMin && n_big <= 2 * kBigResident;
     auto launch = [&](int64_t skip, int64_t take) -> hipError_t {
         const dim3 blocks = grid_of((take + wpb - 1) / wpb), threads(wpb * kWave);
         if (runs) {
@@ -776,14 +784,12 @@ hipError_t launch_merge(const GridView& g, const CoreOut& c, const uint64_t* nei
         }
         return hipGetLastError();
     };
-    for (int p = 0; p < parts; ++p) {
-        const int64_t lo = all * p / parts, hi = all * (p + 1) / parts;
-        if (lo < hi) {
-            const hipError_t e = launch(lo, hi - lo);
-            if (e != hipSuccess) return e;
-        }
+    const int64_t half = halves ? std::min(n_big / 2, all) : 0;
+    if (half > 0) {
+        const hipError_t e = launch(0, half);
+        if (e != hipSuccess) return e;
     }
-    return hipGetLastError();
+    return all > half ? launch(half, all - half) : hipGetLastError();
 }
 
 // ---- The BFS merge order of Algorithm 6 (Section 4.4), for comparison with
