@@ -54,7 +54,9 @@ PHASE_KERNELS = {
     "core_mark": ["core_mark_kernel (core_mark_group_kernel for small grids, core_mark_runs_kernel on sparse data)"],
     "merge": ["merge_small_kernel (merge_family_kernel on sparse data)", "merge_big_kernel"],
     "output": ["hash_clear_kernel", "hash_build_kernel", "output_direct_kernel", "output_kernel"],
-    "nei_fill": ["nei_fill_kernel (lists in walk order and of four dimensions and more: level_kernel)"],
+    "nei_count": ["nei_count_kernel or, level by level, level_kernel", "scan_reduce_kernel", "scan_down_kernel"],
+    "nei_fill": ["nei_fill_kernel (lists in walk order and of four dimensions and more, and node lists: "
+                 "level_kernel)"],
 }
 
 
@@ -106,6 +108,8 @@ def algorithmic_bytes(phase, n, d, st, key_bytes, passes, packed):
     if phase == "output":
         return n * (4 + 4 + 1)
     if phase == "nei_fill":
+        if d >= 4 and not (st["grids"] <= 1 << 19 and n >= 8 * st["grids"]):
+            return None  # node lists instead of lists per grid, whose length the statistics do not give
         return st["neighbor_entries"] * 4 + st["grids"] * (8 + 4 * d)
     return None
 

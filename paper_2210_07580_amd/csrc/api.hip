@@ -171,9 +171,13 @@ struct gd_ctx {
     bool marking = true;
     // phase timing
     bool timing = false;
-    bool events_ok = false;
-    hipEvent_t ev[P_COUNT][2] = {};
-    bool ran[P_COUNT] = {};
+    struct Span {  // of a phase: the lists of several tree levels take several
+        int phase;
+        hipEvent_t ev[2];
+        bool ended;
+    };
+    std::vector<Span> spans;   // created as calls need them, kept for later ones
+    size_t spans_used = 0;
     double phase_ms[P_COUNT] = {};
     hipStream_t st = nullptr;
     // What counting or writing Nei(g) per grid needs, after a call that found
@@ -193,8 +197,23 @@ struct gd_ctx {
     Lists plan_lists;  // of a replay of the captured graph
 
     void mark(int phase, int which) {
-        if (!timing || !events_ok || !marking) return;
-        if (hipEventRecord(ev[phase][which], st) == hipSuccess && which == 1) ran[phase] = true;
+        if (!timing || !marking) return;
+        if (which == 0) {
+            if (spans_used == spans.size()) {
+                Span s{};
+                if (hipEventCreate(&s.ev[0]) != hipSuccess) return;
+                if (hipEventCreate(&s.ev[1]) != hipSuccess) {
+                    (void)hipEventDestroy(s.ev[0]);
+                    return;
+                }
+                spans.push_back(s);
+            }
+            spans[spans_used].phase = phase;
+            spans[spans_used].ended = false;
+            if (hipEventRecord(spans[spans_used].ev[0], st) == hipSuccess) ++spans_used;
+        } else if (spans_used > 0 && spans[spans_used - 1].phase == phase) {
+            spans[spans_used - 1].ended = hipEventRecord(spans[spans_used - 1].ev[1], st) == hipSuccess;
+        }
     }
 
     int fail(int code, const char* fmt, ...) {
@@ -717,10 +736,8 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
 
     ctx->st = st;
     ctx->marking = !plan;
-    for (int p = 0; p < P_COUNT; ++p) {
-        ctx->ran[p] = false;
-        ctx->phase_ms[p] = 0.0;
-    }
+    ctx->spans_used = 0;
+    for (int p = 0; p < P_COUNT; ++p) ctx->phase_ms[p] = 0.0;
 
     // ---- instance table, mn_j and the input check (Eq. (1)), identifier layout
     GD_TRY(hipMemcpyAsync(ctx->inst_dev, ctx->inst_host, sizeof(Inst) * count, hipMemcpyHostToDevice, st));
@@ -954,7 +971,6 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
             for (int l = 0; l <= D; ++l) nodes[l] = (int64_t)H->level_count[l];
             known = true;
         };
-        ctx->mark(P_NEI_COUNT, 0);
         if (!known && last >= 3 && ncell > 65536) {
             if ((rc2 = readback(ctx, st))) return rc2;
             read_nodes();
@@ -967,7 +983,9 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
                               : visits <= 24 || l == D  ? 16
                                                         : kWave;
             if (plan) GD_TRY(launch_plan_check(Hd, 3, l, plan->nodes[l], st));
+            ctx->mark(P_NEI_COUNT, 0);
             GD_TRY(launch_level_count(g, t, nl, l, nodes[l], lanes, L.partial, st));
+            ctx->mark(P_NEI_COUNT, 1);
             if (plan) {
                 GD_TRY(launch_plan_check(Hd, 1, (int64_t)plan->ents[l & 1], 0, st));
             } else {
@@ -987,9 +1005,10 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
                 visits = (double)total / (double)std::max<int64_t>(nodes[l], 1);
                 if (l == D) nei_total = H->nei_total;
             }
+            ctx->mark(P_NEI_FILL, 0);
             GD_TRY(launch_level_fill(g, t, nl, l, nodes[l], lanes, st));
+            ctx->mark(P_NEI_FILL, 1);
         }
-        ctx->mark(P_NEI_COUNT, 1);
         if (!plan)
             for (int l = 0; l < kMaxLevels; ++l) ctx->last_nodes[l] = nodes[l];
         if (last == D) {
@@ -1212,12 +1231,10 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     if (H->err & kErrMergeRunaway) return ctx->fail(GD_EDEVICE, "merge step exceeded its iteration bound");
     if (H->err & (kErrNeiOverflow | kErrCoreCap))
         return ctx->fail(GD_EDEVICE, "internal capacity check failed (error bits 0x%x)", H->err);
-    if (ctx->timing && ctx->events_ok) {
-        for (int p = 0; p < P_COUNT; ++p) {
-            float ms = 0.f;
-            if (ctx->ran[p] && hipEventElapsedTime(&ms, ctx->ev[p][0], ctx->ev[p][1]) == hipSuccess)
-                ctx->phase_ms[p] = ms;
-        }
+    for (size_t i = 0; i < ctx->spans_used; ++i) {
+        const gd_ctx::Span& s = ctx->spans[i];
+        float ms = 0.f;
+        if (s.ended && hipEventElapsedTime(&ms, s.ev[0], s.ev[1]) == hipSuccess) ctx->phase_ms[s.phase] += ms;
     }
 
     ctx->have_last = true;
@@ -1621,12 +1638,6 @@ int gd_create(gd_ctx** out, int device) {
         // with the device current: this device's copy of the scratch array
         if (ok) ctx->scratch = scratch_address(device);
         if (ok) std::memset(ctx->hdr_host, 0, (kSeqWord + 1) * sizeof(uint32_t));
-        if (ok) {
-            ctx->events_ok = true;
-            for (int p = 0; p < P_COUNT; ++p)
-                for (int k = 0; k < 2; ++k)
-                    if (hipEventCreate(&ctx->ev[p][k]) != hipSuccess) ctx->events_ok = false;
-        }
     }
     if (!ok) {
         gd_destroy(ctx);
@@ -1656,9 +1667,8 @@ void gd_destroy(gd_ctx* ctx) {
     drop_graph(ctx);
     if (ctx->gev) (void)hipEventDestroy(ctx->gev);
     if (ctx->gstream) (void)hipStreamDestroy(ctx->gstream);
-    for (int p = 0; p < P_COUNT; ++p)
-        for (int k = 0; k < 2; ++k)
-            if (ctx->ev[p][k]) (void)hipEventDestroy(ctx->ev[p][k]);
+    for (const gd_ctx::Span& s : ctx->spans)
+        for (hipEvent_t e : s.ev) (void)hipEventDestroy(e);
     delete ctx;
 }
 
