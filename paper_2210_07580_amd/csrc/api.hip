@@ -1628,7 +1628,9 @@ int gd_create(gd_ctx** out, int device) {
     {
         DeviceGuard guard(device);
         ok = guard.ok && hipMalloc(&ctx->hdr_dev, sizeof(Header)) == hipSuccess &&
-             hipHostMalloc(&ctx->hdr_host, (kSeqWord + 1) * sizeof(uint32_t), hipHostMallocDefault) == hipSuccess &&
+             // coherent whatever the environment says: the host reads it while a kernel writes it
+             hipHostMalloc(&ctx->hdr_host, (kSeqWord + 1) * sizeof(uint32_t),
+                           hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
              hipHostGetDevicePointer((void**)&ctx->hdr_map, ctx->hdr_host, 0) == hipSuccess &&
              hipMalloc(&ctx->stats_dev, sizeof(StatBlock)) == hipSuccess &&
              hipHostMalloc(&ctx->stats_host, sizeof(StatBlock), hipHostMallocDefault) == hipSuccess &&
