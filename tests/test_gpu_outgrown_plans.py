@@ -1,0 +1,92 @@
+"""Replays whose data outgrow one capacity of the captured run at a time: the
+nodes of a tree level, the entries of the node lists, the grids.  The replay
+is given up (graph_replays 0), the eager result is the oracle's, and the next
+call of the shape replays again."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+D, EPS, SIDE, N = 5, 112, 112 / np.sqrt(5), 6000
+
+
+@pytest.fixture(scope="module")
+def G():
+    import paper_2210_07580_amd as G
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return G
+
+
+def points(cells, extent):
+    """One point in the middle of each of the given cells, in random order, and
+    the corners of a box of `extent` cells, so that all identifiers are alike wide."""
+    cells = np.concatenate([cells, np.zeros((1, D), np.int64), np.full((1, D), extent)])
+    x = np.floor((cells + 0.5) * SIDE).astype(np.int32)
+    x[-2] = 0
+    return x[np.random.default_rng(0).permutation(len(x))]
+
+
+def check(G, ctx, x, minpts=2):
+    want = oracle.dbscan(x, EPS, minpts)
+    lab, core = ctx.dbscan(torch.from_numpy(x.astype(np.float32)).cuda(), EPS, minpts)
+    assert np.array_equal(core.cpu().numpy(), want[1])
+    assert np.array_equal(lab.cpu().numpy(), want[0])
+    return ctx.stats()
+
+
+def spread(width):
+    # distinct cells, `width` keys per dimension
+    seed = np.random.default_rng(width)
+    flat = seed.choice(np.prod(np.array(width, dtype=np.int64)), size=N, replace=False)
+    return np.stack(np.unravel_index(flat, width), axis=1).astype(np.int64)
+
+
+def few_nodes():  # two keys in each of the first four dimensions, long in the last
+    return spread((2, 2, 2, 2, 1000))
+
+
+def many_nodes():  # the same cells, seen from the other end: nodes by the thousand from level 2 on
+    return spread((1000, 2, 2, 2, 2))[:, [0, 4, 1, 2, 3]]
+
+
+def scattered():  # cells far from one another: lists of the own node alone
+    return spread((1000, 1000, 1000, 1000, 1000))
+
+
+def dense():  # a block of neighbours: far fewer nodes, hundreds of entries in each list
+    return spread((6, 6, 6, 6, 6))
+
+
+@pytest.mark.parametrize("options", [[], [("GD_OPT_NEIGHBOR_MODE", 1)]])
+@pytest.mark.parametrize("planned,met", [(few_nodes, many_nodes), (scattered, dense)])
+def test_replay_is_given_up(G, planned, met, options):
+    a, b = points(planned(), 1000), points(met(), 1000)
+    ref = G.Context(0)
+    sa, sb = check(G, ref, a), check(G, ref, b)
+    ref.close()
+    # not by the grid count, which the plan holds (a sixteenth and 1024 more)
+    assert sb["grids"] <= sa["grids"] + sa["grids"] // 16 + 1024
+    if met is dense:  # more entries than planned for, also per node of the level before the last
+        assert sb["neighbor_entries"] > 100 * (sa["neighbor_entries"] + N)
+    ctx = G.Context(0)
+    ctx.set_option(G.GD_OPT_GRAPH, 2)
+    for k, v in options:
+        ctx.set_option(getattr(G, k), v)
+    for x, replayed in ((a, 0), (a, 1), (b, 0), (b, 1), (b, 1)):
+        assert check(G, ctx, x)["graph_replays"] == replayed
+    ctx.close()
+
+
+def test_replay_with_more_grids_is_given_up(G):
+    one = points(np.repeat(spread((10, 10, 10, 10, 10))[:500], 12, axis=0), 1000)
+    many = points(scattered(), 1000)
+    ctx = G.Context(0)
+    ctx.set_option(G.GD_OPT_GRAPH, 2)
+    for x, replayed in ((one, 0), (one, 1), (many, 0), (many, 1)):
+        assert check(G, ctx, x)["graph_replays"] == replayed
+    ctx.close()
