@@ -1057,8 +1057,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     ctx->mark(P_CORE_MARK, 0);
     if (walk)
         GD_TRY(launch_core_walk(g, t, L.core, L.core_cnt, stats ? ctx->stats_dev->core : nullptr, wide, st));
-    else
-    {
+    else {
         SplitQueue sq{};
         sq.tasks = L.rank;
         sq.cap = split_slots(n);
@@ -1197,8 +1196,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
         GD_TRY(launch_output_allcore(g, co, L.cell_label, st));
     if (walk)
         GD_TRY(launch_border_walk(g, co, t, L.cell_label, wide, st));
-    else
-    {
+    else {
         SplitQueue sq{};
         sq.best = (uint64_t*)L.rank;
         sq.tasks = L.rank + (n + 1) / 2;

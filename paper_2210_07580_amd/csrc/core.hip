@@ -529,9 +529,9 @@ __device__ __forceinline__ bool mark_grid(const GridView& gv, const uint32_t* __
 // wave.  Grids that want more are taken by the whole wave one after another.
 // Lists of 40 and grids of 32 points on
 // average: the batch of 256 2,255 -> 1,514 us, 2M 3-D points in small clusters
-// 105 -> 58, 1M 2-D noise beside lumps of 1e5 303 -> 109; without the whole wave
-// the last of these shapes went up to 520 from 390 us.  MinPts above 32 stays
-// with a wave per grid (60: 368 us there, 671 here).
+// 105 -> 58, 1M 2-D noise beside lumps of 1e5 303 -> 109; beside lumps of 2e4 it went
+// up to 520 from 390 us before the whole wave took the long streams.  MinPts above
+// 32 stays with a wave per grid (60: 368 us there, 671 here).
 template <int D, bool kPacked>
 __global__ __launch_bounds__(kBlock) void core_mark_group_kernel(GridView gv, const uint64_t* __restrict__ nei_off,
                                                                  const uint32_t* __restrict__ nei,

@@ -204,7 +204,7 @@ __global__ __launch_bounds__(kBlock) void merge_small_kernel(GridView gv, CoreOu
 // 10M 5-D points: 33.2 -> 10.9 ms for the tiny sets (2.9 + 3.0 + 4.9 ms for the
 // three phases; a first phase over all touching grids and none in between took
 // 13.8, one over faces and then everything 24.7 ms).  Bound by the latency of
-// the pairs' loads (11-18% of the vector issue rate at full occupancy).
+// the pairs' loads (15-22% of the vector issue rate, 18-21 waves per CU).
 constexpr uint32_t kFamilyEmpty = 0xFFFFFFFEu;  // no tiny core grid
 constexpr uint32_t kFamilyMixed = kNone;        // tiny core grids of several sets
 constexpr int kFamilies = 8;

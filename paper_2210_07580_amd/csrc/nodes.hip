@@ -13,7 +13,7 @@
 // 10M 5-D points (6.9M grids, 3.1M families): walks counted and wrote 5.1e9
 // list entries in 52 ms; these lists hold 0.8e9 and take 9.5 ms.  2M and 1M
 // 7-D points: 7.1 -> 0.9 and 5.1 -> 0.6 ms.  The passes over long lists are
-// bound by vector instructions (72-77% of the issue rate), most of them the key
+// bound by vector instructions (74-91% of the issue rate), most of them the key
 // search and the entries' arithmetic; pass 2 therefore writes one entry per
 // lane and round rather than each lane its own run (6.3 -> 5.7 ms).  The lists
 // of the grids themselves in two and three dimensions: 43 -> 35 us for 20k
@@ -190,9 +190,9 @@ __global__ __launch_bounds__(kBlock) void level_kernel(LevelArgs A) {
                     const int left = entry_budget(how) - gap * gap;
                     if constexpr (kOrdered) {
                         const bool self = v && x == (uint32_t)a;
-                    const int off = v && !self ? dk - left : kMaxD;
-                    const uint64_t sm = ballot(self);
-                    if (pass == 1 && sm) own = part[0] + (uint32_t)popc64(ballot(off == 0) & ((sm & -sm) - 1ull));
+                        const int off = v && !self ? dk - left : kMaxD;
+                        const uint64_t sm = ballot(self);
+                        if (pass == 1 && sm) own = part[0] + (uint32_t)popc64(ballot(off == 0) & ((sm & -sm) - 1ull));
                         uint32_t at = 0;
 #pragma unroll
                         for (int o = 0; o < kMaxD; ++o) {
