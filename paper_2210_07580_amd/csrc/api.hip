@@ -859,7 +859,7 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     uint32_t* tpar[kMaxLevels] = {};
     for (int l = 1; l < D && (runs || by_level); ++l) tpar[l] = L.off_counts + (int64_t)(l - 1) * n;
     ctx->mark(P_TREE, 0);
-    GD_TRY(launch_tree(g, L.level_excl, (uint32_t*)L.partial, L.tkey, L.tchild, tpar, st));
+    GD_TRY(launch_tree(g, L.level_excl, (uint32_t*)L.partial, L.tkey, L.tchild, tpar, runs && !plan, st));
     ctx->mark(P_TREE, 1);
     TreeView t{};
     for (int l = 0; l < D; ++l) {

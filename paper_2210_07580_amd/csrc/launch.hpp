@@ -206,9 +206,10 @@ hipError_t launch_cells(const Batch& b, const K* skeys, uint32_t* partial, uint3
 // Grid tree levels over the sorted grids.  level_excl: D x (ncell+1) scratch;
 // partial: scan scratch of 64-bit words (passed as the u32 view).
 // tpar (or nullptr): per level 1 .. D-1, where each node's parent (its index
-// in the level above) goes; then the header's long_families is set, too.
+// in the level above) goes.  long_families: whether to look for what the header
+// says under this name.
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
-                       uint32_t* const* tchild, uint32_t* const* tpar, hipStream_t st);
+                       uint32_t* const* tchild, uint32_t* const* tpar, bool long_families, hipStream_t st);
 
 // ---- nodes.hip: lists of neighbouring tree nodes (runs.hpp)
 // Working set of the level-by-level build: the lists of level l live in

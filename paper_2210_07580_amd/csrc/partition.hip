@@ -848,7 +848,7 @@ struct TreeBuild {
     uint32_t* child[kMaxLevels];
     const uint32_t* excl[kMaxLevels];  // per level: nodes before grid c (c in [0, ncell])
     uint32_t* par[kMaxLevels];         // per level: each node's parent (nullptr: not kept)
-    uint32_t* long_families;           // set where a node of the last of these levels has many grids
+    uint32_t* long_families;           // set where a node of the last of these levels has many grids (or nullptr)
 };
 
 __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict__ ck, int64_t stride,
@@ -860,12 +860,13 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
         if (c == ncell || tb.excl[l][c + 1] != tb.excl[l][c]) {
             const uint32_t a = tb.excl[l][c];
             if (c < ncell) tb.key[l][a] = ck[(int64_t)l * stride + c];
-            if (c < ncell && l > 0 && tb.par[l]) {
-                tb.par[l][a] = tb.excl[l - 1][c + 1] - 1;
-                // the node's grids start here: does it hold the one kFamilyGrids on?
-                if (l + 2 == levels && c + kFamilyGrids < ncell && tb.excl[l][c + kFamilyGrids + 1] == a + 1)
-                    store_rel(tb.long_families, 1u);
-            }
+            if (c < ncell && l > 0 && tb.par[l]) tb.par[l][a] = tb.excl[l - 1][c + 1] - 1;
+            // the node's grids start here: does it hold the one kFamilyGrids on?  (A
+            // cached store, and only while the word reads 0: agent-wide stores by
+            // thousands of nodes took 150 us.)
+            if (tb.long_families && l + 2 == levels && c + kFamilyGrids < ncell &&
+                tb.excl[l][c + kFamilyGrids + 1] == a + 1 && !load_cached(tb.long_families))
+                store_cached(tb.long_families, 1u);
             // children: the level-(l+1) node that starts at grid c; the last level's nodes are the grids
             tb.child[l][a] = (l + 2 < levels) ? tb.excl[l + 1][c] : (uint32_t)c;
         }
@@ -873,11 +874,11 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
 }
 
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
-                       uint32_t* const* tchild, uint32_t* const* tpar, hipStream_t st) {
+                       uint32_t* const* tchild, uint32_t* const* tpar, bool long_families, hipStream_t st) {
     const int levels = g.D + 1;
     uint32_t* level_count = g.b.hdr->level_count;
     TreeBuild tb{};
-    tb.long_families = &g.b.hdr->long_families;
+    tb.long_families = long_families ? &g.b.hdr->long_families : nullptr;
     for (int l = 0; l + 1 < levels; ++l) {
         tb.key[l] = tkey[l];
         tb.child[l] = tchild[l];
