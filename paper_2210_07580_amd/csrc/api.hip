@@ -373,6 +373,8 @@ constexpr int64_t kEpsClamp = (int64_t)1 << 27;
 // build_lists: the full lists do not fit the workspace (limit or fixed
 // scratch) and the consumers may walk the grid tree instead.
 constexpr int kListsDoNotFit = 1;
+// build_levels: the families are such that walks find the lists sooner.
+constexpr int kListsByWalks = 2;
 
 // Hash tables of the grids (the hashing neighbour query's, the output's):
 // 2^bits slots for ncell grids, load <= 1/8 up to 2^20 grids (fewer second
@@ -841,9 +843,10 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     // distances keep the lists.  In two and three dimensions the lists are
     // short, and the same levels end in them (nodes.hip); in two dimensions
     // that takes no further memory.  So do the lists of more dimensions, in
-    // either order: the walks of neighbors.hip are left to bounded workspaces
-    // and to ordered lists in up to three dimensions, where the eight-lane walk
-    // is as fast and needs no read-back (10M 3-D points: 58 us).
+    // either order: the walks of neighbors.hip are left to bounded workspaces,
+    // to families of many grids (build_levels finds out) and to ordered lists in
+    // up to three dimensions, where the eight-lane walk is as fast and needs no
+    // read-back (10M 3-D points: 58 us).
     bool runs = plan ? plan->runs
                      : D >= kMinRunD && sparse && ctx->nei_query == kNeiAuto && ctx->nei_mode == 0 && !ctx->bfs &&
                            !stats && !ctx->proposal_on && !bounded && !wide && !split && ncell < kMaxRunNodes;
@@ -859,7 +862,8 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
     uint32_t* tpar[kMaxLevels] = {};
     for (int l = 1; l < D && (runs || by_level); ++l) tpar[l] = L.off_counts + (int64_t)(l - 1) * n;
     ctx->mark(P_TREE, 0);
-    GD_TRY(launch_tree(g, L.level_excl, (uint32_t*)L.partial, L.tkey, L.tchild, tpar, runs && !plan, st));
+    GD_TRY(launch_tree(g, L.level_excl, (uint32_t*)L.partial, L.tkey, L.tchild, tpar,
+                       !plan && D >= kMinRunD && (runs || by_level), st));
     ctx->mark(P_TREE, 1);
     TreeView t{};
     for (int l = 0; l < D; ++l) {
@@ -971,8 +975,12 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
             for (int l = 0; l <= D; ++l) nodes[l] = (int64_t)H->level_count[l];
             known = true;
         };
+        auto walks_better = [&]() {
+            return D >= kMinRunD && families_apart(H->families, ncell, (int64_t)H->level_count[D - 1]);
+        };
         if (!known && last >= 3 && ncell > 65536) {
             if ((rc2 = readback(ctx, st))) return rc2;
+            if (walks_better()) return kListsByWalks;
             read_nodes();
         }
         for (int l = 2; l <= last; ++l) {
@@ -990,8 +998,12 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
                 GD_TRY(launch_plan_check(Hd, 1, (int64_t)plan->ents[l & 1], 0, st));
             } else {
                 if ((rc2 = readback(ctx, st))) return rc2;
-                if (!known) read_nodes();
+                if (!known) {
+                    if (walks_better()) return kListsByWalks;
+                    read_nodes();
+                }
                 const uint64_t total = std::max<uint64_t>(H->nei_total, 1);
+                if (runs && l == last && families_alone(total, ncell, nodes[l])) return kListsByWalks;
                 if ((rc2 = grow(ctx, *buf[l & 1], (size_t)total * sizeof(uint32_t), ctx->cur->arena.cap))) {
                     if (rc2 != GD_ENOMEM) return rc2;
                     ctx->err.clear();
@@ -1022,13 +1034,13 @@ int run_batch(gd_ctx* ctx, int count, int D, int64_t n, uint32_t tiles, hipStrea
             rsrc.ent = nl.ent[fin];
             rsrc.near = nl.near;
             rsrc.families = nodes[D - 1];
-            rsrc.long_families = plan || H->long_families;
+            rsrc.long_families = plan || H->families.any_long;
         }
         return GD_OK;
     };
     if (runs || by_level) {
         rc = build_levels(runs ? D - 1 : D);
-        if (rc == kListsDoNotFit)
+        if (rc == kListsDoNotFit || rc == kListsByWalks)
             runs = by_level = false;
         else if (rc)
             return rc;

@@ -81,6 +81,12 @@ __device__ __forceinline__ typename Dist<kWide>::T inst_Tm(const Inst& I) {
     if constexpr (kWide) return I.Tm64; else return I.Tm;
 }
 
+// Families: the grids below one level-(D-1) node of the grid tree (runs.hpp).
+struct Families {
+    uint32_t any_long;    // one has more than kFamilyGrids grids
+    uint32_t next, far;   // see families_apart (from kGapBlocks workgroups' grids)
+};
+
 // Batch-wide identifier layout and counters (device).
 struct Header {
     int32_t inst_shift;   // position of the instance field (max over instances of key_bits)
@@ -89,7 +95,7 @@ struct Header {
     uint32_t ncell;       // |Gs| over the batch
     uint32_t level_count[kMaxLevels];
     uint32_t counts[5];   // core points, core grids, max core points per grid, dense grids, tiny core grids
-    uint32_t long_families; // a level-(D-1) node has more than kFamilyGrids grids
+    Families families;
     uint32_t pad;
     SplitCount split[2];  // tasks asked for by core marking and by the border search (SplitQueue)
     uint64_t nei_total;
@@ -206,10 +212,9 @@ hipError_t launch_cells(const Batch& b, const K* skeys, uint32_t* partial, uint3
 // Grid tree levels over the sorted grids.  level_excl: D x (ncell+1) scratch;
 // partial: scan scratch of 64-bit words (passed as the u32 view).
 // tpar (or nullptr): per level 1 .. D-1, where each node's parent (its index
-// in the level above) goes.  long_families: whether to look for what the header
-// says under this name.
+// in the level above) goes.  families: whether to fill in the header's.
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
-                       uint32_t* const* tchild, uint32_t* const* tpar, bool long_families, hipStream_t st);
+                       uint32_t* const* tchild, uint32_t* const* tpar, bool families, hipStream_t st);
 
 // ---- nodes.hip: lists of neighbouring tree nodes (runs.hpp)
 // Working set of the level-by-level build: the lists of level l live in
@@ -252,6 +257,28 @@ hipError_t launch_run_total(const GridView& g, const RunSource& runs, hipStream_
 // Grids of a family that the thread or wave of the family takes; those behind
 // them are spread over others.
 constexpr uint32_t kFamilyGrids = 64;
+constexpr uint32_t kGapBlocks = 64;  // workgroups of the tree kernel that look at the gaps
+// Families of many grids that lie apart (of `next` grids that follow another of
+// their family `far` lie beyond every window): an entry of a node list is then
+// a long search that mostly finds nothing, in neighbouring lanes in different
+// families, where the walks of neighbors.hip take neighbouring grids through the
+// same families.  300k points along the last dimension of 5, 6 and 8 (thousands
+// of grids per family; lists per grid, walked, against runs) 1.3 against 4.6 ms,
+// 2.3 against 8.7 and 9.8 against 50; along the last two of 4 and 5 (about 40 and 8 per
+// family) 1.40 against 2.56 and 1.69 against 2.40; 30k along the last two of 5 (2.4
+// per family) 1.06 against 0.66.
+constexpr int64_t kApartMean = 6;
+inline bool families_apart(const Families& f, int64_t grids, int64_t families) {
+    return grids >= kApartMean * families && 2ull * f.far > f.next;
+}
+// Long families with few others around them: the lists per grid are short, and
+// the merge of the runs searches long rows three times for them.  300k points along
+// the last dimension of 4 (27 entries per family) 0.91 against 2.1 ms; uniform 4-D
+// points (17 grids per family, hundreds of entries) 4.6 against 0.62.
+constexpr int64_t kFewMean = 10, kFewEntries = 40;
+inline bool families_alone(uint64_t entries, int64_t grids, int64_t families) {
+    return grids >= kFewMean * families && entries <= (uint64_t)(kFewEntries * families);
+}
 
 // ---- neighbors.hip (Algorithm 3)
 // The query that produces the lists: the grid tree with offset-ordered lists

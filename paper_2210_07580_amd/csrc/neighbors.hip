@@ -1,7 +1,8 @@
 // Non-empty neighbouring grids query (Section 4.2.2, Algorithm 3, Eq. (2)),
 // written out as lists Nei(g), one walk per grid.  They serve lists ordered by
 // offset in up to three dimensions, D = 1, workspaces that do not hold node
-// lists, more than 2^26 grids, and the comparison with direct hashing; the other
+// lists, more than 2^26 grids, data long and thin in their last dimensions
+// (families_apart, families_alone) and the comparison with direct hashing; the other
 // calls build their lists level by level (nodes.hip) or read neighbours as
 // runs (runs.hpp).
 //

@@ -848,13 +848,25 @@ struct TreeBuild {
     uint32_t* child[kMaxLevels];
     const uint32_t* excl[kMaxLevels];  // per level: nodes before grid c (c in [0, ncell])
     uint32_t* par[kMaxLevels];         // per level: each node's parent (nullptr: not kept)
-    uint32_t* long_families;           // set where a node of the last of these levels has many grids (or nullptr)
+    Families* families;                // what to find out about the last of these levels (or nullptr)
 };
 
 __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict__ ck, int64_t stride,
                                                       const uint32_t* ncell_dev, int levels, TreeBuild tb) {
     const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t ncell = *ncell_dev;
+    if (tb.families && blockIdx.x % max(1u, gridDim.x / kGapBlocks) == 0) {
+        // grids that follow another of their family, and how many of them so
+        // far behind it that no window reaches both
+        const uint32_t* excl = tb.excl[levels - 2];
+        const int32_t* last = ck + (int64_t)(levels - 1) * stride;
+        const bool next = c > 0 && c < ncell && excl[c + 1] == excl[c];
+        const uint64_t all = ballot(next), far = ballot(next && last[c] - last[c - 1] > kNear / 2);
+        if (lane_id() == 0 && all) {
+            atomicAdd(&tb.families->next, (uint32_t)popc64(all));
+            atomicAdd(&tb.families->far, (uint32_t)popc64(far));
+        }
+    }
     if (c > ncell) return;
     for (int l = 0; l + 1 < levels; ++l) {
         if (c == ncell || tb.excl[l][c + 1] != tb.excl[l][c]) {
@@ -864,9 +876,9 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
             // the node's grids start here: does it hold the one kFamilyGrids on?  (A
             // cached store, and only while the word reads 0: agent-wide stores by
             // thousands of nodes took 150 us.)
-            if (tb.long_families && l + 2 == levels && c + kFamilyGrids < ncell &&
-                tb.excl[l][c + kFamilyGrids + 1] == a + 1 && !load_cached(tb.long_families))
-                store_cached(tb.long_families, 1u);
+            if (tb.families && l + 2 == levels && c + kFamilyGrids < ncell &&
+                tb.excl[l][c + kFamilyGrids + 1] == a + 1 && !load_cached(&tb.families->any_long))
+                store_cached(&tb.families->any_long, 1u);
             // children: the level-(l+1) node that starts at grid c; the last level's nodes are the grids
             tb.child[l][a] = (l + 2 < levels) ? tb.excl[l + 1][c] : (uint32_t)c;
         }
@@ -874,11 +886,11 @@ __global__ __launch_bounds__(kBlock) void tree_kernel(const int32_t* __restrict_
 }
 
 hipError_t launch_tree(const GridView& g, uint32_t* level_excl, uint32_t* partial, int32_t* const* tkey,
-                       uint32_t* const* tchild, uint32_t* const* tpar, bool long_families, hipStream_t st) {
+                       uint32_t* const* tchild, uint32_t* const* tpar, bool families, hipStream_t st) {
     const int levels = g.D + 1;
     uint32_t* level_count = g.b.hdr->level_count;
     TreeBuild tb{};
-    tb.long_families = long_families ? &g.b.hdr->long_families : nullptr;
+    tb.families = families ? &g.b.hdr->families : nullptr;
     for (int l = 0; l + 1 < levels; ++l) {
         tb.key[l] = tkey[l];
         tb.child[l] = tchild[l];

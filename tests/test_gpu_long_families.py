@@ -115,3 +115,49 @@ def test_one_long_line_costs_no_more_than_its_points(G):
                 best[mode] = min(best.get(mode, 1e9), time.perf_counter() - t)
         ctx.close()
     assert best[0] < 10 * best[1], best
+
+
+@pytest.mark.parametrize("d,rows,length,minpts", [(4, 9, 900, 3), (5, 12, 400, 2), (8, 3, 250, 2), (4, 5, 16_000, 3)])
+@pytest.mark.parametrize("gap", [1, 2, 9])
+def test_lines_with_gaps(G, d, rows, length, minpts, gap):
+    # grids of a family next to each other, two and nine apart, in few families:
+    # calls below and above 65,536 grids choose walks at different places
+    print(f"case d={d} rows={rows} length={length} gap={gap}", flush=True)
+    rng = np.random.default_rng(gap)
+    x = lines(d + gap, d, length, rows, 2, True)
+    x[:, -1] = x[:, -1] * gap + rng.integers(0, 40, size=len(x))
+    eps = int(50 * np.sqrt(d))
+    want = oracle.dbscan(x, eps, minpts)
+    ctx = G.Context(0)
+    ctx.set_option(G.GD_OPT_GRAPH, 2)
+    for call in range(2):
+        lab, core = ctx.dbscan(dev(x), eps, minpts)
+        assert np.array_equal(core.cpu().numpy(), want[1]), f"call {call}"
+        assert np.array_equal(lab.cpu().numpy(), want[0]), f"call {call}"
+    ctx.close()
+
+
+@pytest.mark.parametrize("d", [4, 5, 8])
+def test_long_and_thin_data_cost_no_more_than_walked_lists(G, d):
+    # 200,000 points along the last dimension: runs took 2.4 to 5 times what the
+    # lists of the allocation-free entry take, which walks the tree for them (this
+    # allows twice)
+    rng = np.random.default_rng(d)
+    n = 200_000
+    x = rng.random((n, d)) * 60
+    x[:, -1] = rng.random(n) * n * 5
+    t = dev(np.floor(x))
+    lab = torch.empty(n, dtype=torch.int32, device="cuda")
+    core = torch.empty(n, dtype=torch.uint8, device="cuda")
+    ctx = G.Context(0)
+    best = [1e9, 1e9]
+    for call in range(8):
+        for k, fn in enumerate((lambda: ctx.dbscan(t, 60, 5), lambda: ctx.dbscan_noalloc(t, 60, 5, lab, core))):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            fn()
+            torch.cuda.synchronize()
+            if call:
+                best[k] = min(best[k], time.perf_counter() - t0)
+    ctx.close()
+    assert best[0] < 2 * best[1], best
