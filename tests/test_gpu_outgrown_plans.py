@@ -46,12 +46,12 @@ def spread(width):
     return np.stack(np.unravel_index(flat, width), axis=1).astype(np.int64)
 
 
-def few_nodes():  # two keys in each of the first four dimensions, long in the last
-    return spread((2, 2, 2, 2, 1000))
+def few_nodes():  # two keys in each of the first two dimensions and the last: four nodes of level 2
+    return spread((2, 2, 60, 60, 2))
 
 
-def many_nodes():  # the same cells, seen from the other end: nodes by the thousand from level 2 on
-    return spread((1000, 2, 2, 2, 2))[:, [0, 4, 1, 2, 3]]
+def many_nodes():  # the same cells, the wide dimensions first: nodes by the thousand from level 2 on
+    return few_nodes()[:, [2, 3, 0, 1, 4]]
 
 
 def scattered():  # cells far from one another: lists of the own node alone
